@@ -519,7 +519,7 @@ static int launch_conv_band(int K, Group& g, int mode, hipStream_t st) {
 }
 
 int run_group(Group& g, int key, int K, int mode, hipStream_t st, hipEvent_t* ev,
-              bool prologue, bool finalize) {
+              bool prologue, bool finalize, bool chain) {
   int rc;
   auto mark = [&](int i) { return ev ? hipEventRecord(ev[i], st) : hipSuccess; };
   GL_HIP(mark(0));
@@ -561,7 +561,7 @@ int run_group(Group& g, int key, int K, int mode, hipStream_t st, hipEvent_t* ev
   GL_HIP(mark(3));
   if (mode != 2) return GL_OK;
   set_blocks(g, blocks_subpix);
-  if ((rc = launch_subpix_adj(key, g, st))) return rc;
+  if ((rc = chain ? launch_chain_adj(key, g, st) : launch_subpix_adj(key, g, st))) return rc;
   GL_HIP(mark(4));
   if (!finalize) return GL_OK;
   set_blocks(g, blocks_prologue);

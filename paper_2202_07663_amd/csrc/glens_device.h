@@ -96,6 +96,12 @@ GL_HD void decode_light(const float* th, LightC& L) {
   L.e1 = float(e1);
   L.e2 = float(e2);
   L.inv1me2 = float(den);
+  const double ire2 = 1.0 / (re * re);
+  L.as = float((1.0 + ee - 2.0 * e1) * den * ire2);
+  L.bs = float(-2.0 * e2 * den * ire2);
+  L.cs = float((1.0 + ee + 2.0 * e1) * den * ire2);
+  L.fls = float(double(kR2Floor) * ire2);
+  L.kqi = float(-(1.9992 * n - 0.3271) / n * double(th[6]));
   L.j11 = float(j11);
   L.j12 = float(j12);
   L.j22 = float(j22);
@@ -122,6 +128,8 @@ GL_HD void decode_mass(const float* th, int mass, int shear, PConst& c) {
     c.g1 = 0.0;
     c.g2 = 0.0;
   }
+  c.omg1 = 1.0 - c.g1;
+  c.opg1 = 1.0 + c.g1;
   const double ee = e1 * e1 + e2 * e2, eabs = sqrt(ee);
   const double B = theta_e * sqrt(1.0 - ee);
   c.t = t;
@@ -132,16 +140,22 @@ GL_HD void decode_mass(const float* th, int mass, int shear, PConst& c) {
   c.w2floor = 1e-12 * (1.0 + eabs) * (1.0 + eabs);
   c.epsabs = eabs;
   c.theta_e = float(theta_e);
-  c.tf = float(t);
   c.hp = float(1.0 - 0.5 * t);
   c.hm = float(-0.5 * t);
+  c.omt = float(1.0 - t);
   c.e1f = float(e1);
   c.e2f = float(e2);
+  c.eef = float(ee);
+  c.w2floorf = float(c.w2floor);
+  c.tlnb2 = float(c.tlnb * 1.4426950408889634);
+  c.l2b2 = float(2.0 * log(B) * 1.4426950408889634);
+  c.hb = float(0.5 * B);
+  c.tf = float(t);
   c.lnb = float(log(B));
   c.xcf = float(c.xc);
   c.ycf = float(c.yc);
-  c.w2floorf = float(c.w2floor);
-  c.tlnb2 = float(c.tlnb * 1.4426950408889634);
+  c.iebr = eabs >= kSxClosedMin ? float(e1 / ee) : 0.f;
+  c.iebi = eabs >= kSxClosedMin ? float(e2 / ee) : 0.f;
   c.tfac = float(t / (2.0 * (1.0 - ee)));
   c.mj11 = float(j11);
   c.mj12 = float(j12);
@@ -166,8 +180,6 @@ GL_HD void decode_mass(const float* th, int mass, int shear, PConst& c) {
   } else {
     c.sr = c.si = 0.0;
   }
-  c.iebr = eabs >= kSxClosedMin ? float(e1 / ee) : 0.f;
-  c.iebi = eabs >= kSxClosedMin ? float(e2 / ee) : 0.f;
 }
 
 // Series ratio c_n / c_{n-1} = (2n - 2 + t) / (2n + 2 - t) and the increment of
@@ -377,6 +389,7 @@ GL_HD void decode_lights_lane(const float* th, int mass, int shear, int lens_lig
   if (q == 0) {
     c.beta = float(beta);
     c.inv_beta = float(1.0 / beta);
+    c.rt2_ib = float(1.4142135623730951 / beta);
   }
   const double f = 0.56418958354775628 / beta;  // 1 / (beta sqrt(pi))
   int n1, n2;
@@ -407,6 +420,8 @@ __device__ __forceinline__ float log2_f32(float x) { return __builtin_amdgcn_log
 __host__ inline float log2_f32(float x) { return log2f(x); }
 __device__ __forceinline__ float rcp_f32(float x) { return __builtin_amdgcn_rcpf(x); }
 __host__ inline float rcp_f32(float x) { return 1.0f / x; }
+__device__ __forceinline__ float rsq_f32(float x) { return __builtin_amdgcn_rsqf(x); }
+__host__ inline float rsq_f32(float x) { return 1.0f / sqrtf(x); }
 constexpr float kLn2f = 0.69314718055994531f;
 constexpr float kLog2e = 1.44269504088896341f;
 
@@ -480,16 +495,6 @@ GL_HD Cx cconj(Cx a) { return {a.r, -a.i}; }
 GL_HD Cx cmuli(Cx a) { return {-a.i, a.r}; }  // i a
 GL_HD float cdot(Cx g, Cx v) { return g.r * v.r + g.i * v.i; }  // real dot product
 
-// The lens quantities of one sub-pixel that the adjoint uses (FP32).
-struct MassState {
-  float sdx, sdy;     // beta - x_s (source offset)
-  Cx z, w, u2, X;     // z, w, w^2/|w|^2, X = conj(eps) u2
-  float lnw2;         // ln |w|^2 (floored)
-  float A;            // B^t |w|^-t
-  Cx S, XSX, U2SX, St;  // S_t(X), X dS/dX, u2 dS/dX, dS/dt
-  Cx alpha;
-};
-
 // EPL / SIE deflection plus shear at image position (x, y), in FP64: returns beta - x_s with
 // beta = x - alpha - alpha_ext. cs: the particle's series coefficients c.c (the kernels pass
 // a copy staged in LDS).
@@ -551,148 +556,113 @@ GL_HD void ray_trace(const PConst& c, const double* __restrict__ cs,
   sdy = float(y - ai - (c.g2 * x - c.g1 * y) - c.sys);
 }
 
-// The lens quantities the adjoint needs, in FP32: z, w, u2, X, ln|w|^2, A, S, X dS/dX,
-// u2 dS/dX, dS/dt, alpha. (sdx, sdy) is beta - x_s of the forward pass's FP64 ray trace (SysDesc::beta): the
-// light profiles and their derivatives are evaluated there (an FP32 ray trace moves it by
-// ~3e-7 arcsec, which shows at 2e-3 in the gradient of a vector far from the posterior). The
-// rest only enters the Jacobian d(beta)/d(theta) and the local derivatives, whose tolerance
-// (a relative 1e-3 on the gradient) is far above FP32 rounding:
-//   alpha = x - alpha_ext - x_s - (beta - x_s), formed from the kept offset (FP64 up to the
-//         last subtraction), and S = alpha / (A w), so the value series is not run again
-//         (a sub-pixel whose |w|^2 hit the floor, where alpha carries no S, sums it);
-//   dS/dX by the closed form of the identity below for |eps| >= kSxClosedMin (its numerator
-//         cancels like |eps|, costing at most a relative 1e-6 / 0.02), by its series below;
-//   dS/dt (EPL) by its series; the series run over the FP32-resolution length nterms_d;
-//   log and exp are the hardware ones.
-// |w|^2 is kept at or above the floor so that every quantity stays finite; the particle's
-// floored sub-pixel itself (c.fl_*) takes its mass terms from the prologue's exact
-// derivatives instead (the caller passes a zero weight here).
-// ncs / dcs: the particle's c.nc / c.dc (staged in LDS). SXS = false: the caller has checked
-// that |eps| >= kSxClosedMin, so dS/dX takes the closed form without a test.
-template <int MASS, bool SXS = true>
-__device__ __forceinline__ void mass_jacobian_f32(const PConst& c, const float* __restrict__ ncs,
-                                                  const float* __restrict__ dcs, double x,
-                                                  double y, float sdx, float sdy, MassState& m) {
-  const float zr = float(x) - c.xcf, zi = float(y) - c.ycf;
+// The mass terms of one sub-pixel, added to acc (FP32): z the offset from the lens centre, alpha
+// the deflection, g = d s / d beta weighted by the pixel adjoint. alpha comes from the kept
+// beta - x_s of the forward pass's FP64 ray trace (an FP32 ray trace would move it by ~3e-7
+// arcsec, which shows at 2e-3 in the gradient of a vector far from the posterior); the rest
+// only enters derivatives, whose tolerance (a relative 1e-3 on the gradient) is far above FP32
+// rounding. With w = z - eps conj(z), A = B^t |w|^-t and alpha = A w S_t(X), X = conj(eps) w^2 /
+// |w|^2, no series is summed for the derivatives in z and eps:
+//   * alpha_z = kappa = (1 - t/2) A, a real number: the series obeys
+//       X (1 + X) dS/dX = (1 - t/2)(1 - S) - (t/2) X S
+//     (equal coefficients of (-X)^n for every n), which turns A ((1 - t/2) S + X S_X +
+//     X ((t/2) S + X S_X)), the derivative of the closed form, into (1 - t/2) A;
+//   * alpha has degree 1 - t in z, so z alpha_z + conj(z) alpha_zb = (1 - t) alpha gives
+//       Gamma = alpha_zb = ((1 - t) alpha - kappa z) z / |z|^2   (SIE: -kappa z^2 / |z|^2);
+//   * d alpha / d(eps, conj(eps)) are combinations of kappa, Gamma, z and alpha by
+//     per-particle constants, formed from sums over the sub-pixels in mass_sums. One of them is
+//     divided by |eps|, at a relative cost of 1e-7 / |eps|: for |eps| < kSxClosedMin its sum
+//     (slots A_M_WR, A_M_WI) is taken from the derivative series instead;
+//   * d alpha / dt = alpha (ln B - ln|w|^2 / 2) + A w S_t by its series (EPL), with the
+//     coefficients times -2 / ln 2 so that the sum runs over base-2 logarithms.
+// Series are summed by synthetic division at y = -X (ray_trace), four terms per trip (the length
+// rounded up, the padding coefficients are zero); |y|^2 = |eps|^2 is a constant of the particle.
+// dcs / ncs: the particle's c.dc (scaled) / c.nc staged in LDS.
+// GENERAL = false: the particle has no floored sub-pixel and |eps| >= kSxClosedMin. At a floored
+// sub-pixel everything is kept finite and the caller passes g = 0.
+template <int MASS, bool GENERAL>
+__device__ __forceinline__ void mass_adjoint(const PConst& c, const float* __restrict__ ncs,
+                                             const float* __restrict__ dcs, float zr, float zi,
+                                             float ar, float ai, Cx g, float* acc) {
   const float e1 = c.e1f, e2 = c.e2f;
-  const float wr = zr - e1 * zr - e2 * zi, wi = zi - e2 * zr + e1 * zi;
-  const float w2 = fmaxf(wr * wr + wi * wi, c.w2floorf);
-  const float inv_w2 = rcp_f32(w2);
-  const float u2r = (wr * wr - wi * wi) * inv_w2, u2i = 2.0f * wr * wi * inv_w2;
-  const float Xr = e1 * u2r + e2 * u2i, Xi = e1 * u2i - e2 * u2r;
-  const float l2w2 = log2_f32(w2);
-  m.sdx = sdx;
-  m.sdy = sdy;
-  m.z = {zr, zi};
-  m.w = {wr, wi};
-  m.u2 = {u2r, u2i};
-  m.X = {Xr, Xi};
-  m.lnw2 = kLn2f * l2w2;
-  // A = B^t |w|^-t = 2^(t log2 B - (t/2) log2 |w|^2) (SIE: t = 1)
-  const float A = exp2_f32(fmaf(-0.5f * c.tf, l2w2, c.tlnb2));
-  const float ar = float(x - (c.g1 * x + c.g2 * y) - c.sxs) - sdx;
-  const float ai = float(y - (c.g2 * x - c.g1 * y) - c.sys) - sdy;
-  // series by synthetic division at y = -X (ray_trace): dS/dt (EPL) and, for small |eps|,
-  // dS/dy
-  const float yr = -Xr, yi = -Xi, r2 = 2.0f * yr, yy = yr * yr + yi * yi;
-  const bool sx_series = SXS && c.epsabs < kSxClosedMin;
-  // four terms per trip, the length rounded up to a multiple of four (the padding
-  // coefficients are zero): the LDS reads of a trip go out together, which at this kernel's
-  // three waves per SIMD was measured faster than two terms per trip. dS/dt (EPL) here, dS/dy
-  // (small |eps| only) below in a loop of its own, so that the common path carries no state
-  // of the other.
-  const int nd4 = (c.nterms_d + 3) & ~3;
-  float t1 = 0.f, t2 = 0.f;
-  if (MASS == 1) {
-    for (int n0 = nd4 - 4; n0 >= 0; n0 -= 4) {
-#pragma unroll
-      for (int q = 3; q >= 0; --q) {
-        const float t0 = fmaf(r2, t1, fmaf(-yy, t2, dcs[n0 + q]));
-        t2 = t1;
-        t1 = t0;
-      }
-    }
+  const float wr = fmaf(-e2, zi, fmaf(-e1, zr, zr)), wi = fmaf(-e2, zr, fmaf(e1, zi, zi));
+  const float wr2 = wr * wr, zr2 = zr * zr;
+  float w2 = fmaf(wi, wi, wr2), z2 = fmaf(zi, zi, zr2);
+  if (GENERAL) {
+    w2 = fmaxf(w2, c.w2floorf);
+    z2 = fmaxf(z2, kR2Floor);
   }
-  // S = alpha conj(w) / (A |w|^2)
-  const float r = rcp_f32(A * w2);
-  const float Sr = (ar * wr + ai * wi) * r;
-  const float Si = (ai * wr - ar * wi) * r;
-  if (sx_series) {
-    float d1 = 0.f, d2 = 0.f;
-    for (int n0 = nd4 - 4; n0 >= 0; n0 -= 4) {
-#pragma unroll
-      for (int q = 3; q >= 0; --q) {
-        const float d0 = fmaf(r2, d1, fmaf(-yy, d2, ncs[n0 + q]));
-        d2 = d1;
-        d1 = d0;
-      }
-    }
-    const Cx SX = {-fmaf(-yr, d2, d1), -yi * d2};  // dS/dX = -dS/dy
-    m.XSX = cmul(m.X, SX);
-    m.U2SX = cmul(m.u2, SX);
+  const float iz2 = rcp_f32(z2);
+  const float gar = fmaf(g.i, ai, g.r * ar);  // Re(gb alpha)
+  float kap, A = 0.f, l2w2 = 0.f, Gr, Gi;
+  if (MASS == 1) {
+    l2w2 = log2_f32(w2);
+    A = exp2_f32(fmaf(c.hm, l2w2, c.tlnb2));
+    kap = c.hp * A;
+    const float vr = fmaf(c.omt, ar, -kap * zr), vi = fmaf(c.omt, ai, -kap * zi);
+    const float ur = zr * iz2, ui = zi * iz2;
+    Gr = fmaf(vr, ur, -vi * ui);
+    Gi = fmaf(vr, ui, vi * ur);
   } else {
-    // S = sum c_n (-X)^n with c_n / c_(n-1) = (2n - 2 + t) / (2n + 2 - t) obeys
-    //   X (1 + X) dS/dX = (1 - t/2)(1 - S) - (t/2) X S
-    // (as series: the coefficient of (-X)^n on both sides agrees for every n; for the SIE,
-    // t = 1, it is S_X = (1/(1+X) - S) / (2X), which the closed form atan(zeta)/zeta obeys),
-    // so X dS/dX is the right side over 1 + X, and u2 dS/dX = X dS/dX / conj(eps), as
-    // X = conj(eps) u2. The numerator cancels like |X| = |eps|, so this is used for
-    // |eps| >= kSxClosedMin only.
-    const float xsr = Xr * Sr - Xi * Si, xsi = Xr * Si + Xi * Sr;
-    const float numr = c.hp * (1.0f - Sr) + c.hm * xsr;
-    const float numi = -c.hp * Si + c.hm * xsi;
-    const float opr = 1.0f + Xr, inv = rcp_f32(opr * opr + Xi * Xi);
-    m.XSX = {(numr * opr + numi * Xi) * inv, (numi * opr - numr * Xi) * inv};
-    m.U2SX = cmul(m.XSX, Cx{c.iebr, c.iebi});
+    kap = c.hb * rsq_f32(w2);
+    A = 2.0f * kap;
+    const float f = -kap * iz2;
+    Gr = f * fmaf(-zi, zi, zr2);
+    Gi = (2.0f * f) * (zr * zi);
   }
-  m.St = MASS == 1 ? Cx{fmaf(-yr, t2, t1), yi * t2} : Cx{0.f, 0.f};
-  m.A = A;
-  m.S = {Sr, Si};
-  m.alpha = {ar, ai};
-}
-
-// Adds the mass-parameter terms g . d alpha/d(theta) to acc, with g = d s / d beta (already
-// weighted by the pixel adjoint); beta = x - alpha - alpha_ext, so the signs are applied at
-// the mapping. For a complex derivative D, g . D = Re(gb D) with gb = conj(g), and every
-// derivative is contracted with gb as soon as it is formed:
-//   with aw = d alpha/dw = A P1 and awb = d alpha/d conj(w) = A u2 P2 (eps fixed),
-//   U = gb aw, V = gb awb;
-//   d alpha/dz = aw - conj(eps) awb, d alpha/d conj(z) = awb - eps aw, and with x = z +
-//   conj z, y = i (z - conj z):
-//     g . d alpha/dx = Re((1 - eps) U + (1 - conj eps) V) = (1 - e1) Sp + e2 Dm,
-//     g . d alpha/dy = -Im((1 + eps) U - (1 + conj eps) V) = -(1 + e1) Dm - e2 Sp,
-//   Sp = Re U + Re V, Dm = Im U - Im V;
-//   d alpha/d eps = -tfac conj(eps) alpha - conj(z) aw,
-//   d alpha/d conj(eps) = -tfac eps alpha - z awb + A w u2 S_X (A depends on |eps|^2, X on
-//   conj(eps)); with eps = e1 + i e2 and W = gb A w u2 S_X:
-//     g . d alpha/de1 = -2 tfac e1 Re(gb alpha) - Re(z) Sp - Im(z) Dm + Re W,
-//     g . d alpha/de2 = -2 tfac e2 Re(gb alpha) + Re(z) Dm - Im(z) Sp + Im W;
-//   d alpha/dt = alpha (ln B - ln|w|^2 / 2) + A w S_t.
-template <int MASS>
-GL_HD void mass_adjoint(const PConst& c, const MassState& m, float x, float y, Cx g, float* acc) {
-  const Cx XSX = m.XSX;
-  const Cx P1 = cadd(cscale(m.S, c.hp), XSX);  // (1 - t/2) S + X S_X
-  const Cx P2 = csub(cscale(m.S, c.hm), XSX);  // -(t/2) S - X S_X
-  const Cx gA = {g.r * m.A, -g.i * m.A};  // A gb
-  const Cx U = cmul(gA, P1);
-  const Cx V = cmul(gA, cmul(m.u2, P2));
-  const float Sp = U.r + V.r, Dm = U.i - V.i;
-  const float e1 = c.e1f, e2 = c.e2f;
-  const float ga = cdot(g, m.alpha);  // Re(gb alpha)
-  const Cx gAw = cmul(gA, m.w);
-  const Cx W = cmul(gAw, m.U2SX);
-  acc[A_M_ALPHA] += ga;
-  if (MASS == 1) {
-    const float lt = fmaf(-0.5f, m.lnw2, c.lnb);  // ln B - ln|w|^2 / 2
-    acc[A_M_T] += fmaf(lt, ga, gAw.r * m.St.r - gAw.i * m.St.i);
+  const float kr = kap * g.r, ki = kap * g.i;
+  const float hxr = fmaf(g.i, Gi, fmaf(g.r, Gr, kr));
+  const float hxi = fmaf(-g.i, Gr, fmaf(g.r, Gi, ki));
+  acc[A_M_GAR] += gar;
+  acc[A_M_GAI] = fmaf(-g.i, ar, fmaf(g.r, ai, acc[A_M_GAI]));
+  acc[A_M_X] += hxr;
+  acc[A_M_Y] += hxi;
+  acc[A_M_KRR] = fmaf(kr, zr, acc[A_M_KRR]);
+  acc[A_M_KRI] = fmaf(kr, zi, acc[A_M_KRI]);
+  acc[A_M_KIR] = fmaf(ki, zr, acc[A_M_KIR]);
+  acc[A_M_KII] = fmaf(ki, zi, acc[A_M_KII]);
+  acc[A_M_HZR] = fmaf(-hxi, zi, fmaf(hxr, zr, acc[A_M_HZR]));
+  acc[A_M_HZI] = fmaf(hxi, zr, fmaf(hxr, zi, acc[A_M_HZI]));
+  acc[A_M_G1] = fmaf(-g.i, zi, fmaf(g.r, zr, acc[A_M_G1]));
+  acc[A_M_G2] = fmaf(g.i, zr, fmaf(g.r, zi, acc[A_M_G2]));
+  const bool sx = GENERAL && c.epsabs < kSxClosedMin;
+  if (MASS == 1 || sx) {
+    const float iw2 = rcp_f32(w2);
+    const float u2r = fmaf(-wi, wi, wr2) * iw2, u2i = 2.0f * wr * wi * iw2;
+    const float Xr = e1 * u2r + e2 * u2i, Xi = e1 * u2i - e2 * u2r;
+    const float r2 = -2.0f * Xr, yy = c.eef;
+    const float gwr = fmaf(g.i, wi, g.r * wr), gwi = fmaf(g.r, wi, -g.i * wr);  // gb w
+    const int nd4 = (c.nterms_d + 3) & ~3;
+    if (MASS == 1) {
+      float t1 = 0.f, t2 = 0.f;
+      for (int n0 = nd4 - 4; n0 >= 0; n0 -= 4) {
+#pragma unroll
+        for (int q = 3; q >= 0; --q) {
+          const float t0 = fmaf(r2, t1, fmaf(-yy, t2, dcs[n0 + q]));
+          t2 = t1;
+          t1 = t0;
+        }
+      }
+      // Re(gb w S_t), S_t = t1 + conj(X) t2
+      const float p = fmaf(gwr, t1, t2 * fmaf(gwi, Xi, gwr * Xr));
+      acc[A_M_T] = fmaf(A, p, fmaf(l2w2 - c.l2b2, gar, acc[A_M_T]));
+    }
+    if (sx) {
+      float d1 = 0.f, d2 = 0.f;
+      for (int n0 = nd4 - 4; n0 >= 0; n0 -= 4) {
+#pragma unroll
+        for (int q = 3; q >= 0; --q) {
+          const float d0 = fmaf(r2, d1, fmaf(-yy, d2, ncs[n0 + q]));
+          d2 = d1;
+          d1 = d0;
+        }
+      }
+      const Cx SX = {-fmaf(Xr, d2, d1), Xi * d2};  // dS/dX = -dS/dy
+      const Cx W = cmul(Cx{A * gwr, A * gwi}, cmul(Cx{u2r, u2i}, SX));
+      acc[A_M_WR] += W.r;
+      acc[A_M_WI] += W.i;
+    }
   }
-  const float k = -2.0f * c.tfac;
-  acc[A_M_E1] += fmaf(k * e1, ga, W.r - m.z.r * Sp - m.z.i * Dm);
-  acc[A_M_E2] += fmaf(k * e2, ga, W.i + m.z.r * Dm - m.z.i * Sp);
-  acc[A_M_X] += fmaf(1.0f - e1, Sp, e2 * Dm);
-  acc[A_M_Y] -= fmaf(1.0f + e1, Dm, e2 * Sp);
-  acc[A_M_G1] += g.r * x - g.i * y;
-  acc[A_M_G2] += g.r * y + g.i * x;
 }
 
 // Elliptical Sersic intensity at offset (dx, dy) from its centre.
@@ -705,33 +675,27 @@ GL_HD float sersic_fwd(const LightC& L, float dx, float dy) {
   return L.i0 * exp2_f32(fmaf(-L.bnl, rho, L.bnl));
 }
 
-// Accumulator terms (weight sb) and the weighted sb dI/d(dx, dy). With the half gradient of
-// R^2, (px, py) = (qa dx + qb dy / 2, qb dx / 2 + qc dy), R^2 = dx px + dy py and
-// dR^2/d(dx, dy) = 2 (px, py); dI/dR^2 = -I b_n rho / (2 n R^2), so
-// 2 sb dI/dR^2 = sb I rho (-b_n / n) / R^2 =: sIQ2 and sb dI/d(dx, dy) = sIQ2 (px, py).
-// Slots: L_E: sb E; L_RHO: sb I rho; L_RHO1: sb I (rho - 1); L_RHOLN: sb I rho log2(rho)
-// (ln 2 is applied at the mapping); L_Q1, L_Q2: the two eccentricity terms times
-// 2 sb dI/dR^2 (the 1/2 is applied at the mapping).
-GL_HD void sersic_adj(const LightC& L, float dx, float dy, float sb, float* acc, float& gdx,
-                      float& gdy) {
-  const float px = fmaf(L.qa, dx, L.qbh * dy), py = fmaf(L.qc, dy, L.qbh * dx);
-  float q = fmaf(dx, px, dy * py);
-  const bool fl = q < kR2Floor;
-  q = fl ? kR2Floor : q;
-  const float l2rho = fmaf(log2_f32(q), L.inv2n, -L.l2re_n);
+// Accumulator terms (weight sb) of the lens light or the source, and s of LightSlot. With the
+// half gradient (px, py) = (as dx + bs dy, bs dx + cs dy) of Q = R^2 / R_eff^2 = dx px + dy py,
+// log2(rho) = log2(Q) / (2n) and dI/d(dx, dy) = s (px, py), s = I0 (-b_n / n) E rho / Q. The
+// sums over the ellipticity terms are combinations of s dx^2, s dx dy and s dy^2 (R^2 itself is
+// one), so only these three are kept, and I0 multiplies the sums instead of their terms.
+__device__ __forceinline__ float sersic_adj(const LightC& L, float dx, float dy, float px,
+                                            float py, float sb, float* acc) {
+  const float q0 = fmaf(dx, px, dy * py);
+  const float q = fmaxf(q0, L.fls);  // a NaN offset has made log L non-finite already
+  const float l2rho = log2_f32(q) * L.inv2n;
   const float rho = exp2_f32(l2rho);
-  const float sE = sb * exp2_f32(fmaf(-L.bnl, rho, L.bnl));
-  const float sI = L.i0 * sE, sIr = sI * rho;
-  const float sIQ2 = fl ? 0.0f : sIr * L.kq * rcp_f32(q);
-  gdx = sIQ2 * px;
-  gdy = sIQ2 * py;
-  const float r2q = fmaf(dx, dx, fmaf(dy, dy, q));
+  const float sE = sb * exp2_f32(fmaf(-L.bnl, rho, L.bnl)), sEr = sE * rho;
+  const float s = q0 < L.fls ? 0.0f : sEr * L.kqi * rcp_f32(q);
   acc[L_E] += sE;
-  acc[L_RHO] += sIr;
-  acc[L_RHO1] += sIr - sI;
-  acc[L_RHOLN] = fmaf(sIr, l2rho, acc[L_RHOLN]);
-  acc[L_Q1] = fmaf(sIQ2, fmaf(L.e1, r2q, fmaf(dy, dy, -dx * dx)), acc[L_Q1]);
-  acc[L_Q2] = fmaf(sIQ2, fmaf(L.e2, r2q, -2.0f * dx * dy), acc[L_Q2]);
+  acc[L_RHO] += sEr;
+  acc[L_RHOLN] = fmaf(sEr, l2rho, acc[L_RHOLN]);
+  const float sx = s * dx, sy = s * dy;
+  acc[L_XX] = fmaf(sx, dx, acc[L_XX]);
+  acc[L_XY] = fmaf(sx, dy, acc[L_XY]);
+  acc[L_YY] = fmaf(sy, dy, acc[L_YY]);
+  return s;
 }
 
 // Scaled Hermite polynomials g_n(u) = H_n(u) / 2^n (H_n the physicists' polynomials):
@@ -776,47 +740,67 @@ GL_HD float shapelet_fwd(const PConst& c, float sdx, float sdy, const float* shp
   return exp2_f32(-0.5f * kLog2e * (u * u + v * v)) * U;
 }
 
-// Shapelet accumulator terms and the weighted derivatives sb dI/d(beta_x, beta_y), using
-// g_n' = n g_(n-1) for the scaled Hermite polynomials:
-//   dI/du = G (sum_n1 n1 g_(n1-1)(u) T_n1 - u U),
-//   dI/dv = G (sum_n1 g_n1(u) Tv_n1 - v U),  Tv_n1 = sum_n2 c'_(n1,n2) n2 g_(n2-1)(v),
-//   dI/dc_k = G g_n1(u) g_n2(v) r_n1 r_n2 / (beta sqrt(pi)) (the factor r_n1 r_n2 /
-//   (beta sqrt(pi)) is applied when the accumulators are mapped onto the gradient).
-// The u-polynomials are taken times sg = sb G, so every sum over them carries the weight:
-// U, Uu and Uv below are sb G times the sums above, and sb I = U.
+// Factors 2^(-n/2) that take a coefficient of g_n1(u) g_n2(v), n = n1 + n2, to one of
+// He_n1(x) He_n2(y) (shapelet_adj).
+constexpr float kHeScale[kMaxNmax + 1] = {1.0f, 0.70710678118654752f, 0.5f, 0.35355339059327376f,
+                                          0.25f, 0.17677669529663688f, 0.125f,
+                                          0.08838834764831844f, 0.0625f};
+
+// Shapelet accumulator terms and the weighted derivatives sb dI/d(beta_x, beta_y). They run
+// over the probabilists' polynomials He_n(x) = 2^(n/2) g_n(u), x = sqrt(2) u:
+// He_(n+1) = x He_n - n He_(n-1) and He_n' = n He_(n-1), so that the products n He_(n-1) serve
+// the recurrence and the derivative sums. he: the coefficients c'_k 2^(-n/2).
+//   dI/dx = G (sum_n1 n1 He_(n1-1)(x) T_n1 - x U / 2),
+//   dI/dy = G (sum_n1 He_n1(x) Tv_n1 - y U / 2),  Tv_n1 = sum_n2 he_(n1,n2) n2 He_(n2-1)(y),
+//   dI/dc_k = G He_n1(x) He_n2(y) / (sqrt(n1! n2!) beta sqrt(pi)) (the factor is applied when
+//   the accumulators are mapped onto the gradient, and so is -1 / beta of the beta sum).
+// The x-polynomials are taken times sg = sb G, so every sum over them carries the weight:
+// U, Ux and Uy below are sb G times the sums above, and sb I = U.
 template <int NMAX>
-GL_HD void shapelet_adj(const PConst& c, float sdx, float sdy, const float* shp, float sb,
+GL_HD void shapelet_adj(const PConst& c, float sdx, float sdy, const float* he, float sb,
                         float* acc, float& gbx, float& gby) {
-  const float ib = c.inv_beta;
-  const float u = sdx * ib, v = sdy * ib;
-  const float sg = sb * exp2_f32(-0.5f * kLog2e * (u * u + v * v));
-  float hu[NMAX + 1], hv[NMAX + 1];
-  hermite<NMAX>(u, hu, sg);
-  hermite<NMAX>(v, hv);
-  float U = 0.f, Uu = 0.f, Uv = 0.f;
+  const float ib = c.rt2_ib;
+  const float x = sdx * ib, y = sdy * ib;
+  const float sg = sb * exp2_f32(-0.25f * kLog2e * fmaf(x, x, y * y));
+  float hx[NMAX + 2], hy[NMAX + 2];  // He_n, hx times sg
+  float ex[NMAX + 2], ey[NMAX + 2];  // n He_(n-1), ex times sg
+  hx[0] = sg;
+  hy[0] = 1.f;
+  ex[0] = ey[0] = 0.f;
+#pragma unroll
+  for (int n = 0; n < NMAX; ++n) {
+    ex[n + 1] = n == 0 ? hx[0] : float(n + 1) * hx[n];
+    ey[n + 1] = n == 0 ? 1.f : float(n + 1) * hy[n];
+    hx[n + 1] = n == 0 ? x * hx[0] : fmaf(x, hx[n], -ex[n]);
+    hy[n + 1] = n == 0 ? y : fmaf(y, hy[n], -ey[n]);
+  }
+  float U = 0.f, Ux = 0.f, Uy = 0.f;
 #pragma unroll
   for (int n1 = 0; n1 <= NMAX; ++n1) {
-    // g_0(v) = 1: T starts from its n2 = 0 term (no addition of a zero)
-    float T = shp[shp_index(n1, 0)], Tv = 0.f;
+    // He_0 = 1: T and Tv start from their first terms (no addition of a zero)
+    float T = he[shp_index(n1, 0)], Tv = 0.f;
 #pragma unroll
     for (int n2 = 1; n2 <= NMAX - n1; ++n2) {
-      const float ck = shp[shp_index(n1, n2)];
-      T = fmaf(ck, hv[n2], T);
-      Tv = n2 == 1 ? ck : fmaf(ck, float(n2) * hv[n2 - 1], Tv);
+      const float ck = he[shp_index(n1, n2)];
+      T = fmaf(ck, hy[n2], T);
+      Tv = n2 == 1 ? ck : fmaf(ck, ey[n2], Tv);
     }
-    U = n1 == 0 ? hu[0] * T : fmaf(hu[n1], T, U);
-    if (n1 < NMAX) Uv = n1 == 0 ? hu[0] * Tv : fmaf(hu[n1], Tv, Uv);
-    if (n1 > 0) Uu = n1 == 1 ? hu[0] * T : fmaf(float(n1) * hu[n1 - 1], T, Uu);
+    U = n1 == 0 ? hx[0] * T : fmaf(hx[n1], T, U);
+    if (n1 < NMAX) Uy = n1 == 0 ? hx[0] * Tv : fmaf(hx[n1], Tv, Uy);
+    if (n1 > 0) Ux = n1 == 1 ? ex[1] * T : fmaf(ex[n1], T, Ux);
   }
 #pragma unroll
-  for (int n1 = 0; n1 <= NMAX; ++n1)
+  for (int n1 = 0; n1 <= NMAX; ++n1) {
+    acc[A_SHP_C + shp_index(n1, 0)] += hx[n1];
 #pragma unroll
-    for (int n2 = 0; n2 <= NMAX - n1; ++n2)
-      acc[A_SHP_C + shp_index(n1, n2)] = fmaf(hu[n1], hv[n2], acc[A_SHP_C + shp_index(n1, n2)]);
-  const float Iu = Uu - u * U, Iv = Uv - v * U;  // sb dI/du, sb dI/dv
-  acc[A_SHP_BETA] += (-U - u * Iu - v * Iv) * ib;
-  gbx = Iu * ib;
-  gby = Iv * ib;
+    for (int n2 = 1; n2 <= NMAX - n1; ++n2)
+      acc[A_SHP_C + shp_index(n1, n2)] = fmaf(hx[n1], hy[n2], acc[A_SHP_C + shp_index(n1, n2)]);
+  }
+  const float Uh = 0.5f * U;
+  const float Ix = fmaf(-x, Uh, Ux), Iy = fmaf(-y, Uh, Uy);  // sb dI/dx, sb dI/dy
+  acc[A_SHP_BETA] += fmaf(y, Iy, fmaf(x, Ix, U));
+  gbx = Ix * ib;
+  gby = Iy * ib;
 }
 
 // d(source Sersic + shapelets)/d(beta) at offset (sdx, sdy) from the source centre, in FP64
@@ -863,37 +847,92 @@ GL_HD void source_light_grad(const PConst& c, int nmax, double sdx, double sdy, 
 // ------------------------------------------------------------------------------------------
 // Accumulators -> d logL / d theta in the parameter order of gl.h. Returns d.
 // ------------------------------------------------------------------------------------------
-GL_HD void light_grad(const LightC& L, const double* a, float* g) {
-  g[0] = float(a[L_RHO] * L.bn / (double(L.n) * L.re));                 // R_eff
-  g[1] = float(-1.9992 * a[L_RHO1] + L.bn / double(L.n) * kLn2 * a[L_RHOLN]);  // n
-  const double ge1 = L.inv1me2 * a[L_Q1], ge2 = L.inv1me2 * a[L_Q2];
-  g[2] = float(L.j11 * ge1 + L.j12 * ge2);                               // eps1
-  g[3] = float(L.j12 * ge1 + L.j22 * ge2);                               // eps2
-  g[4] = float(-a[L_DX]);                                                // x
-  g[5] = float(-a[L_DY]);                                                // y
-  g[6] = float(a[L_E]);                                                  // I0
+// offsets: the centre slots hold s dx, s dy (lens light) instead of the gradient itself (source).
+GL_HD void light_grad(const LightC& L, const double* a, bool offsets, float* g) {
+  const double i0 = L.i0, n = L.n, re2 = double(L.re) * L.re;
+  const double rho = i0 * a[L_RHO], rho1 = i0 * (a[L_RHO] - a[L_E]);
+  g[0] = float(rho * L.bn / (n * L.re));                                       // R_eff
+  g[1] = float(-1.9992 * rho1 + L.bn / n * kLn2 * i0 * a[L_RHOLN]);            // n
+  // sum s R^2 / R_eff^2 (as, bs, cs) and the two eccentricity sums, over R_eff^2
+  const double xx = a[L_XX] / re2, xy = a[L_XY] / re2, yy = a[L_YY] / re2;
+  const double r2q = xx + yy + re2 * (L.as * xx + 2.0 * L.bs * xy + L.cs * yy);
+  const double ge1 = L.inv1me2 * (L.e1 * r2q + yy - xx);
+  const double ge2 = L.inv1me2 * (L.e2 * r2q - 2.0 * xy);
+  g[2] = float(L.j11 * ge1 + L.j12 * ge2);                                     // eps1
+  g[3] = float(L.j12 * ge1 + L.j22 * ge2);                                     // eps2
+  const double dx = a[L_DX], dy = a[L_DY];
+  g[4] = float(offsets ? -(L.as * dx + L.bs * dy) : -dx);                      // x
+  g[5] = float(offsets ? -(L.bs * dx + L.cs * dy) : -dy);                      // y
+  g[6] = float(a[L_E]);                                                        // I0
 }
 
-GL_HD int map_gradient(const PConst& c, const double* a, int mass, int shear, int lens_light,
-                       int nmax, float* gr) {
+// Sums of g . d alpha/d(theta) over the sub-pixels, from the accumulators a (mass_adjoint):
+// gb alpha, and with K = kappa gb, H = gb Gamma and Hx = H + kappa g the sums
+//   S1 = K z, S2 = K conj(z), S3 = H z = Hx z - kappa g z,
+//   S4 = H conj(z) = (1 - t) gb alpha - K z  (Gamma conj(z) = (1 - t) alpha - kappa z).
+// aw = d alpha/dw and awb = d alpha/d conj(w) at fixed eps solve kappa = aw - conj(eps) awb,
+// Gamma = awb - eps aw, so (1 - |eps|^2)(aw, awb) = (kappa + conj(eps) Gamma, Gamma + eps kappa);
+//   d alpha/d eps = -tfac conj(eps) alpha - conj(z) aw,
+//   d alpha/d conj(eps) = -tfac eps alpha - z awb + (w aw - (1 - t/2) alpha) / conj(eps),
+// tfac = t / (2 (1 - |eps|^2)); the last term is A w u2 dS/dX (A depends on |eps|^2, X on
+// conj(eps); w aw = alpha (1 - t/2) + A w X S_X).
+struct MassSums {
+  double alpha, t, e1, e2, x, y, g1, g2;
+};
+GL_HD MassSums mass_sums(const PConst& c, const double* a) {
+  MassSums m;
+  const double e1 = c.e1, e2 = c.e2, ee = e1 * e1 + e2 * e2, oo = 1.0 / (1.0 - ee);
+  const double gar = a[A_M_GAR], gai = a[A_M_GAI];
+  const double s1r = a[A_M_KRR] + a[A_M_KII], s1i = a[A_M_KRI] - a[A_M_KIR];
+  const double s2r = a[A_M_KRR] - a[A_M_KII], s2i = -a[A_M_KRI] - a[A_M_KIR];
+  const double s3r = a[A_M_HZR] - s2r, s3i = a[A_M_HZI] + s2i;  // kappa g z = conj(S2)
+  const double omt = 1.0 - c.t;
+  const double s4r = omt * gar - s1r, s4i = omt * gai - s1i;
+  // sums of gb conj(z) aw, gb z awb, gb z aw
+  const double zbr = (s2r + e1 * s4r + e2 * s4i) * oo, zbi = (s2i + e1 * s4i - e2 * s4r) * oo;
+  const double zwr = (s3r + e1 * s1r - e2 * s1i) * oo, zwi = (s3i + e1 * s1i + e2 * s1r) * oo;
+  const double zar = (s1r + e1 * s3r + e2 * s3i) * oo, zai = (s1i + e1 * s3i - e2 * s3r) * oo;
+  double wr = a[A_M_WR], wi = a[A_M_WI];
+  if (!(c.epsabs < kSxClosedMin)) {  // (sum gb w aw - (1 - t/2) gb alpha) / conj(eps)
+    const double hp = 1.0 - 0.5 * c.t;
+    const double nr = zar - (e1 * zbr - e2 * zbi) - hp * gar;
+    const double ni = zai - (e1 * zbi + e2 * zbr) - hp * gai;
+    wr = (nr * e1 - ni * e2) / ee;
+    wi = (ni * e1 + nr * e2) / ee;
+  }
+  const double k = -c.t * oo;  // -2 tfac
+  m.alpha = gar;
+  m.t = -0.5 * kLn2 * a[A_M_T];
+  m.e1 = k * e1 * gar - zbr - zwr + wr;
+  m.e2 = k * e2 * gar + zbi - zwi + wi;
+  m.x = a[A_M_X];
+  m.y = a[A_M_Y];
+  const double gr = a[A_SRC + L_DX], gi = a[A_SRC + L_DY];  // sum g
+  m.g1 = a[A_M_G1] + c.xc * gr - c.yc * gi;
+  m.g2 = a[A_M_G2] + c.yc * gr + c.xc * gi;
+  return m;
+}
+
+GL_HD int map_gradient(const PConst& c, const MassSums& m, const double* a, int mass, int shear,
+                       int lens_light, int nmax, float* gr) {
   int j = 0;
-  gr[j++] = float(-double(c.t) / c.theta_e * a[A_M_ALPHA]);
-  if (mass == 1) gr[j++] = float(-a[A_M_T]);
-  gr[j++] = float(-(c.mj11 * a[A_M_E1] + c.mj12 * a[A_M_E2]));
-  gr[j++] = float(-(c.mj12 * a[A_M_E1] + c.mj22 * a[A_M_E2]));
-  gr[j++] = float(a[A_M_X]);
-  gr[j++] = float(a[A_M_Y]);
+  gr[j++] = float(-double(c.t) / c.theta_e * m.alpha);
+  if (mass == 1) gr[j++] = float(-m.t);
+  gr[j++] = float(-(c.mj11 * m.e1 + c.mj12 * m.e2));
+  gr[j++] = float(-(c.mj12 * m.e1 + c.mj22 * m.e2));
+  gr[j++] = float(m.x);
+  gr[j++] = float(m.y);
   if (shear) {
-    gr[j++] = float(-a[A_M_G1]);
-    gr[j++] = float(-a[A_M_G2]);
+    gr[j++] = float(-m.g1);
+    gr[j++] = float(-m.g2);
   }
   if (lens_light) {
-    light_grad(c.lens, a + A_LENS, gr + j);
+    light_grad(c.lens, a + A_LENS, true, gr + j);
     j += 7;
   }
-  light_grad(c.src, a + A_SRC, gr + j);
+  light_grad(c.src, a + A_SRC, false, gr + j);
   j += 7;
-  if (nmax >= 0) gr[j++] = float(a[A_SHP_BETA]);
+  if (nmax >= 0) gr[j++] = float(-double(c.inv_beta) * a[A_SHP_BETA]);
   return j;
 }
 
@@ -902,7 +941,8 @@ GL_HD int map_gradient(const PConst& c, const double* a, int mass, int shear, in
 GL_HD float shapelet_coef_grad(const PConst& c, const double* a, int q) {
   int n1, n2;
   shapelet_orders(q, n1, n2);
-  return float(a[A_SHP_C + q] * (double(c.inv_beta) * kInvSqrtPi) * hermite_scale(n1, n2));
+  return float(a[A_SHP_C + q] * (double(c.inv_beta) * kInvSqrtPi) *
+               (hermite_scale(n1, n2) * double(kHeScale[n1 + n2])));
 }
 
 }  // namespace glens

@@ -171,7 +171,7 @@ __device__ __forceinline__ void grad_move(const HmcArgs& a, float scale, int dri
 // per leapfrog step than finalize, kick/drift and prologue apart, with the same arithmetic.
 __global__ void __launch_bounds__(kHmcThreads) hmc_finalize_move_kernel(SysDesc s, HmcArgs a,
                                                                         float scale, int drift) {
-  finalize_particle(s, blockIdx.x);
+  finalize_particle<true>(s, blockIdx.x);
   __syncthreads();  // this chain's log L and gradient are written
   grad_move(a, scale, drift);
   if (!drift) return;
@@ -531,7 +531,7 @@ static int hmc_gradient(gl_hmc* h, float scale, int drift, hipStream_t st) {
   h->a.grad = m->ws.grad;
   h->a.theta = m->ws.theta;
   // the previous step's fused kernel decoded the current positions unless pc_ready is false
-  rc = run_group(g, subpix_key(c), c.K, 2, st, nullptr, !h->pc_ready, false);
+  rc = run_group(g, subpix_key(c), c.K, 2, st, nullptr, !h->pc_ready, false, true);
   h->pc_ready = false;
   if (rc) return rc;
   hipLaunchKernelGGL(hmc_finalize_move_kernel, dim3(h->C), dim3(kHmcThreads), 0, st, g.sys[0],

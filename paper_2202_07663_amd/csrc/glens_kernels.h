@@ -18,10 +18,10 @@
 #include "glens_device.h"
 #include "glens_fit_device.h"
 #include "glens_particle.h"
+#include "glens_sums.h"
 
 namespace glens {
 
-constexpr int kSubThreads = 256;
 constexpr int kConvThreads = 256;
 constexpr int kConvRows = 8;  // output rows per lane in the PSF pass
 constexpr int kConvMaxStrips = 8;  // strips per lane: (H/8 rounded up) * W <= 8 * 256
@@ -35,15 +35,6 @@ __global__ void __launch_bounds__(64) prologue_kernel(Group g) {
 // ------------------------------------------------------------------------------------------
 // sub-pixel forward: lanes own pixels, loop over the k x k sub-pixels
 // ------------------------------------------------------------------------------------------
-// Copies the particle's derivative-series coefficients to LDS (read uniformly by every lane).
-__device__ __forceinline__ void stage_series(const PConst& c, float* s_nc, float* s_dc) {
-  for (int n = threadIdx.x; n < kMaxTerms; n += blockDim.x) {
-    s_nc[n] = c.nc[n];
-    s_dc[n] = c.dc[n];
-  }
-  __syncthreads();
-}
-
 template <int MASS, int LL, int NMAX>
 __device__ __forceinline__ float surface_brightness(const PConst& c, const double* cs,
                                                     const double* s_pw, double x, double y,
@@ -715,114 +706,73 @@ constexpr int n_slots() {
   return NMAX < 0 ? A_SHP_BETA : A_SHP_C + (NMAX + 1) * (NMAX + 2) / 2;
 }
 
-constexpr int halved(int n) { return n > 1 ? n / 2 : 1; }
-
-// One step of the transposed butterfly below for a lane holding NV values (all indices
-// compile-time, so the values stay in registers).
-template <int NV>
-__device__ __forceinline__ void wave_sum_step(double* v, int off, int lane) {
-  if constexpr (NV > 1) {
-    const bool up = lane & off;
-#pragma unroll
-    for (int i = 0; i < NV / 2; ++i) {
-      const double send = up ? v[i] : v[i + NV / 2];
-      const double keep = up ? v[i + NV / 2] : v[i];
-      v[i] = keep + __shfl_xor(send, off, 64);
-    }
-  } else {
-    v[0] += __shfl_xor(v[0], off, 64);
-  }
-}
-
-// Wave sums of NS per-lane FP32 values, in FP64, written to out[0 .. NS). A transposed
-// butterfly: with the values padded to N (a power of two), at the step with lane offset o a
-// lane keeps one half of its values, sends the other half to lane ^ o and adds what it
-// receives, so each step halves the values a lane holds. Every sum pairs lanes in the same
-// order as a separate xor butterfly per value would, with about N shuffles instead of
-// 6 NS. The first step shuffles the FP32 values and adds them in FP64.
-template <int NS>
-__device__ __forceinline__ void wave_sums(const float* acc, double* out) {
-  constexpr int N = NS <= 32 ? 32 : (NS <= 64 ? 64 : 128);
-  static_assert(NS <= 128, "too many accumulators");
-  const int lane = threadIdx.x & 63;
-  double v[N / 2];
-  {
-    const bool up = lane & 32;
-#pragma unroll
-    for (int i = 0; i < N / 2; ++i) {
-      const float lo = i < NS ? acc[i] : 0.f, hi = i + N / 2 < NS ? acc[i + N / 2] : 0.f;
-      const float send = up ? lo : hi;
-      v[i] = double(up ? hi : lo) + double(__shfl_xor(send, 32, 64));
-    }
-  }
-  constexpr int n1 = N / 2, n2 = halved(n1), n3 = halved(n2), n4 = halved(n3), n5 = halved(n4);
-  wave_sum_step<n1>(v, 16, lane);
-  wave_sum_step<n2>(v, 8, lane);
-  wave_sum_step<n3>(v, 4, lane);
-  wave_sum_step<n4>(v, 2, lane);
-  wave_sum_step<n5>(v, 1, lane);
-  // lane l now holds value (l * N / 64) + i for i < N / 64 (N = 32: lanes 2q and 2q + 1
-  // both hold value q)
-  if (N >= 64) {
-#pragma unroll
-    for (int i = 0; i < N / 64; ++i) {
-      const int q = lane * (N / 64) + i;
-      if (q < NS) out[q] = v[i];
-    }
-  } else if ((lane & 1) == 0 && (lane >> 1) < NS) {
-    out[lane >> 1] = v[0];
-  }
-}
-
 // The sub-pixels of pixels [p0, p1) of one particle into the per-lane accumulators.
 // GENERAL = false: the particle has no floored sub-pixel and |eps| >= kSxClosedMin.
 template <int MASS, int LL, int NMAX, bool GENERAL>
 __device__ __forceinline__ void adj_pixels(const SysDesc& s, const PConst& c,
                                            const float* s_nc, const float* s_dc,
-                                           const float* shp, const float2* beta,
+                                           const float* he, const float2* beta,
                                            const float* sbar, int p0, int p1, float* acc) {
   const int HW = s.H * s.W, W = s.W, k = s.k;
   const int fl_i = c.fl_i, fl_j = c.fl_j;
+  const double dxs = s.dxs;
   for (int pix = p0 + threadIdx.x; pix < p1; pix += blockDim.x) {
     const int i = pix / W, j = pix - i * W;
     const float sb = sbar[pix];
+    const double xj = subpix_coord(s.x0, j * k, dxs);
+    const float2* bp = beta + pix;
     for (int a = 0; a < k; ++a) {
-      const double y = subpix_coord(s.y0, i * k + a, s.dxs);
-      for (int b = 0; b < k; ++b) {
-        const double x = subpix_coord(s.x0, j * k + b, s.dxs);
-        MassState m;
-        const float* bp = reinterpret_cast<const float*>(beta + (a * k + b) * HW + pix);
-        mass_jacobian_f32<MASS, GENERAL>(c, s_nc, s_dc, x, y, __builtin_nontemporal_load(bp),
-                                         __builtin_nontemporal_load(bp + 1), m);
-        // gx, gy: sb d(source light)/d(beta)
-        float gx, gy;
-        sersic_adj(c.src, m.sdx, m.sdy, sb, acc + A_SRC, gx, gy);
+      const double y = subpix_coord(s.y0, i * k + a, dxs);
+      const float zi = float(y - c.yc), ly = float(y - c.lys);
+      // alpha = x - alpha_ext - x_s - (beta - x_s): its part of this row
+      const double cx = -c.g2 * y - c.sxs, cy = c.opg1 * y - c.sys;
+      const float lpx = c.lens.bs * ly, lpy = c.lens.cs * ly;
+      double x = xj;
+      for (int b = 0; b < k; ++b, x += dxs, bp += HW) {
+        const float sdx = __builtin_nontemporal_load(&bp->x);
+        const float sdy = __builtin_nontemporal_load(&bp->y);
+        // g: sb d(source light)/d(beta)
+        const float px = fmaf(c.src.as, sdx, c.src.bs * sdy);
+        const float py = fmaf(c.src.cs, sdy, c.src.bs * sdx);
+        const float sv = sersic_adj(c.src, sdx, sdy, px, py, sb, acc + A_SRC);
+        Cx g;
         if (NMAX >= 0) {
-          float hx, hy;
-          shapelet_adj<(NMAX < 0 ? 0 : NMAX)>(c, m.sdx, m.sdy, shp, sb, acc, hx, hy);
-          gx += hx;
-          gy += hy;
+          shapelet_adj<(NMAX < 0 ? 0 : NMAX)>(c, sdx, sdy, he, sb, acc, g.r, g.i);
+          g = {fmaf(sv, px, g.r), fmaf(sv, py, g.i)};
+        } else {
+          g = {sv * px, sv * py};
         }
-        acc[A_SRC + L_DX] += gx;
-        acc[A_SRC + L_DY] += gy;
+        acc[A_SRC + L_DX] += g.r;
+        acc[A_SRC + L_DY] += g.i;
         if (LL) {
-          float lx, ly;
-          sersic_adj(c.lens, float(x - c.lxs), float(y - c.lys), sb, acc + A_LENS, lx, ly);
-          acc[A_LENS + L_DX] += lx;
-          acc[A_LENS + L_DY] += ly;
+          const float lx = float(x - c.lxs);
+          const float lv = sersic_adj(c.lens, lx, ly, fmaf(c.lens.as, lx, lpx),
+                                      fmaf(c.lens.bs, lx, lpy), sb, acc + A_LENS);
+          acc[A_LENS + L_DX] = fmaf(lv, lx, acc[A_LENS + L_DX]);
+          acc[A_LENS + L_DY] = fmaf(lv, ly, acc[A_LENS + L_DY]);
         }
         // the floored sub-pixel's mass terms are added by finalize from the prologue's
         // exact derivatives
-        const bool at_floor = GENERAL && i * k + a == fl_i && j * k + b == fl_j;
-        mass_adjoint<MASS>(c, m, float(x), float(y),
-                           at_floor ? Cx{0.f, 0.f} : Cx{gx, gy}, acc);
+        if (GENERAL && i * k + a == fl_i && j * k + b == fl_j) g = {0.f, 0.f};
+        mass_adjoint<MASS, GENERAL>(c, s_nc, s_dc, float(x - c.xc), zi,
+                                    float(fma(x, c.omg1, cx)) - sdx,
+                                    float(fma(x, -c.g2, cy)) - sdy, g, acc);
       }
     }
   }
 }
 
+// Bound by VALU issue (one instruction per CU and cycle; packed FP32 is not used), so what counts
+// is instructions per sub-pixel: about 385 with every sum of the gradient taken per sub-pixel,
+// 320 with the sums of mass_adjoint, sersic_adj and shapelet_adj. Measured: 543 -> 463 us (60 x 60,
+// n_max 6, 4096 vectors), 67 -> 53 us (80 x 80 without shapelets, 300), 122 -> 90 us (53 x 37 SIE,
+// k = 3, n_max 3, 777). From n_max = 7 the accumulators and coefficients (up to 122 registers) do
+// not fit three waves per SIMD (168 registers: 60 spilled in the loop); two waves hide the
+// latencies of this instruction mix as well, and the 100 x 100, n_max 8 system went
+// 1510 -> 879 us at 2048 vectors.
 template <int MASS, int LL, int NMAX>
-__global__ void __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ void __launch_bounds__(kSubThreads)
+__attribute__((amdgpu_waves_per_eu(NMAX >= 7 ? 2 : 3)))
 subpix_adj_kernel(Group g) {
   constexpr int NS = n_slots<NMAX>();
   __shared__ double red[kSubThreads / 64][NS];
@@ -832,7 +782,7 @@ subpix_adj_kernel(Group g) {
   const int part = lb / s.tiles, tile = lb - part * s.tiles;
   const PConst& c = s.pc[part];
   __shared__ float s_nc[kMaxTerms], s_dc[kMaxTerms];
-  stage_series(c, s_nc, s_dc);
+  stage_series(c, -2.8853900817779268f, s_nc, s_dc);  // mass_adjoint's -2 / ln 2
   // beta - x_s from the forward pass (kept there for gradient calls)
   const float2* beta = s.beta + (size_t)part * s.k * s.k * s.H * s.W;
   const int HW = s.H * s.W;
@@ -842,37 +792,30 @@ subpix_adj_kernel(Group g) {
   float acc[NS];
 #pragma unroll
   for (int q = 0; q < NS; ++q) acc[q] = 0.f;
-  // shapelet coefficients in vector registers (as in the forward pass): their sums then start
-  // from a register operand instead of a copy of a scalar one
+  // shapelet coefficients in vector registers (as in the forward pass), scaled for the He_n
   constexpr int M = NMAX < 0 ? 1 : (NMAX + 1) * (NMAX + 2) / 2;
   float shp[M];
 #pragma unroll
-  for (int q = 0; q < M; ++q) {
-    shp[q] = NMAX < 0 ? 0.f : c.shp[q];
-    asm("" : "+v"(shp[q]));
-  }
+  for (int n = 0; n <= (NMAX < 0 ? 0 : NMAX); ++n)
+#pragma unroll
+    for (int n2 = 0; n2 <= n; ++n2) {
+      const int q = shp_index(n - n2, n2);
+      shp[q] = NMAX < 0 ? 0.f : c.shp[q] * kHeScale[n];
+      asm("" : "+v"(shp[q]));
+    }
   // the common case (no floored sub-pixel, |eps| >= kSxClosedMin) runs a loop without those
   // tests
   if (c.fl_i < 0 && !(c.epsabs < kSxClosedMin))
     adj_pixels<MASS, LL, NMAX, false>(s, c, s_nc, s_dc, shp, beta, sbar, p0, p1, acc);
   else
     adj_pixels<MASS, LL, NMAX, true>(s, c, s_nc, s_dc, shp, beta, sbar, p0, p1, acc);
-  // FP64 sums: across the wave, then across the waves of the block
-  const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  wave_sums<NS>(acc, red[wave]);
-  __syncthreads();
-  double* out = s.acc + ((size_t)part * s.tiles + tile) * kNAcc;
-  for (int q = threadIdx.x; q < NS; q += blockDim.x) {
-    double v = 0.0;
-    for (int w = 0; w < nw; ++w) v += red[w][q];
-    out[q] = v;
-  }
+  block_sums<NS>(acc, red, s.acc + ((size_t)part * s.tiles + tile) * kNAcc);
 }
 
 // finalize: one 64-lane block per particle (finalize_particle)
 __global__ void __launch_bounds__(64) finalize_kernel(Group g) {
   const int si = find_sys(g, blockIdx.x);
-  finalize_particle(g.sys[si], blockIdx.x - g.block0[si]);
+  finalize_particle<false>(g.sys[si], blockIdx.x - g.block0[si]);
 }
 
 }  // namespace glens

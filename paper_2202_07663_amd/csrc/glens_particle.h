@@ -7,6 +7,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "glens_chain.h"
 #include "glens_device.h"
 #include "glens_fit_device.h"
 
@@ -66,9 +67,12 @@ __device__ __forceinline__ void prologue_particle(const SysDesc& s, int p) {
 // coefficients' components one per lane); a vector whose log L or gradient is not finite
 // gets log L = -inf and a zero gradient
 // ------------------------------------------------------------------------------------------
+// CHAIN: the accumulators are those of the sampler's adjoint (glens_chain.h).
+template <bool CHAIN>
 __device__ __forceinline__ void finalize_particle(const SysDesc& s, int p) {
   __shared__ double a[kNAcc];
-  const int ns = s.nmax < 0 ? A_SHP_BETA : A_SHP_C + (s.nmax + 1) * (s.nmax + 2) / 2;
+  const int beta0 = CHAIN ? int(chain::A_SHP_BETA) : int(A_SHP_BETA);
+  const int ns = beta0 + (s.nmax < 0 ? 0 : 1 + (s.nmax + 1) * (s.nmax + 2) / 2);
   const double* acc = s.acc + (size_t)p * s.tiles * kNAcc;
   for (int q = threadIdx.x; q < ns; q += blockDim.x) {
     double v = 0.0;
@@ -78,28 +82,48 @@ __device__ __forceinline__ void finalize_particle(const SysDesc& s, int p) {
   }
   __syncthreads();
   const PConst& c = s.pc[p];
-  if (threadIdx.x == 0 && c.fl_i >= 0) {
-    // the floored sub-pixel: g = sbar d(source light)/d(beta) there (FP64), contracted with
-    // the prologue's exact deflection derivatives; shear terms as the main loop forms them
+  // the floored sub-pixel (if any): g = sbar d(source light)/d(beta) there (FP64), contracted
+  // with the prologue's exact deflection derivatives; shear terms as the main loop forms them
+  double gx = 0.0, gy = 0.0;
+  const bool floored = threadIdx.x == 0 && c.fl_i >= 0;
+  if (floored) {
     const int k = s.k, HW = s.H * s.W;
     const int pi = c.fl_i / k, pj = c.fl_j / k, sub = (c.fl_i - pi * k) * k + (c.fl_j - pj * k);
     const int pix = pi * s.W + pj;
     const double sb = s.sbar[(size_t)p * HW + pix];
     const float2 bs = s.beta[((size_t)p * k * k + sub) * HW + pix];
-    double gx, gy;
     source_light_grad(c, s.nmax, bs.x, bs.y, gx, gy);
     gx *= sb;
     gy *= sb;
-    a[A_M_ALPHA] += gx * c.fl_a[0] + gy * c.fl_a[1];
-    a[A_M_T] += gx * c.fl_d[0][0] + gy * c.fl_d[0][1];
-    a[A_M_E1] += gx * c.fl_d[1][0] + gy * c.fl_d[1][1];
-    a[A_M_E2] += gx * c.fl_d[2][0] + gy * c.fl_d[2][1];
-    a[A_M_X] -= gx * c.fl_d[3][0] + gy * c.fl_d[3][1];  // d/dx = -d/dx_c
-    a[A_M_Y] -= gx * c.fl_d[4][0] + gy * c.fl_d[4][1];
+  }
+  MassSums ms;  // lane 0
+  if (!CHAIN && threadIdx.x == 0) {
+    ms = mass_sums(c, a);
+    if (floored) {
+      ms.alpha += gx * c.fl_a[0] + gy * c.fl_a[1];
+      ms.t += gx * c.fl_d[0][0] + gy * c.fl_d[0][1];
+      ms.e1 += gx * c.fl_d[1][0] + gy * c.fl_d[1][1];
+      ms.e2 += gx * c.fl_d[2][0] + gy * c.fl_d[2][1];
+      ms.x -= gx * c.fl_d[3][0] + gy * c.fl_d[3][1];  // d/dx = -d/dx_c
+      ms.y -= gx * c.fl_d[4][0] + gy * c.fl_d[4][1];
+      // the sums of g in mass_sums hold this sub-pixel's, those of g z do not
+      const double zr = subpix_coord(s.x0, c.fl_j, s.dxs) - c.xc;
+      const double zi = subpix_coord(s.y0, c.fl_i, s.dxs) - c.yc;
+      ms.g1 += gx * zr - gy * zi;
+      ms.g2 += gx * zi + gy * zr;
+    }
+  }
+  if (CHAIN && floored) {
+    a[chain::A_M_ALPHA] += gx * c.fl_a[0] + gy * c.fl_a[1];
+    a[chain::A_M_T] += gx * c.fl_d[0][0] + gy * c.fl_d[0][1];
+    a[chain::A_M_E1] += gx * c.fl_d[1][0] + gy * c.fl_d[1][1];
+    a[chain::A_M_E2] += gx * c.fl_d[2][0] + gy * c.fl_d[2][1];
+    a[chain::A_M_X] -= gx * c.fl_d[3][0] + gy * c.fl_d[3][1];
+    a[chain::A_M_Y] -= gx * c.fl_d[4][0] + gy * c.fl_d[4][1];
     const double x = float(subpix_coord(s.x0, c.fl_j, s.dxs));
     const double y = float(subpix_coord(s.y0, c.fl_i, s.dxs));
-    a[A_M_G1] += gx * x - gy * y;
-    a[A_M_G2] += gx * y + gy * x;
+    a[chain::A_M_G1] += gx * x - gy * y;
+    a[chain::A_M_G2] += gx * y + gy * x;
   }
   __syncthreads();
   // lane 0 maps the sums (to LDS, not to a lane-private array the compiler would spill);
@@ -107,10 +131,13 @@ __device__ __forceinline__ void finalize_particle(const SysDesc& s, int p) {
   __shared__ float gr[kMaxParams];
   // the shapelet coefficients' components (if any) follow the others, one per lane
   __shared__ int s_j0;
-  if (threadIdx.x == 0) s_j0 = map_gradient(c, a, s.mass, s.shear, s.lens_light, s.nmax, gr);
+  if (threadIdx.x == 0)
+    s_j0 = CHAIN ? chain::map_gradient(c, a, s.mass, s.shear, s.lens_light, s.nmax, gr)
+                 : map_gradient(c, ms, a, s.mass, s.shear, s.lens_light, s.nmax, gr);
   __syncthreads();
   const int M = s.nmax < 0 ? 0 : (s.nmax + 1) * (s.nmax + 2) / 2;
-  for (int q = threadIdx.x; q < M; q += blockDim.x) gr[s_j0 + q] = shapelet_coef_grad(c, a, q);
+  for (int q = threadIdx.x; q < M; q += blockDim.x) 
+    gr[s_j0 + q] = CHAIN ? chain::shapelet_coef_grad(c, a, q) : shapelet_coef_grad(c, a, q);
   __syncthreads();
   const int j = s_j0 + M;
   int bad = 0;

@@ -1,0 +1,96 @@
+// What the sub-pixel adjoint kernels share: the staged derivative series and the FP64 sums of
+// their per-lane accumulators.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "glens_device.h"
+
+namespace glens {
+
+constexpr int kSubThreads = 256;
+
+// Copies the particle's derivative-series coefficients to LDS (read uniformly by every lane),
+// those of dS/dt times `scale`.
+__device__ __forceinline__ void stage_series(const PConst& c, float scale, float* s_nc,
+                                             float* s_dc) {
+  for (int n = threadIdx.x; n < kMaxTerms; n += blockDim.x) {
+    s_nc[n] = c.nc[n];
+    s_dc[n] = c.dc[n] * scale;
+  }
+  __syncthreads();
+}
+
+constexpr int halved(int n) { return n > 1 ? n / 2 : 1; }
+
+// One step of the transposed butterfly below for a lane holding NV values (all indices
+// compile-time, so the values stay in registers).
+template <int NV>
+__device__ __forceinline__ void wave_sum_step(double* v, int off, int lane) {
+  if constexpr (NV > 1) {
+    const bool up = lane & off;
+#pragma unroll
+    for (int i = 0; i < NV / 2; ++i) {
+      const double send = up ? v[i] : v[i + NV / 2];
+      const double keep = up ? v[i + NV / 2] : v[i];
+      v[i] = keep + __shfl_xor(send, off, 64);
+    }
+  } else {
+    v[0] += __shfl_xor(v[0], off, 64);
+  }
+}
+
+// Wave sums of NS per-lane FP32 values, in FP64, written to out[0 .. NS). A transposed
+// butterfly: with the values padded to N (a power of two), at the step with lane offset o a
+// lane keeps one half of its values, sends the other half to lane ^ o and adds what it
+// receives, so each step halves the values a lane holds. Every sum pairs lanes in the same
+// order as a separate xor butterfly per value would, with about N shuffles instead of
+// 6 NS. The first step shuffles the FP32 values and adds them in FP64.
+template <int NS>
+__device__ __forceinline__ void wave_sums(const float* acc, double* out) {
+  constexpr int N = NS <= 32 ? 32 : (NS <= 64 ? 64 : 128);
+  static_assert(NS <= 128, "too many accumulators");
+  const int lane = threadIdx.x & 63;
+  double v[N / 2];
+  {
+    const bool up = lane & 32;
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+      const float lo = i < NS ? acc[i] : 0.f, hi = i + N / 2 < NS ? acc[i + N / 2] : 0.f;
+      const float send = up ? lo : hi;
+      v[i] = double(up ? hi : lo) + double(__shfl_xor(send, 32, 64));
+    }
+  }
+  constexpr int n1 = N / 2, n2 = halved(n1), n3 = halved(n2), n4 = halved(n3), n5 = halved(n4);
+  wave_sum_step<n1>(v, 16, lane);
+  wave_sum_step<n2>(v, 8, lane);
+  wave_sum_step<n3>(v, 4, lane);
+  wave_sum_step<n4>(v, 2, lane);
+  wave_sum_step<n5>(v, 1, lane);
+  // lane l now holds value (l * N / 64) + i for i < N / 64 (N = 32: lanes 2q and 2q + 1
+  // both hold value q)
+  if (N >= 64) {
+#pragma unroll
+    for (int i = 0; i < N / 64; ++i) {
+      const int q = lane * (N / 64) + i;
+      if (q < NS) out[q] = v[i];
+    }
+  } else if ((lane & 1) == 0 && (lane >> 1) < NS) {
+    out[lane >> 1] = v[0];
+  }
+}
+
+// FP64 sums of the block's accumulators, across each wave, then across the waves, to out[0 .. NS).
+template <int NS>
+__device__ __forceinline__ void block_sums(const float* acc, double (*red)[NS], double* out) {
+  const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  wave_sums<NS>(acc, red[wave]);
+  __syncthreads();
+  for (int q = threadIdx.x; q < NS; q += blockDim.x) {
+    double v = 0.0;
+    for (int w = 0; w < nw; ++w) v += red[w][q];
+    out[q] = v;
+  }
+}
+
+}  // namespace glens

@@ -16,7 +16,7 @@ constexpr int kPowDeg = 6;
 constexpr int kMaxNmax = 8;        // shapelet order
 constexpr int kMaxShp = (kMaxNmax + 1) * (kMaxNmax + 2) / 2;  // 45
 constexpr int kMaxParams = 68;
-constexpr int kNAcc = 72;          // adjoint accumulator slots per (particle, tile)
+constexpr int kNAcc = 80;          // adjoint accumulator slots per (particle, tile)
 constexpr float kR2Floor = 1e-12f; // arcsec^2 floor on elliptical radii
 constexpr double kR2FloorD = 1e-12;
 // Smallest sub-pixel pitch (arcsec): a mass radius below the floor needs the sub-pixel within
@@ -31,19 +31,29 @@ constexpr double kSeriesTolDeriv = 1e-7;  // truncation of the derivative series
 // costs 1e-10 / |eps| relative: below 1e-8 here); the derivative series below
 constexpr double kSxClosedMin = 0.02;
 
-// Accumulator slots of the adjoint (per particle, summed over sub-pixels).
+// Accumulator slots of the adjoint (per particle, summed over sub-pixels). Only sums that need a
+// value of their own per sub-pixel are kept: with g the weighted light gradient, gb = conj(g),
+// kappa = d alpha / dz (real), Gamma = d alpha / d conj(z) and Hx = gb Gamma + kappa g, every
+// other sum of the mass gradient is a combination of these by per-particle constants
+// (mass_sums), and so are those of the light profiles (light_grad).
 enum AccSlot {
-  A_M_ALPHA = 0,  // sum g.alpha                      -> theta_E (and SIE)
-  A_M_T = 1,      // sum g.(d alpha / d t)             -> gamma_epl
-  A_M_E1 = 2, A_M_E2 = 3,   // sum g.(d alpha / d eps_k) (clamped eps)
-  A_M_X = 4, A_M_Y = 5,     // sum g.(d alpha / d x), g.(d alpha / d y)
-  A_M_G1 = 6, A_M_G2 = 7,   // sum g.(x, -y), g.(y, x)
-  A_LENS = 8,     // 8 slots, see LightSlot
-  A_SRC = 16,     // 8 slots; the centre slots also collect the shapelet beta-gradient
-  A_SHP_BETA = 24,
-  A_SHP_C = 25,   // kMaxShp slots
+  A_M_GAR = 0, A_M_GAI = 1,  // sum gb alpha
+  A_M_T = 2,      // sum g.(d alpha / d t) / (-ln 2 / 2)
+  A_M_X = 3, A_M_Y = 4,      // sum Hx = g.(d alpha / dx) + i g.(d alpha / dy)
+  A_M_KRR = 5, A_M_KRI = 6,  // sum kappa Re(g) z
+  A_M_KIR = 7, A_M_KII = 8,  // sum kappa Im(g) z
+  A_M_HZR = 9, A_M_HZI = 10, // sum Hx z
+  A_M_G1 = 11, A_M_G2 = 12,  // sum g.(zr, -zi), g.(zi, zr)
+  A_M_WR = 13, A_M_WI = 14,  // sum gb A w u2 dS/dX (|eps| < kSxClosedMin only)
+  A_LENS = 15,    // 8 slots, see LightSlot
+  A_SRC = 23,     // 8 slots; the centre slots also collect the shapelet gradient
+  A_SHP_BETA = 31,
+  A_SHP_C = 32,   // kMaxShp slots
 };
-enum LightSlot { L_E = 0, L_RHO = 1, L_RHO1 = 2, L_RHOLN = 3, L_Q1 = 4, L_Q2 = 5, L_DX = 6, L_DY = 7 };
+// Sums of one light profile, with E = I / I0, rho = (R / R_eff)^(1/n) and s the weighted
+// (R_eff^2 / R^2) d I / d ln R^2 times 2: E, E rho, E rho log2(rho) (all weighted), s dx^2,
+// s dx dy, s dy^2; L_DX, L_DY: the source's gradient in the offset, the lens light's s dx, s dy.
+enum LightSlot { L_E = 0, L_RHO = 1, L_RHOLN = 2, L_XX = 3, L_XY = 4, L_YY = 5, L_DX = 6, L_DY = 7 };
 static_assert(A_SHP_C + kMaxShp <= kNAcc, "accumulator slots");
 
 // Elliptical Sersic constants of one particle.
@@ -58,6 +68,10 @@ struct LightC {
   float n, re;         // Sersic index, R_eff
   float e1, e2;        // clamped eccentricities
   float inv1me2;       // 1 / (1 - |eps|^2)
+  // the adjoint's form of the profile: R^2 / R_eff^2 = as dx^2 + 2 bs dx dy + cs dy^2
+  float as, bs, cs;
+  float fls;           // the R^2 floor over R_eff^2
+  float kqi;           // kq I0
   float j11, j12, j22; // d eps_clamped / d eps (symmetric)
 };
 
@@ -73,6 +87,7 @@ struct PConst {
   double t;            // gamma - 1
   double e1, e2;       // clamped mass eccentricities
   double xc, yc, g1, g2;
+  double omg1, opg1;   // 1 - g1, 1 + g1
   double tlnb;         // t ln B, B = theta_E sqrt(1 - |eps|^2)
   double bmass;        // B
   double w2floor;      // R^2 floor expressed on |w|^2: 1e-12 (1 + |eps|)^2
@@ -97,18 +112,22 @@ struct PConst {
   double sxs, sys;     // source centre
   double lxs, lys;     // lens-light centre
   // FP32 part
-  float theta_e, tf;   // Einstein radius, t
+  float theta_e;       // Einstein radius
   float hp, hm;        // 1 - t/2, -t/2
-  float xcf, ycf;      // lens centre (FP32, adjoint Jacobian)
+  float omt;           // 1 - t
   float w2floorf;      // R^2 floor on |w|^2 (FP32)
-  float tlnb2;         // t ln B log2(e)
-  float iebr, iebi;    // 1 / conj(eps) for |eps| >= kSxClosedMin, else 0 (adjoint Jacobian)
-  float e1f, e2f;
-  float lnb;
+  float tlnb2;         // t log2 B
+  float l2b2;          // 2 log2 B
+  float hb;            // B / 2
+  float e1f, e2f, eef; // clamped eccentricities, |eps|^2
+  float tf, lnb;       // t, ln B, and below the constants of the chains' adjoint (glens_chain.h):
+  float xcf, ycf;      // lens centre
+  float iebr, iebi;    // 1 / conj(eps) for |eps| >= kSxClosedMin, else 0
   float tfac;          // t / (2 (1 - |eps|^2))
   float mj11, mj12, mj22;
   LightC lens, src;
   float beta, inv_beta;
+  float rt2_ib;        // sqrt(2) / beta
   float shp[kMaxShp];  // c_k r_n1 r_n2 / (beta sqrt(pi)), r_n = sqrt(2^n / n!)
   float dc[kMaxTerms]; // d c_n / dt (zero from nterms_d on)
   float nc[kMaxTerms]; // (n + 1) c_{n+1}: coefficients of dS/dy (zero from nterms_d - 1 on)

@@ -167,7 +167,7 @@ __device__ __forceinline__ void sample_objective(const ViArgs& a) {
 // The pipeline's finalize (log L and its gradient) for sample blockIdx.x, then f and its
 // gradient: one launch instead of two.
 __global__ void __launch_bounds__(kViThreads) vi_finalize_objective_kernel(SysDesc s, ViArgs a) {
-  finalize_particle(s, blockIdx.x);
+  finalize_particle<false>(s, blockIdx.x);
   __syncthreads();  // this sample's log L and gradient are written
   sample_objective(a);
 }
