@@ -332,7 +332,7 @@ SysDesc make_sys(const SystemData& sd, const Workspace& ws, int P, int tiles) {
   // matrix-core PSF pass for whole-image launches when the image's tiles and LDS fit; the
   // choice depends on this system alone, so its results do not depend on its launch partners
   const MfmaGeom q = mfma_geom(c.H, c.W, c.K);
-  s.conv_mfma = sd.psf_mfma && s.bands == 1 && q.T <= 4 * kMfmaWaveTiles &&
+  s.conv_mfma = sd.psf_mfma && s.bands == 1 && q.T <= kMfmaMaxTiles &&
                 size_t(mfma_lds_bytes(q, c.H, c.W)) <= kConvLdsMax;
   return s;
 }
@@ -464,10 +464,23 @@ static int conv_lds_limit(size_t lds) {
   return GL_OK;
 }
 
+// Static LDS of the matrix-core kernel (the reduction buffers), rounded up.
+constexpr int kMfmaStaticLds = 256;
+
 static int launch_conv_mfma(const Group& g, size_t lds, hipStream_t st) {
   int rc = conv_lds_limit(lds);
   if (rc) return rc;
-  return launch(conv_mfma_kernel, g.block0[g.nsys], kConvThreads, lds, g, st);
+  // sixteen waves per CU (four per SIMD), from the blocks that its LDS holds and the batch has;
+  // a wave with fewer than two tiles has too few independent products to hide their latency
+  const int blocks = g.block0[g.nsys];
+  const int per_cu = std::min(int(160 * 1024 / (lds + kMfmaStaticLds)), blocks / 256);
+  int threads = per_cu >= 4 ? 256 : (per_cu >= 2 ? 512 : kMfmaMaxThreads);
+  int tiles = 0;
+  for (int i = 0; i < g.nsys; ++i)
+    if (g.sys[i].conv_mfma)
+      tiles = std::max(tiles, mfma_geom(g.sys[i].H, g.sys[i].W, g.sys[i].K).T);
+  while (threads > 256 && threads / 64 * 2 > tiles) threads /= 2;
+  return launch(conv_mfma_kernel, blocks, threads, lds, g, st);
 }
 
 int launch_conv(int K, const Group& g, size_t lds, hipStream_t st) {

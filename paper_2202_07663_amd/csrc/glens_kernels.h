@@ -23,6 +23,7 @@
 namespace glens {
 
 constexpr int kConvThreads = 256;
+constexpr int kMfmaMaxThreads = 1024;
 constexpr int kConvRows = 8;  // output rows per lane in the PSF pass
 constexpr int kConvMaxStrips = 8;  // strips per lane: (H/8 rounded up) * W <= 8 * 256
 
@@ -320,19 +321,19 @@ __device__ __forceinline__ f32x4 mfma_f16(f16x8 a, f16x8 b, f32x4 c) {
 }
 
 // acc[v] = correlation of the scaled LDS image (parts x, x + nel) with the scaled PSF over
-// the wave's tiles wave + 4 (U0 + v), v < G. tab: this direction's fragments [K][64][h, l];
+// the tiles t0 + v nw, v < G, of one of the block's nw waves. tab: this direction's fragments [K][64][h, l];
 // those of row a + 2 are loaded while row a is computed. Each product is issued over the G
 // tiles before the next, so consecutive matrix instructions are independent.
-template <int U0, int G>
+template <int G>
 __device__ __forceinline__ void mfma_tiles(const uint16_t* x, int nel, const MfmaGeom& q,
-                                           const uint4* __restrict__ tab, int K, int wave,
+                                           const uint4* __restrict__ tab, int K, int t0, int nw,
                                            f32x4* acc) {
   const int lane = threadIdx.x & 63, mr = lane & 15, g = lane >> 4;
   int off[G];  // this lane's fragment offset in tile v at row a = 0
   f16x8 ah[G], al[G];
 #pragma unroll
   for (int v = 0; v < G; ++v) {
-    const int t = wave + 4 * (U0 + v);
+    const int t = t0 + v * nw;
     const int tr = t / q.TC, tc = t - tr * q.TC;
     off[v] = (tr * 16 + mr) * q.pitch + tc * q.N + 8 * g;
     ah[v] = lds_frag(x + off[v]);
@@ -384,7 +385,7 @@ __device__ __forceinline__ void mfma_tiles(const uint16_t* x, int nel, const Mfm
 // loaded again for every pixel.
 struct MfmaPass {
   const MfmaGeom& q;
-  int wave;
+  int nw;             // waves of the block
   int unscale;        // exponent that takes the scaled sums back: -(image scale + PSF scale)
   int H, W, mode;
   float s2b, inv_gt, inv_k2;
@@ -394,15 +395,15 @@ struct MfmaPass {
   double ll, c2;
 };
 
-// Pixels of tiles wave + 4 (U0 + v), v < G: element r of acc[v] is pixel (i0 + r, j).
+// Pixels of tiles t0 + v nw, v < G: element r of acc[v] is pixel (i0 + r, j).
 // Forward (ADJ false): the model image, or the likelihood terms and the seed; adjoint: sbar.
-template <int U0, int G, bool ADJ>
-__device__ __forceinline__ void mfma_pixels(MfmaPass& P, const f32x4* acc) {
+template <int G, bool ADJ>
+__device__ __forceinline__ void mfma_pixels(MfmaPass& P, int t0, const f32x4* acc) {
   const int lane = threadIdx.x & 63, n = lane & 15, r0 = 4 * (lane >> 4);
   const int H = P.H, W = P.W;
 #pragma unroll
   for (int v = 0; v < G; ++v) {
-    const int t = P.wave + 4 * (U0 + v), tr = t / P.q.TC, tc = t - tr * P.q.TC;
+    const int t = t0 + v * P.nw, tr = t / P.q.TC, tc = t - tr * P.q.TC;
     const int j = tc * P.q.N + n, i0 = tr * 16 + r0;
     if (n >= P.q.N || j >= W) continue;
 #pragma unroll
@@ -430,52 +431,73 @@ __device__ __forceinline__ void mfma_pixels(MfmaPass& P, const f32x4* acc) {
   }
 }
 
-// Tiles U0 .. U0 + G - 1 of the wave: correlate, then the per-pixel step.
-template <int U0, int G, bool ADJ>
+// G tiles of the wave: correlate, then the per-pixel step.
+template <int G, bool ADJ>
 __device__ __forceinline__ void mfma_group(MfmaPass& P, const uint16_t* x, int nel,
-                                           const uint4* tab, int K) {
+                                           const uint4* tab, int K, int t0) {
   f32x4 acc[G];
-  mfma_tiles<U0, G>(x, nel, P.q, tab, K, P.wave, acc);
-  mfma_pixels<U0, G, ADJ>(P, acc);
+  mfma_tiles<G>(x, nel, P.q, tab, K, t0, P.nw, acc);
+  mfma_pixels<G, ADJ>(P, t0, acc);
 }
 
-// The wave's ntw tiles (wave-uniform) in groups of at most five, as even as possible: a
-// group's products hide the latency of the PSF fragment loads only when it has several tiles.
+// The wave's tiles wave, wave + nw, .. in groups of at most five, as even as possible: a group's
+// products hide the latency of the PSF fragment loads only when it has several tiles.
 template <bool ADJ>
 __device__ __forceinline__ void mfma_pass(MfmaPass& P, const uint16_t* x, int nel,
-                                          const uint4* tab, int K, int ntw) {
-  static_assert(kMfmaWaveTiles == 16, "group table for up to 16 tiles");
-#define GL_G(U0, G) mfma_group<U0, G, ADJ>(P, x, nel, tab, K)
-  switch (ntw) {
-    case 1: GL_G(0, 1); break;
-    case 2: GL_G(0, 2); break;
-    case 3: GL_G(0, 3); break;
-    case 4: GL_G(0, 4); break;
-    case 5: GL_G(0, 5); break;
-    case 6: GL_G(0, 3); GL_G(3, 3); break;
-    case 7: GL_G(0, 4); GL_G(4, 3); break;
-    case 8: GL_G(0, 4); GL_G(4, 4); break;
-    case 9: GL_G(0, 5); GL_G(5, 4); break;
-    case 10: GL_G(0, 5); GL_G(5, 5); break;
-    case 11: GL_G(0, 4); GL_G(4, 4); GL_G(8, 3); break;
-    case 12: GL_G(0, 4); GL_G(4, 4); GL_G(8, 4); break;
-    case 13: GL_G(0, 5); GL_G(5, 4); GL_G(9, 4); break;
-    case 14: GL_G(0, 5); GL_G(5, 5); GL_G(10, 4); break;
-    case 15: GL_G(0, 5); GL_G(5, 5); GL_G(10, 5); break;
-    case 16: GL_G(0, 4); GL_G(4, 4); GL_G(8, 4); GL_G(12, 4); break;
-    default: break;
+                                          const uint4* tab, int K) {
+  // wave-uniform: kept in scalar registers
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ntw = wave < P.q.T ? (P.q.T - wave + P.nw - 1) / P.nw : 0;
+  const int ng = (ntw + 4) / 5;
+  for (int gi = 0, u = 0; gi < ng; ++gi) {
+    const int n = (ntw - u + ng - gi - 1) / (ng - gi), t0 = wave + u * P.nw;
+    switch (n) {
+      case 1: mfma_group<1, ADJ>(P, x, nel, tab, K, t0); break;
+      case 2: mfma_group<2, ADJ>(P, x, nel, tab, K, t0); break;
+      case 3: mfma_group<3, ADJ>(P, x, nel, tab, K, t0); break;
+      case 4: mfma_group<4, ADJ>(P, x, nel, tab, K, t0); break;
+      default: mfma_group<5, ADJ>(P, x, nel, tab, K, t0); break;
+    }
+    u += n;
   }
-#undef GL_G
 }
 
-// Four waves per SIMD (at most 128 VGPRs) and at most 40 KB of LDS at the 60 x 60, K = 21
-// size let four workgroups share a CU: 4096 particles then fill the chip in four rounds
-// instead of five and a third.
-__global__ void __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(4)))
+// Row and column of the pixels idx = threadIdx.x + n blockDim.x of a W-column image, stepped
+// without a division per pixel.
+struct PixelWalk {
+  int i, j, di, dj, W;
+  __device__ __forceinline__ PixelWalk(int W_) : W(W_) {
+    i = int(threadIdx.x) / W;
+    j = int(threadIdx.x) - i * W;
+    di = int(blockDim.x) / W;
+    dj = int(blockDim.x) - di * W;
+  }
+  __device__ __forceinline__ void next() {
+    i += di;
+    j += dj;
+    if (j >= W) {
+      j -= W;
+      ++i;
+    }
+  }
+};
+
+// One block per particle. Its size (launch_conv_mfma) is what fills a CU: 256 threads where four
+// blocks fit a CU's LDS (four waves per SIMD at the 128 registers allowed here), 512 or 1024
+// where the image leaves room for two or one, or where the batch has too few particles for
+// more; a tile's sums do not depend on the wave that takes it. 256 threads throughout against
+// this rule: 100 x 100 (103 KB of LDS: one block per CU), 2048 vectors 720 -> 443 us; 80 x 80,
+// 512 vectors (images) 37 -> 30 us; 60 x 60, 512 vectors 42 -> 37 us. At 60 x 60 and 4096 vectors
+// (193 us) the fill and split of the image take 35 us of the forward half's 119, the products 64
+// (matrix cores 34, row shifts and LDS reads of the new rows the rest: reloading either part of
+// the fragments from LDS instead of shifting it measured 278 us for the kernel, both 394), the
+// likelihood terms 22.
+// mode 3: only the adjoint pass, from the seed that the banded forward kernel left in memory.
+__global__ void __launch_bounds__(kMfmaMaxThreads) __attribute__((amdgpu_waves_per_eu(4)))
 conv_mfma_kernel(Group g) {
   extern __shared__ __align__(16) uint16_t xlds[];
-  __shared__ double red[kConvThreads / 64];
-  __shared__ float redf[kConvThreads / 64];
+  __shared__ double red[kMfmaMaxThreads / 64];
+  __shared__ float redf[kMfmaMaxThreads / 64];
   const int si = find_sys(g, blockIdx.x);
   const SysDesc& s = g.sys[si];
   const int part = blockIdx.x - g.block0[si];
@@ -485,53 +507,51 @@ conv_mfma_kernel(Group g) {
   float* seed = reinterpret_cast<float*>(xlds + 2 * nel);
   for (int i = threadIdx.x; i < nel / 4; i += blockDim.x)
     reinterpret_cast<uint4*>(xlds)[i] = make_uint4(0u, 0u, 0u, 0u);
+  const bool adj_only = mode == 3;
   // the image goes through the (still unused) seed area: one coalesced pass over global
   // memory with many loads in flight, its largest magnitude found on the way
-  const float* m0 = s.m0 + (size_t)part * HW;
+  const float* src = (adj_only ? s.seed : s.m0) + (size_t)part * HW;
   float mx = 0.f;
 #pragma unroll 8
   for (int idx = threadIdx.x; idx < HW; idx += blockDim.x) {
-    const float v = m0[idx];
+    const float v = src[idx];
     seed[idx] = v;
     mx = fmaxf(mx, fabsf(v));
   }
-  const int sx = f16_scale_exp(block_max(mx, redf));  // its barriers also end the zero fill
-  for (int idx = threadIdx.x; idx < HW; idx += blockDim.x) {
-    const int i = idx / W, j = idx - i * W;
-    split2_f16(ldexpf(seed[idx], sx), xlds + (i + C) * q.pitch + j + C, nel);
-  }
+  // the block_max barriers also end the zero fill
+  int sx = f16_scale_exp(block_max(mx, redf));
+  PixelWalk w0(W);
+  for (int idx = threadIdx.x; idx < HW; idx += blockDim.x, w0.next())
+    split2_f16(ldexpf(seed[idx], sx), xlds + (w0.i + C) * q.pitch + w0.j + C, nel);
   __syncthreads();
-  const int wave = threadIdx.x >> 6;
-  // tiles of this wave (wave-uniform: kept in a scalar register)
-  const int ntw = __builtin_amdgcn_readfirstlane(wave < q.T ? (q.T - wave + 3) / 4 : 0);
-  MfmaPass P{q, wave, -(sx + s.psf_mfma_exp), H, W, mode, s.s2b, s.inv_gt, s.inv_k2, s.obs,
-             (mode == 0 ? s.img : s.sbar) + (size_t)part * HW, seed, 0.0, 0.0};
-  mfma_pass<false>(P, xlds, nel, s.psf_mfma, K, ntw);
-  if (mode == 0) return;
-  const double tot = block_sum(P.ll, red);
-  if (threadIdx.x == 0) {
-    const double v = -0.5 * tot;
-    s.logl[part] = isfinite(v) ? v : -INFINITY;
+  MfmaPass P{q, int(blockDim.x) >> 6, -(sx + s.psf_mfma_exp), H, W, mode, s.s2b, s.inv_gt,
+             s.inv_k2, s.obs, (mode == 0 ? s.img : s.sbar) + (size_t)part * HW, seed, 0.0, 0.0};
+  if (!adj_only) {
+    mfma_pass<false>(P, xlds, nel, s.psf_mfma, K);
+    if (mode == 0) return;
+    const double tot = block_sum(P.ll, red);
+    if (threadIdx.x == 0) {
+      const double v = -0.5 * tot;
+      s.logl[part] = isfinite(v) ? v : -INFINITY;
+    }
+    if (s.chi2) {
+      const double ctot = block_sum(P.c2, red);
+      if (threadIdx.x == 0) s.chi2[part] = ctot;
+    }
+    if (mode != 2) return;
+    // every wave is done with the image (block_max below starts with a barrier): its interior
+    // takes the scaled seed
+    mx = 0.f;
+    for (int idx = threadIdx.x; idx < HW; idx += blockDim.x) mx = fmaxf(mx, fabsf(seed[idx]));
+    sx = f16_scale_exp(block_max(mx, redf));
+    PixelWalk w1(W);
+    for (int idx = threadIdx.x; idx < HW; idx += blockDim.x, w1.next())
+      split2_f16(ldexpf(seed[idx], sx), xlds + (w1.i + C) * q.pitch + w1.j + C, nel);
+    __syncthreads();
+    P.unscale = -(sx + s.psf_mfma_exp);
   }
-  if (s.chi2) {
-    const double ctot = block_sum(P.c2, red);
-    if (threadIdx.x == 0) s.chi2[part] = ctot;
-  }
-  if (mode != 2) return;
-  // every wave is done with the image (block_max below starts with a barrier): its interior
-  // takes the scaled seed
-  mx = 0.f;
-  for (int idx = threadIdx.x; idx < HW; idx += blockDim.x) mx = fmaxf(mx, fabsf(seed[idx]));
-  const int ss = f16_scale_exp(block_max(mx, redf));
-  for (int idx = threadIdx.x; idx < HW; idx += blockDim.x) {
-    const int i = idx / W, j = idx - i * W;
-    split2_f16(ldexpf(seed[idx], ss), xlds + (i + C) * q.pitch + j + C, nel);
-  }
-  __syncthreads();
   // d logL / d m0 = correlation of the pixel seed with the (unflipped) PSF
-  P.unscale = -(ss + s.psf_mfma_exp);
-  P.out = s.sbar + (size_t)part * HW;
-  mfma_pass<true>(P, xlds, nel, s.psf_mfma + 2 * 64 * K, K, ntw);
+  mfma_pass<true>(P, xlds, nel, s.psf_mfma + 2 * 64 * K, K);
 }
 
 // ------------------------------------------------------------------------------------------

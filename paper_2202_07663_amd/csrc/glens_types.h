@@ -201,7 +201,7 @@ struct FitOut {
 // Toeplitz matrix T_a[kk][n] = psf[a][kk - n]). N = min(16, 33 - K), rounded down to a
 // multiple of 4, columns fit the window.
 constexpr int kMfmaMaxK = 21;       // largest PSF for this pass
-constexpr int kMfmaWaveTiles = 16;  // output tiles per wave (4 waves: <= 64 tiles per image)
+constexpr int kMfmaMaxTiles = 64;   // output tiles per image
 
 struct MfmaGeom {
   int N;       // useful output columns per tile
