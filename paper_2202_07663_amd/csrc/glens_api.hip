@@ -364,7 +364,7 @@ using GroupKernel = void (*)(Group);
 
 template <int MASS, int LL, int NMAX>
 struct SubKernels {
-  static constexpr GroupKernel fwd = subpix_fwd_kernel<MASS, LL, NMAX>;
+  static constexpr GroupKernel fwd = subpix_fwd_kernel<LL, NMAX>;
   static constexpr GroupKernel adj = subpix_adj_kernel<MASS, LL, NMAX>;
 };
 
@@ -543,7 +543,7 @@ int run_group(Group& g, int key, int K, int mode, hipStream_t st, hipEvent_t* ev
   GL_HIP(mark(1));
   for (int i = 0; i < g.nsys; ++i) g.sys[i].mode = mode;  // the forward pass keeps beta in mode 2
   set_blocks(g, blocks_subpix_fwd);
-  if ((rc = launch_subpix_fwd(key, g, st))) return rc;
+  if ((rc = chain ? launch_chain_fwd(key, g, st) : launch_subpix_fwd(key, g, st))) return rc;
   GL_HIP(mark(2));
   // PSF pass: systems flagged for matrix cores in one launch, the others in the banded or the
   // whole-image VALU kernels (a system with one band gets the same bits from either)

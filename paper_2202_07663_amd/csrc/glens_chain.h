@@ -1,4 +1,5 @@
-// The sub-pixel adjoint of the sampler's chains: every sum of the gradient taken per sub-pixel.
+// The sub-pixel passes of the sampler's chains: the ray trace with the SIE's closed form, and the
+// adjoint with every sum of the gradient taken per sub-pixel.
 //
 // A chain's position reaches the pipeline rounded to FP32, and a rounding that falls the other
 // way moves log p~ of a sharp posterior by up to 1e-5 of itself (measured on the 60 x 60 system:
@@ -17,6 +18,122 @@
 
 namespace glens {
 namespace chain {
+
+// EPL / SIE deflection plus shear at image position (x, y), in FP64: returns beta - x_s with
+// beta = x - alpha - alpha_ext. cs: the particle's series coefficients c.c (the kernels pass
+// a copy staged in LDS).
+// at_floor: this is the particle's floored sub-pixel (c.fl_*); the SIE then takes the
+// frozen-radius closed form the prologue evaluated (the EPL's value there is this formula's).
+// cs / pw: the particle's series coefficients c.c and power tables c.pw (staged in LDS).
+template <int MASS>
+GL_HD void ray_trace(const PConst& c, const double* __restrict__ cs,
+                     const double* __restrict__ pw, double x, double y, bool at_floor,
+                     float& sdx, float& sdy) {
+  const double zr = x - c.xc, zi = y - c.yc;
+  const double e1 = c.e1, e2 = c.e2;
+  const double wr = zr - e1 * zr - e2 * zi, wi = zi - e2 * zr + e1 * zi;
+  const double w2 = fmax(wr * wr + wi * wi, c.w2floor);
+  const double inv_w2 = rcp_f64(w2);
+  const double u2r = (wr * wr - wi * wi) * inv_w2, u2i = 2.0 * wr * wi * inv_w2;
+  const double Xr = e1 * u2r + e2 * u2i, Xi = e1 * u2i - e2 * u2r;
+  double Sr, Si, A;
+  if (MASS == 0 && c.sie_closed) {
+    // S_1(X) = atan(zeta) / zeta, zeta = s w / |w|; atan of |zeta| < 1 in closed form
+    const double rinv = sqrt(inv_w2);
+    const double ur = wr * rinv, ui = wi * rinv;
+    const double a = c.sr * ur - c.si * ui, b = c.sr * ui + c.si * ur;
+    const double aa = a * a;
+    const double atr = 0.5 * atan(2.0 * a / (1.0 - c.epsabs));
+    const double ati = 0.25 * log(((1.0 + b) * (1.0 + b) + aa) / ((1.0 - b) * (1.0 - b) + aa));
+    const double ie = 1.0 / c.epsabs;  // S = atan(zeta) conj(zeta) / |eps|
+    Sr = (atr * a + ati * b) * ie;
+    Si = (ati * a - atr * b) * ie;
+    A = c.bmass * rinv;
+  } else {
+    // The coefficients are real, so the series is evaluated at the complex point y = -X by
+    // synthetic division by the real quadratic (v - y)(v - conj y) = v^2 - 2 Re(y) v + |y|^2
+    // (Knuth, TAOCP vol. 2, sec. 4.6.4): b_n = c_n + 2 Re(y) b_(n+1) - |y|^2 b_(n+2) from the
+    // top down to n = 0, and the sum is b_0 - Re(y) b_1 + i Im(y) b_1. That is two real FMAs
+    // per term where complex Horner takes four. |y| = |eps| < 1, so rounding errors made
+    // early are damped as the recurrence runs down. Terms are taken two per trip (so that the
+    // two carried values need no register moves); coefficients past the series length are
+    // zero, so rounding the length up to an even number is exact.
+    const double yr = -Xr, yi = -Xi;
+    const double r2 = 2.0 * yr, yy = fma(yr, yr, yi * yi);
+    double b1 = 0.0, b2 = 0.0;  // b_(n+1), b_(n+2)
+    const int nt2 = (c.nterms + 1) & ~1;
+    for (int n0 = nt2 - 2; n0 >= 0; n0 -= 2) {  // leaves b_n0 in b1 and b_(n0+1) in b2
+      b2 = fma(r2, b1, fma(-yy, b2, cs[n0 + 1]));
+      b1 = fma(r2, b2, fma(-yy, b1, cs[n0]));
+    }
+    Sr = fma(-yr, b2, b1);
+    Si = yi * b2;
+    A = pow_from_table(pw, w2);
+  }
+  double ar = A * (wr * Sr - wi * Si), ai = A * (wr * Si + wi * Sr);
+  if (MASS == 0 && at_floor) {
+    ar = c.fl_a[0];
+    ai = c.fl_a[1];
+  }
+  // beta - x_s = x - alpha - alpha_ext - x_s
+  sdx = float(x - ar - (c.g1 * x + c.g2 * y) - c.sxs);
+  sdy = float(y - ai - (c.g2 * x - c.g1 * y) - c.sys);
+}
+
+template <int MASS, int LL, int NMAX>
+__device__ __forceinline__ float surface_brightness(const PConst& c, const double* cs,
+                                                    const double* s_pw, double x, double y,
+                                                    bool at_floor, const float* shp,
+                                                    float2& sd) {
+  chain::ray_trace<MASS>(c, cs, s_pw, x, y, at_floor, sd.x, sd.y);
+  float v = sersic_fwd(c.src, sd.x, sd.y);
+  if (NMAX >= 0) v += shapelet_fwd<(NMAX < 0 ? 0 : NMAX)>(c, sd.x, sd.y, shp);
+  if (LL) v += sersic_fwd(c.lens, float(x - c.lxs), float(y - c.lys));
+  return v;
+}
+
+// MASS: 0 SIE, 1 EPL; LL: lens light on (1) or off (0); NMAX: shapelet order (-1: none).
+// Every system of one launch has the same (MASS, LL, NMAX).
+// The pixels [p0, p1) of one particle's model image. The restrict qualifiers tell the compiler
+// that the image stores do not write the particle's constants, which then stay scalar loads.
+template <int MASS, int LL, int NMAX>
+// beta (or null): where beta - x_s of each sub-pixel is kept for the adjoint, [k^2][H][W].
+__device__ __forceinline__ void forward_pixels(const SysDesc& s, const PConst* __restrict__ c,
+                                               const double* cs, const double* s_pw,
+                                               float* __restrict__ out,
+                                               float2* __restrict__ beta, int p0, int p1) {
+  const int W = s.W, k = s.k;
+  // shapelet coefficients held in vector registers for the whole loop (an empty asm with a
+  // vector-register operand): the scalar registers, which the compiler had filled, keep the
+  // other constants instead of reloading them every sub-pixel
+  constexpr int M = NMAX < 0 ? 1 : (NMAX + 1) * (NMAX + 2) / 2;
+  float shp[M];
+#pragma unroll
+  for (int q = 0; q < M; ++q) {
+    shp[q] = NMAX < 0 ? 0.f : c->shp[q];
+    asm("" : "+v"(shp[q]));
+  }
+  for (int pix = p0 + threadIdx.x; pix < p1; pix += blockDim.x) {
+    const int i = pix / W, j = pix - i * W;
+    float sum = 0.f;
+    for (int a = 0; a < k; ++a) {
+      const double y = subpix_coord(s.y0, i * k + a, s.dxs);
+      for (int b = 0; b < k; ++b) {
+        const double x = subpix_coord(s.x0, j * k + b, s.dxs);
+        // the SIE's floored sub-pixel takes the prologue's frozen-radius deflection
+        const bool at_floor = MASS == 0 && i * k + a == c->fl_i && j * k + b == c->fl_j;
+        float2 sd;
+        sum += surface_brightness<MASS, LL, NMAX>(*c, cs, s_pw, x, y, at_floor, shp, sd);
+        if (beta) {  // streamed past the caches: read once, by the adjoint, much later
+          float* bp = reinterpret_cast<float*>(beta + (a * k + b) * (s.H * W) + pix);
+          __builtin_nontemporal_store(sd.x, bp);
+          __builtin_nontemporal_store(sd.y, bp + 1);
+        }
+      }
+    }
+    out[pix] = sum * s.inv_k2;
+  }
+}
 
 // Accumulator slots (per particle, summed over sub-pixels).
 enum AccSlot {

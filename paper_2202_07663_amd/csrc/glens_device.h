@@ -130,11 +130,16 @@ GL_HD void decode_mass(const float* th, int mass, int shear, PConst& c) {
   }
   c.omg1 = 1.0 - c.g1;
   c.opg1 = 1.0 + c.g1;
+  c.ome1 = 1.0 - e1;
+  c.ope1 = 1.0 + e1;
+  c.e12 = 2.0 * e1;
+  c.e22 = 2.0 * e2;
   const double ee = e1 * e1 + e2 * e2, eabs = sqrt(ee);
   const double B = theta_e * sqrt(1.0 - ee);
   c.t = t;
   c.e1 = e1;
   c.e2 = e2;
+  c.ee = ee;
   c.tlnb = t * log(B);
   c.bmass = B;
   c.w2floor = 1e-12 * (1.0 + eabs) * (1.0 + eabs);
@@ -329,9 +334,9 @@ GL_HD void floored_deflection(const PConst& c, int mass, double x, double y, D5&
 }
 
 // Finds the floored sub-pixel of one particle (fills c.fl_*; after decode_mass). Only the
-// sub-pixel nearest the lens centre can have R below the floor.
-GL_HD void decode_floor(const SysDesc& s, PConst& c) {
-  c.fl_i = c.fl_j = -1;
+// sub-pixel nearest the lens centre can have R below the floor. xs: the source centre.
+GL_HD void decode_floor(const SysDesc& s, const float* xs, PConst& c) {
+  c.fl_i = c.fl_j = c.fl_pix = c.fl_sub = -1;
   c.fl_a[0] = c.fl_a[1] = 0.0;
   const double fj = rint((c.xc - s.x0) / s.dxs), fi = rint((c.yc - s.y0) / s.dxs);
   if (!(fj >= 0.0 && fj < double(s.W * s.k) && fi >= 0.0 && fi < double(s.H * s.k))) return;
@@ -344,6 +349,10 @@ GL_HD void decode_floor(const SysDesc& s, PConst& c) {
   floored_deflection(c, s.mass, x, y, ar, ai);
   c.fl_i = ii;
   c.fl_j = jj;
+  c.fl_pix = (ii / s.k) * s.W + jj / s.k;
+  c.fl_sub = (ii % s.k) * s.k + jj % s.k;
+  c.fl_s[0] = float(x - ar.v - (c.g1 * x + c.g2 * y) - double(xs[0]));
+  c.fl_s[1] = float(y - ai.v - (c.g2 * x - c.g1 * y) - double(xs[1]));
   c.fl_a[0] = ar.v;
   c.fl_a[1] = ai.v;
   for (int k = 0; k < 5; ++k) {
@@ -477,7 +486,7 @@ GL_HD double pow_from_table(const double* __restrict__ pw, double w2) {
   p = fma(p, x, a[1]);
   p = fma(p, x, a[0]);
   const int ie = e + kPowExp / 2;
-  return pw[ie < 0 ? 0 : (ie >= kPowExp ? kPowExp - 1 : ie)] * p;
+  return pw[min(max(ie, 0), kPowExp - 1)] * p;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -495,65 +504,55 @@ GL_HD Cx cconj(Cx a) { return {a.r, -a.i}; }
 GL_HD Cx cmuli(Cx a) { return {-a.i, a.r}; }  // i a
 GL_HD float cdot(Cx g, Cx v) { return g.r * v.r + g.i * v.i; }  // real dot product
 
-// EPL / SIE deflection plus shear at image position (x, y), in FP64: returns beta - x_s with
-// beta = x - alpha - alpha_ext. cs: the particle's series coefficients c.c (the kernels pass
-// a copy staged in LDS).
-// at_floor: this is the particle's floored sub-pixel (c.fl_*); the SIE then takes the
-// frozen-radius closed form the prologue evaluated (the EPL's value there is this formula's).
-// cs / pw: the particle's series coefficients c.c and power tables c.pw (staged in LDS).
-template <int MASS>
-GL_HD void ray_trace(const PConst& c, const double* __restrict__ cs,
-                     const double* __restrict__ pw, double x, double y, bool at_floor,
-                     float& sdx, float& sdy) {
-  const double zr = x - c.xc, zi = y - c.yc;
-  const double e1 = c.e1, e2 = c.e2;
-  const double wr = zr - e1 * zr - e2 * zi, wi = zi - e2 * zr + e1 * zi;
-  const double w2 = fmax(wr * wr + wi * wi, c.w2floor);
-  const double inv_w2 = rcp_f64(w2);
-  const double u2r = (wr * wr - wi * wi) * inv_w2, u2i = 2.0 * wr * wi * inv_w2;
-  const double Xr = e1 * u2r + e2 * u2i, Xi = e1 * u2i - e2 * u2r;
-  double Sr, Si, A;
-  if (MASS == 0 && c.sie_closed) {
-    // S_1(X) = atan(zeta) / zeta, zeta = s w / |w|; atan of |zeta| < 1 in closed form
-    const double rinv = sqrt(inv_w2);
-    const double ur = wr * rinv, ui = wi * rinv;
-    const double a = c.sr * ur - c.si * ui, b = c.sr * ui + c.si * ur;
-    const double aa = a * a;
-    const double atr = 0.5 * atan(2.0 * a / (1.0 - c.epsabs));
-    const double ati = 0.25 * log(((1.0 + b) * (1.0 + b) + aa) / ((1.0 - b) * (1.0 - b) + aa));
-    const double ie = 1.0 / c.epsabs;  // S = atan(zeta) conj(zeta) / |eps|
-    Sr = (atr * a + ati * b) * ie;
-    Si = (ati * a - atr * b) * ie;
-    A = c.bmass * rinv;
-  } else {
-    // The coefficients are real, so the series is evaluated at the complex point y = -X by
-    // synthetic division by the real quadratic (v - y)(v - conj y) = v^2 - 2 Re(y) v + |y|^2
-    // (Knuth, TAOCP vol. 2, sec. 4.6.4): b_n = c_n + 2 Re(y) b_(n+1) - |y|^2 b_(n+2) from the
-    // top down to n = 0, and the sum is b_0 - Re(y) b_1 + i Im(y) b_1. That is two real FMAs
-    // per term where complex Horner takes four. |y| = |eps| < 1, so rounding errors made
-    // early are damped as the recurrence runs down. Terms are taken two per trip (so that the
-    // two carried values need no register moves); coefficients past the series length are
-    // zero, so rounding the length up to an even number is exact.
-    const double yr = -Xr, yi = -Xi;
-    const double r2 = 2.0 * yr, yy = fma(yr, yr, yi * yi);
-    double b1 = 0.0, b2 = 0.0;  // b_(n+1), b_(n+2)
-    const int nt2 = (c.nterms + 1) & ~1;
-    for (int n0 = nt2 - 2; n0 >= 0; n0 -= 2) {  // leaves b_n0 in b1 and b_(n0+1) in b2
-      b2 = fma(r2, b1, fma(-yy, b2, cs[n0 + 1]));
-      b1 = fma(r2, b2, fma(-yy, b1, cs[n0]));
-    }
-    Sr = fma(-yr, b2, b1);
-    Si = yi * b2;
-    A = pow_from_table(pw, w2);
+// EPL / SIE deflection plus shear at image position x, in FP64: beta - x_s with beta = x - alpha
+// - alpha_ext. The row's y enters through RayRow, so that w takes one FMA per component. Both
+// masses take the series (the SIE is t = 1, its power table's A = B / |w|): the closed form of
+// the SIE, a complex arctangent, costs three times the instructions of the longest series kept
+// (|eps| = 0.6) and is kept for the sampler's launches only (glens_chain.h).
+// The radius is not floored here (|w|^2 is above its floor and |X| = |eps|): at the particle's
+// floored sub-pixel, if it has one, the result is not finite or not used, and the caller takes
+// the prologue's c.fl_s instead.
+// pw: the particle's power tables c.pw (staged in LDS); yy: c.ee, in vector registers (an FMA
+// reads one scalar operand, and that is the series coefficient).
+struct RayRow {
+  double wr, wi;       // w = (1 - e1) x + wr, -e2 x + wi
+  double ax, ay;       // -g2 y - x_s, (1 + g1) y - y_s
+};
+__device__ __forceinline__ RayRow ray_row(const PConst& c, double y) {
+  const double zi = y - c.yc;
+  return {fma(-c.e2, zi, -c.ome1 * c.xc), fma(c.ope1, zi, c.e2 * c.xc), fma(-c.g2, y, -c.sxs),
+          fma(c.opg1, y, -c.sys)};
+}
+__device__ __forceinline__ void ray_trace(const PConst& c, const double* __restrict__ cs,
+                                          const double* __restrict__ pw, double yy, double x,
+                                          const RayRow& row, float& sdx, float& sdy) {
+  const double wr = fma(c.ome1, x, row.wr), wi = fma(-c.e2, x, row.wi);
+  const double wi2 = wi * wi;
+  const double w2 = fma(wr, wr, wi2);
+  const double inv = rcp_f64(w2);
+  const double pr = fma(wr, wr, -wi2), pi = wr * wi;  // w^2 = pr + 2 i pi
+  const double Xr = inv * fma(c.e1, pr, c.e22 * pi), Xi = inv * fma(c.e12, pi, -c.e2 * pr);
+  // The coefficients are real, so the series is evaluated at the complex point y = -X by
+  // synthetic division by the real quadratic (v - y)(v - conj y) = v^2 - 2 Re(y) v + |y|^2
+  // (Knuth, TAOCP vol. 2, sec. 4.6.4): b_n = c_n + 2 Re(y) b_(n+1) - |y|^2 b_(n+2) from the
+  // top down to n = 0, and the sum is b_0 - Re(y) b_1 + i Im(y) b_1. That is two real FMAs
+  // per term where complex Horner takes four. |y| = |eps| < 1, so rounding errors made
+  // early are damped as the recurrence runs down. Terms are taken two per trip (so that the
+  // two carried values need no register moves); coefficients past the series length are
+  // zero, so rounding the length up to an even number is exact.
+  const double r2 = -2.0 * Xr;
+  double b1 = 0.0, b2 = 0.0;  // b_(n+1), b_(n+2)
+  const int nt2 = (c.nterms + 1) & ~1;
+  for (int n0 = nt2 - 2; n0 >= 0; n0 -= 2) {  // leaves b_n0 in b1 and b_(n0+1) in b2
+    b2 = fma(r2, b1, fma(-yy, b2, cs[n0 + 1]));
+    b1 = fma(r2, b2, fma(-yy, b1, cs[n0]));
   }
-  double ar = A * (wr * Sr - wi * Si), ai = A * (wr * Si + wi * Sr);
-  if (MASS == 0 && at_floor) {
-    ar = c.fl_a[0];
-    ai = c.fl_a[1];
-  }
+  const double Sr = fma(Xr, b2, b1), Sm = Xi * b2;  // S = Sr - i Sm
+  const double A = pow_from_table(pw, w2);
+  const double tr = fma(wr, Sr, wi * Sm), ti = fma(wi, Sr, -wr * Sm);
   // beta - x_s = x - alpha - alpha_ext - x_s
-  sdx = float(x - ar - (c.g1 * x + c.g2 * y) - c.sxs);
-  sdy = float(y - ai - (c.g2 * x - c.g1 * y) - c.sys);
+  sdx = float(fma(-A, tr, fma(x, c.omg1, row.ax)));
+  sdy = float(fma(-A, ti, fma(x, -c.g2, row.ay)));
 }
 
 // The mass terms of one sub-pixel, added to acc (FP32): z the offset from the lens centre, alpha

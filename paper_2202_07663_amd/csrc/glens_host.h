@@ -110,6 +110,7 @@ int launch_prologue(const Group& g, hipStream_t st);
 int launch_subpix_fwd(int key, const Group& g, hipStream_t st);
 int launch_conv(int K, const Group& g, size_t lds_bytes, hipStream_t st);
 int launch_subpix_adj(int key, const Group& g, hipStream_t st);
+int launch_chain_fwd(int key, const Group& g, hipStream_t st);
 int launch_chain_adj(int key, const Group& g, hipStream_t st);
 int launch_finalize(const Group& g, hipStream_t st);
 size_t conv_lds_bytes(int H, int W, int K, int mode);
@@ -129,8 +130,8 @@ void conv_bands(int P, int H, int W, int* bands, int* band_rows, int* split);
 // ev (optional): GL_NSTAGES + 1 events, recorded before the first and after every stage.
 // prologue = false skips the decode (the particles' constants are already those of their
 // current parameters); finalize = false stops after the sub-pixel adjoint (the caller runs
-// finalize_particle itself, fused with its own per-particle step); chain: the sampler's adjoint
-// (glens_chain.h), whose accumulators finalize_particle<true> reads.
+// finalize_particle itself, fused with its own per-particle step); chain: the sampler's
+// sub-pixel passes (glens_chain.h), whose accumulators finalize_particle<true> reads.
 int run_group(Group& g, int key, int K, int mode, hipStream_t st, hipEvent_t* ev = nullptr,
               bool prologue = true, bool finalize = true, bool chain = false);
 

@@ -36,29 +36,18 @@ __global__ void __launch_bounds__(64) prologue_kernel(Group g) {
 // ------------------------------------------------------------------------------------------
 // sub-pixel forward: lanes own pixels, loop over the k x k sub-pixels
 // ------------------------------------------------------------------------------------------
-template <int MASS, int LL, int NMAX>
-__device__ __forceinline__ float surface_brightness(const PConst& c, const double* cs,
-                                                    const double* s_pw, double x, double y,
-                                                    bool at_floor, const float* shp,
-                                                    float2& sd) {
-  ray_trace<MASS>(c, cs, s_pw, x, y, at_floor, sd.x, sd.y);
-  float v = sersic_fwd(c.src, sd.x, sd.y);
-  if (NMAX >= 0) v += shapelet_fwd<(NMAX < 0 ? 0 : NMAX)>(c, sd.x, sd.y, shp);
-  if (LL) v += sersic_fwd(c.lens, float(x - c.lxs), float(y - c.lys));
-  return v;
-}
-
-// MASS: 0 SIE, 1 EPL; LL: lens light on (1) or off (0); NMAX: shapelet order (-1: none).
-// Every system of one launch has the same (MASS, LL, NMAX).
+// LL: lens light on (1) or off (0); NMAX: shapelet order (-1: none). Every system of one launch
+// has the same (LL, NMAX).
 // The pixels [p0, p1) of one particle's model image. The restrict qualifiers tell the compiler
 // that the image stores do not write the particle's constants, which then stay scalar loads.
-template <int MASS, int LL, int NMAX>
 // beta (or null): where beta - x_s of each sub-pixel is kept for the adjoint, [k^2][H][W].
+template <int LL, int NMAX>
 __device__ __forceinline__ void forward_pixels(const SysDesc& s, const PConst* __restrict__ c,
-                                               const double* cs, const double* s_pw,
-                                               float* __restrict__ out,
+                                               const double* s_pw, float* __restrict__ out,
                                                float2* __restrict__ beta, int p0, int p1) {
-  const int W = s.W, k = s.k;
+  const int W = s.W, HW = s.H * W, k = s.k;
+  const int fl_sub = c->fl_sub;
+  const double dxs = s.dxs;
   // shapelet coefficients held in vector registers for the whole loop (an empty asm with a
   // vector-register operand): the scalar registers, which the compiler had filled, keep the
   // other constants instead of reloading them every sub-pixel
@@ -69,21 +58,34 @@ __device__ __forceinline__ void forward_pixels(const SysDesc& s, const PConst* _
     shp[q] = NMAX < 0 ? 0.f : c->shp[q];
     asm("" : "+v"(shp[q]));
   }
-  for (int pix = p0 + threadIdx.x; pix < p1; pix += blockDim.x) {
-    const int i = pix / W, j = pix - i * W;
+  double yy = c->ee;
+  asm("" : "+v"(yy));
+  PixelWalk w(W, p0);
+  for (int pix = p0 + threadIdx.x; pix < p1; pix += blockDim.x, w.next()) {
+    const double xj = subpix_coord(s.x0, w.j * k, dxs);
+    char* bp = reinterpret_cast<char*>(beta);  // uniform: the lane adds its 32-bit offset
+    const unsigned off = unsigned(pix) * unsigned(sizeof(float2));
     float sum = 0.f;
     for (int a = 0; a < k; ++a) {
-      const double y = subpix_coord(s.y0, i * k + a, s.dxs);
-      for (int b = 0; b < k; ++b) {
-        const double x = subpix_coord(s.x0, j * k + b, s.dxs);
-        // the SIE's floored sub-pixel takes the prologue's frozen-radius deflection
-        const bool at_floor = MASS == 0 && i * k + a == c->fl_i && j * k + b == c->fl_j;
-        float2 sd;
-        sum += surface_brightness<MASS, LL, NMAX>(*c, cs, s_pw, x, y, at_floor, shp, sd);
+      const double y = subpix_coord(s.y0, w.i * k + a, dxs);
+      const RayRow row = ray_row(*c, y);
+      const float ly = float(y - c->lys);
+      double x = xj;
+      for (int b = 0; b < k; ++b, x += dxs, bp += HW * sizeof(float2)) {
+        float sdx, sdy;
+        ray_trace(*c, c->c, s_pw, yy, x, row, sdx, sdy);
+        if (a * k + b == fl_sub && pix == c->fl_pix) {  // the first test is wave-uniform
+          sdx = c->fl_s[0];
+          sdy = c->fl_s[1];
+        }
+        float v = sersic_fwd(c->src, sdx, sdy);
+        if (NMAX >= 0) v += shapelet_fwd<(NMAX < 0 ? 0 : NMAX)>(*c, sdx, sdy, shp);
+        if (LL) v += sersic_fwd(c->lens, float(x - c->lxs), ly);
+        sum += v;
         if (beta) {  // streamed past the caches: read once, by the adjoint, much later
-          float* bp = reinterpret_cast<float*>(beta + (a * k + b) * (s.H * W) + pix);
-          __builtin_nontemporal_store(sd.x, bp);
-          __builtin_nontemporal_store(sd.y, bp + 1);
+          float* p = reinterpret_cast<float*>(bp + off);
+          __builtin_nontemporal_store(sdx, p);
+          __builtin_nontemporal_store(sdy, p + 1);
         }
       }
     }
@@ -91,8 +93,15 @@ __device__ __forceinline__ void forward_pixels(const SysDesc& s, const PConst* _
   }
 }
 
-template <int MASS, int LL, int NMAX>
-__global__ void __launch_bounds__(kSubThreads) subpix_fwd_kernel(Group g) {
+// Bound by VALU issue at large batches: 172 instructions per sub-pixel at 60 x 60, n_max 6 (190
+// with w and beta - x_s formed term by term), 36 of them the FP64 series. The register cap keeps
+// six waves per SIMD (five from n_max = 7, whose coefficients alone take 36 or 45 registers):
+// left to itself the compiler takes 83 registers and five waves. Measured: 312 -> 291 us (60 x 60,
+// 4096 vectors, log L), 149 -> 76 us (53 x 37 SIE + lens light, k = 3, 777 vectors; its closed
+// form needed 116 registers and two library transcendentals per sub-pixel).
+template <int LL, int NMAX>
+__global__ void __launch_bounds__(kSubThreads)
+__attribute__((amdgpu_waves_per_eu(NMAX >= 7 ? 5 : 6))) subpix_fwd_kernel(Group g) {
   const int si = find_sys(g, blockIdx.x);
   const SysDesc& s = g.sys[si];
   const int lb = blockIdx.x - g.block0[si];
@@ -108,7 +117,8 @@ __global__ void __launch_bounds__(kSubThreads) subpix_fwd_kernel(Group g) {
   const int p0 = tile * s.fpix_per_tile;
   const int p1 = min(HW, p0 + s.fpix_per_tile);
   float2* beta = s.mode == 2 && s.beta ? s.beta + (size_t)part * s.k * s.k * HW : nullptr;
-  forward_pixels<MASS, LL, NMAX>(s, &c, c.c, s_pw, s.m0 + (size_t)part * HW, beta, p0, p1);
+  float* out = s.m0 + (size_t)part * HW;
+  forward_pixels<LL, NMAX>(s, &c, s_pw, out, beta, p0, p1);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -462,26 +472,6 @@ __device__ __forceinline__ void mfma_pass(MfmaPass& P, const uint16_t* x, int ne
   }
 }
 
-// Row and column of the pixels idx = threadIdx.x + n blockDim.x of a W-column image, stepped
-// without a division per pixel.
-struct PixelWalk {
-  int i, j, di, dj, W;
-  __device__ __forceinline__ PixelWalk(int W_) : W(W_) {
-    i = int(threadIdx.x) / W;
-    j = int(threadIdx.x) - i * W;
-    di = int(blockDim.x) / W;
-    dj = int(blockDim.x) - di * W;
-  }
-  __device__ __forceinline__ void next() {
-    i += di;
-    j += dj;
-    if (j >= W) {
-      j -= W;
-      ++i;
-    }
-  }
-};
-
 // One block per particle. Its size (launch_conv_mfma) is what fills a CU: 256 threads where four
 // blocks fit a CU's LDS (four waves per SIMD at the 128 registers allowed here), 512 or 1024
 // where the image leaves room for two or one, or where the batch has too few particles for
@@ -736,11 +726,13 @@ __device__ __forceinline__ void adj_pixels(const SysDesc& s, const PConst& c,
   const int HW = s.H * s.W, W = s.W, k = s.k;
   const int fl_i = c.fl_i, fl_j = c.fl_j;
   const double dxs = s.dxs;
-  for (int pix = p0 + threadIdx.x; pix < p1; pix += blockDim.x) {
-    const int i = pix / W, j = pix - i * W;
+  PixelWalk w(W, p0);
+  for (int pix = p0 + threadIdx.x; pix < p1; pix += blockDim.x, w.next()) {
+    const int i = w.i, j = w.j;
     const float sb = sbar[pix];
     const double xj = subpix_coord(s.x0, j * k, dxs);
-    const float2* bp = beta + pix;
+    const char* bp = reinterpret_cast<const char*>(beta);  // uniform, as in the forward pass
+    const unsigned off = unsigned(pix) * unsigned(sizeof(float2));
     for (int a = 0; a < k; ++a) {
       const double y = subpix_coord(s.y0, i * k + a, dxs);
       const float zi = float(y - c.yc), ly = float(y - c.lys);
@@ -748,9 +740,10 @@ __device__ __forceinline__ void adj_pixels(const SysDesc& s, const PConst& c,
       const double cx = -c.g2 * y - c.sxs, cy = c.opg1 * y - c.sys;
       const float lpx = c.lens.bs * ly, lpy = c.lens.cs * ly;
       double x = xj;
-      for (int b = 0; b < k; ++b, x += dxs, bp += HW) {
-        const float sdx = __builtin_nontemporal_load(&bp->x);
-        const float sdy = __builtin_nontemporal_load(&bp->y);
+      for (int b = 0; b < k; ++b, x += dxs, bp += HW * sizeof(float2)) {
+        const float* p = reinterpret_cast<const float*>(bp + off);
+        const float sdx = __builtin_nontemporal_load(p);
+        const float sdy = __builtin_nontemporal_load(p + 1);
         // g: sb d(source light)/d(beta)
         const float px = fmaf(c.src.as, sdx, c.src.bs * sdy);
         const float py = fmaf(c.src.cs, sdy, c.src.bs * sdx);

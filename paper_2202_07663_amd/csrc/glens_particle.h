@@ -55,7 +55,7 @@ __device__ __forceinline__ void prologue_particle(const SysDesc& s, int p) {
   // lane 63 looks for the floored sub-pixel; the others fill the power tables (both from
   // decode_mass's constants, written before the barrier)
   if (lane == 63)
-    decode_floor(s, c);
+    decode_floor(s, th + mass_param_count(s.mass, s.shear) + (s.lens_light ? 7 : 0) + 4, c);
   else
     pow_tables_lane(c.t, log2(c.bmass), lane, 63, c.pw);
   if (lane < kMaxTerms) series_store(c, lane, cn, dsum);

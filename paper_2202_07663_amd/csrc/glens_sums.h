@@ -1,5 +1,5 @@
-// What the sub-pixel adjoint kernels share: the staged derivative series and the FP64 sums of
-// their per-lane accumulators.
+// What the sub-pixel kernels share: their walk over the pixels, the staged derivative series and
+// the FP64 sums of the adjoint's per-lane accumulators.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -9,6 +9,26 @@
 namespace glens {
 
 constexpr int kSubThreads = 256;
+
+// Row and column of the pixels p0 + threadIdx.x + n blockDim.x of a W-column image, stepped
+// without a division per pixel.
+struct PixelWalk {
+  int i, j, di, dj, W;
+  __device__ __forceinline__ PixelWalk(int W_, int p0 = 0) : W(W_) {
+    i = (p0 + int(threadIdx.x)) / W;
+    j = p0 + int(threadIdx.x) - i * W;
+    di = int(blockDim.x) / W;
+    dj = int(blockDim.x) - di * W;
+  }
+  __device__ __forceinline__ void next() {
+    i += di;
+    j += dj;
+    if (j >= W) {
+      j -= W;
+      ++i;
+    }
+  }
+};
 
 // Copies the particle's derivative-series coefficients to LDS (read uniformly by every lane),
 // those of dS/dt times `scale`.

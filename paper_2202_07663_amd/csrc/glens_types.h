@@ -88,6 +88,7 @@ struct PConst {
   double e1, e2;       // clamped mass eccentricities
   double xc, yc, g1, g2;
   double omg1, opg1;   // 1 - g1, 1 + g1
+  double ome1, ope1, e12, e22, ee;  // 1 - e1, 1 + e1, 2 e1, 2 e2, |eps|^2
   double tlnb;         // t ln B, B = theta_E sqrt(1 - |eps|^2)
   double bmass;        // B
   double w2floor;      // R^2 floor expressed on |w|^2: 1e-12 (1 + |eps|)^2
@@ -107,6 +108,8 @@ struct PConst {
   // x_c, y_c) (clamped eccentricities), all FP64. The adjoint adds that sub-pixel's mass terms
   // from these instead of from its per-lane Jacobian.
   int fl_i, fl_j;
+  int fl_pix, fl_sub;  // its pixel, and its index among the pixel's k^2 sub-pixels (-1: none)
+  float fl_s[2];       // beta - x_s there
   double fl_a[2];
   double fl_d[5][2];
   double sxs, sys;     // source centre
