@@ -332,8 +332,13 @@ SysDesc make_sys(const SystemData& sd, const Workspace& ws, int P, int tiles) {
   // matrix-core PSF pass for whole-image launches when the image's tiles and LDS fit; the
   // choice depends on this system alone, so its results do not depend on its launch partners
   const MfmaGeom q = mfma_geom(c.H, c.W, c.K);
-  s.conv_mfma = sd.psf_mfma && s.bands == 1 && q.T <= kMfmaMaxTiles &&
-                size_t(mfma_lds_bytes(q, c.H, c.W)) <= kConvLdsMax;
+  const bool fits = sd.psf_mfma && q.T <= kMfmaMaxTiles &&
+                    size_t(mfma_lds_bytes(q, c.H, c.W)) <= kConvLdsMax;
+  s.conv_mfma = fits && s.bands == 1;
+  // the adjoint half of a banded pass: from about 2e8 products the matrix cores win over the VALU
+  // kernel's shorter latency (60 x 60, K = 21: 64 vectors, 1.0e8, 13.2 us against 10.2; 80 x 80, 300
+  // vectors, 8.5e8, 33.3 against 43.4)
+  s.adj_mfma = fits && s.bands > 1 && double(P) * HW * c.K * c.K >= 2e8;
   return s;
 }
 
@@ -434,6 +439,17 @@ int launch_finalize(const Group& g, hipStream_t st) {
   return launch(finalize_kernel, g.block0[g.nsys], 64, 0, g, st);
 }
 
+// Block offsets of each system for one stage.
+template <class F>
+static void set_blocks(Group& g, F per_sys) {
+  int b = 0;
+  for (int i = 0; i < g.nsys; ++i) {
+    g.block0[i] = b;
+    b += per_sys(g.sys[i]);
+  }
+  g.block0[g.nsys] = b;
+}
+
 size_t conv_lds_bytes(int H, int W, int K, int mode) {
   const int nstrip = (H + kConvRows - 1) / kConvRows;
   const size_t np = size_t((nstrip * kConvRows + K - 1) | 1) * (W + K - 1);
@@ -467,7 +483,19 @@ static int conv_lds_limit(size_t lds) {
 // Static LDS of the matrix-core kernel (the reduction buffers), rounded up.
 constexpr int kMfmaStaticLds = 256;
 
-static int launch_conv_mfma(const Group& g, size_t lds, hipStream_t st) {
+// Systems with take(s): block offsets are set here.
+template <class F>
+static int launch_conv_mfma(Group& g, F take, hipStream_t st) {
+  size_t lds = 0;
+  int tiles = 0;
+  for (int i = 0; i < g.nsys; ++i) {
+    const SysDesc& s = g.sys[i];
+    if (!take(s)) continue;
+    const MfmaGeom q = mfma_geom(s.H, s.W, s.K);
+    lds = std::max(lds, size_t(mfma_lds_bytes(q, s.H, s.W)));
+    tiles = std::max(tiles, q.T);
+  }
+  set_blocks(g, [&](const SysDesc& s) { return take(s) ? blocks_conv(s) : 0; });
   int rc = conv_lds_limit(lds);
   if (rc) return rc;
   // sixteen waves per CU (four per SIMD), from the blocks that its LDS holds and the batch has;
@@ -475,10 +503,6 @@ static int launch_conv_mfma(const Group& g, size_t lds, hipStream_t st) {
   const int blocks = g.block0[g.nsys];
   const int per_cu = std::min(int(160 * 1024 / (lds + kMfmaStaticLds)), blocks / 256);
   int threads = per_cu >= 4 ? 256 : (per_cu >= 2 ? 512 : kMfmaMaxThreads);
-  int tiles = 0;
-  for (int i = 0; i < g.nsys; ++i)
-    if (g.sys[i].conv_mfma)
-      tiles = std::max(tiles, mfma_geom(g.sys[i].H, g.sys[i].W, g.sys[i].K).T);
   while (threads > 256 && threads / 64 * 2 > tiles) threads /= 2;
   return launch(conv_mfma_kernel, blocks, threads, lds, g, st);
 }
@@ -497,19 +521,8 @@ int launch_conv(int K, const Group& g, size_t lds, hipStream_t st) {
 
 
 
-// Block offsets of each system for one stage.
-template <class F>
-static void set_blocks(Group& g, F per_sys) {
-  int b = 0;
-  for (int i = 0; i < g.nsys; ++i) {
-    g.block0[i] = b;
-    b += per_sys(g.sys[i]);
-  }
-  g.block0[g.nsys] = b;
-}
-
 // The banded PSF pass (small batches): block offsets are set here for each kernel.
-static int launch_conv_band(int K, Group& g, int mode, hipStream_t st) {
+static int launch_conv_band(int K, Group& g, int mode, bool chain, hipStream_t st) {
   size_t lds = 0;
   for (int i = 0; i < g.nsys; ++i) {
     const SysDesc& s = g.sys[i];
@@ -522,8 +535,23 @@ static int launch_conv_band(int K, Group& g, int mode, hipStream_t st) {
   set_blocks(g, [](const SysDesc& s) { return s.conv_mfma ? 0 : blocks_conv_band(s); });
   if ((rc = launch(conv_table().band[(K - 1) / 2], g.block0[g.nsys], kConvThreads, lds, g, st)))
     return rc;
-  if (mode == 2)
-    return launch(conv_table().band_adj[(K - 1) / 2], g.block0[g.nsys], kConvThreads, lds, g, st);
+  if (mode == 2) {
+    // the sampler's chains keep the VALU sums (glens_chain.h)
+    const auto on_mfma = [chain](const SysDesc& s) { return s.adj_mfma && !chain; };
+    bool any_mfma = false;
+    for (int i = 0; i < g.nsys; ++i) any_mfma = any_mfma || on_mfma(g.sys[i]);
+    set_blocks(g, [&](const SysDesc& s) {
+      return s.conv_mfma || on_mfma(s) ? 0 : blocks_conv_band(s);
+    });
+    if ((rc = launch(conv_table().band_adj[(K - 1) / 2], g.block0[g.nsys], kConvThreads, lds, g,
+                     st)))
+      return rc;
+    if (!any_mfma) return GL_OK;
+    for (int i = 0; i < g.nsys; ++i) g.sys[i].mode = 3;
+    rc = launch_conv_mfma(g, on_mfma, st);
+    for (int i = 0; i < g.nsys; ++i) g.sys[i].mode = mode;
+    return rc;
+  }
   if (mode == 1) {
     set_blocks(g, [](const SysDesc& s) { return s.conv_mfma ? 0 : (s.P + 63) / 64; });
     return launch(conv_band_sum_kernel, g.block0[g.nsys], 64, 0, g, st);
@@ -547,14 +575,13 @@ int run_group(Group& g, int key, int K, int mode, hipStream_t st, hipEvent_t* ev
   GL_HIP(mark(2));
   // PSF pass: systems flagged for matrix cores in one launch, the others in the banded or the
   // whole-image VALU kernels (a system with one band gets the same bits from either)
-  size_t lds = 0, lds_mfma = 0;
+  size_t lds = 0;
   bool banded = false, any_mfma = false, any_valu = false;
   for (int i = 0; i < g.nsys; ++i) {
     SysDesc& s = g.sys[i];
     s.mode = mode;
     if (s.conv_mfma) {
       any_mfma = true;
-      lds_mfma = std::max(lds_mfma, size_t(mfma_lds_bytes(mfma_geom(s.H, s.W, s.K), s.H, s.W)));
     } else {
       any_valu = true;
       lds = std::max(lds, conv_lds_bytes(s.H, s.W, K, mode));
@@ -562,11 +589,11 @@ int run_group(Group& g, int key, int K, int mode, hipStream_t st, hipEvent_t* ev
     }
   }
   if (any_mfma) {
-    set_blocks(g, [](const SysDesc& s) { return s.conv_mfma ? blocks_conv(s) : 0; });
-    if ((rc = launch_conv_mfma(g, lds_mfma, st))) return rc;
+    const auto on_mfma = [](const SysDesc& s) { return s.conv_mfma != 0; };
+    if ((rc = launch_conv_mfma(g, on_mfma, st))) return rc;
   }
   if (any_valu && banded) {
-    if ((rc = launch_conv_band(K, g, mode, st))) return rc;
+    if ((rc = launch_conv_band(K, g, mode, chain, st))) return rc;
   } else if (any_valu) {
     set_blocks(g, [](const SysDesc& s) { return s.conv_mfma ? 0 : blocks_conv(s); });
     if ((rc = launch_conv(K, g, lds, st))) return rc;

@@ -472,6 +472,19 @@ __device__ __forceinline__ void mfma_pass(MfmaPass& P, const uint16_t* x, int ne
   }
 }
 
+// log L and chi^2 of one particle from its bands' partial sums.
+__device__ __forceinline__ void band_totals(const SysDesc& s, int part) {
+  const double* lp = s.lpart + (size_t)part * kConvMaxBands * 2;
+  double tot = 0.0, ctot = 0.0;
+  for (int q = 0; q < s.bands; ++q) {
+    tot += lp[2 * q];
+    ctot += lp[2 * q + 1];
+  }
+  const double v = -0.5 * tot;
+  s.logl[part] = isfinite(v) ? v : -INFINITY;
+  if (s.chi2) s.chi2[part] = ctot;
+}
+
 // One block per particle. Its size (launch_conv_mfma) is what fills a CU: 256 threads where four
 // blocks fit a CU's LDS (four waves per SIMD at the 128 registers allowed here), 512 or 1024
 // where the image leaves room for two or one, or where the batch has too few particles for
@@ -482,7 +495,9 @@ __device__ __forceinline__ void mfma_pass(MfmaPass& P, const uint16_t* x, int ne
 // (matrix cores 34, row shifts and LDS reads of the new rows the rest: reloading either part of
 // the fragments from LDS instead of shifting it measured 278 us for the kernel, both 394), the
 // likelihood terms 22.
-// mode 3: only the adjoint pass, from the seed that the banded forward kernel left in memory.
+// mode 3: only the adjoint pass, from the seed that the banded forward kernel left in memory (and
+// log L from its bands' partial sums). Against the banded VALU
+// adjoint: 43 -> 33 us (80 x 80, 300 vectors), 52 -> 35 us (500).
 __global__ void __launch_bounds__(kMfmaMaxThreads) __attribute__((amdgpu_waves_per_eu(4)))
 conv_mfma_kernel(Group g) {
   extern __shared__ __align__(16) uint16_t xlds[];
@@ -516,7 +531,9 @@ conv_mfma_kernel(Group g) {
   __syncthreads();
   MfmaPass P{q, int(blockDim.x) >> 6, -(sx + s.psf_mfma_exp), H, W, mode, s.s2b, s.inv_gt,
              s.inv_k2, s.obs, (mode == 0 ? s.img : s.sbar) + (size_t)part * HW, seed, 0.0, 0.0};
-  if (!adj_only) {
+  if (adj_only) {
+    if (threadIdx.x == 0) band_totals(s, part);
+  } else {
     mfma_pass<false>(P, xlds, nel, s.psf_mfma, K);
     if (mode == 0) return;
     const double tot = block_sum(P.ll, red);
@@ -551,7 +568,9 @@ conv_mfma_kernel(Group g) {
 //   conv_band_kernel       the PSF, the likelihood terms (partial sums per band) and the
 //                          adjoint seed of each pixel (to a [P][H][W] buffer);
 //   conv_band_adj_kernel   the correlation of the seed with the PSF; the first band of a
-//                          particle also adds the likelihood partials (band order);
+//                          particle also adds the likelihood partials (band order). Where the
+//                          matrix-core kernel takes the system it does this instead (mode 3),
+//                          except for the sampler's chains;
 //   conv_band_sum_kernel   the same addition when there is no adjoint pass.
 // With band_split = 1 the arithmetic per pixel is that of conv_kernel (only the order of the
 // log L sum differs). Very small batches split each strip's K PSF columns over G = 2 or 4
@@ -655,19 +674,6 @@ __global__ void __launch_bounds__(kConvThreads) conv_band_kernel(Group g) {
     lp[0] = tot;
     lp[1] = ctot;
   }
-}
-
-// log L and chi^2 of one particle from its bands' partial sums.
-__device__ __forceinline__ void band_totals(const SysDesc& s, int part) {
-  const double* lp = s.lpart + (size_t)part * kConvMaxBands * 2;
-  double tot = 0.0, ctot = 0.0;
-  for (int q = 0; q < s.bands; ++q) {
-    tot += lp[2 * q];
-    ctot += lp[2 * q + 1];
-  }
-  const double v = -0.5 * tot;
-  s.logl[part] = isfinite(v) ? v : -INFINITY;
-  if (s.chi2) s.chi2[part] = ctot;
 }
 
 template <int K>

@@ -165,6 +165,7 @@ struct SysDesc {
   const uint4* psf_mfma; // [2][K][64 lanes][2 parts] Toeplitz fragments (flipped, plain)
   int psf_mfma_exp;      // the fragments hold psf 2^psf_mfma_exp
   int conv_mfma;         // 1: PSF pass on matrix cores
+  int adj_mfma;          // 1: the banded pass's adjoint half on matrix cores
   const float* theta;    // [P][d] physical parameters, or null if z is given
   float* z;              // [P][d] unconstrained parameters (fit), or null
   const Prior* prior;    // [d] (fit)
