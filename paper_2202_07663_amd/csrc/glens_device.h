@@ -96,11 +96,6 @@ GL_HD void decode_light(const float* th, LightC& L) {
   L.e1 = float(e1);
   L.e2 = float(e2);
   L.inv1me2 = float(den);
-  const double ire2 = 1.0 / (re * re);
-  L.as = float((1.0 + ee - 2.0 * e1) * den * ire2);
-  L.bs = float(-2.0 * e2 * den * ire2);
-  L.cs = float((1.0 + ee + 2.0 * e1) * den * ire2);
-  L.fls = float(double(kR2Floor) * ire2);
   L.kqi = float(-(1.9992 * n - 0.3271) / n * double(th[6]));
   L.j11 = float(j11);
   L.j12 = float(j12);
@@ -675,18 +670,18 @@ GL_HD float sersic_fwd(const LightC& L, float dx, float dy) {
 }
 
 // Accumulator terms (weight sb) of the lens light or the source, and s of LightSlot. With the
-// half gradient (px, py) = (as dx + bs dy, bs dx + cs dy) of Q = R^2 / R_eff^2 = dx px + dy py,
-// log2(rho) = log2(Q) / (2n) and dI/d(dx, dy) = s (px, py), s = I0 (-b_n / n) E rho / Q. The
-// sums over the ellipticity terms are combinations of s dx^2, s dx dy and s dy^2 (R^2 itself is
-// one), so only these three are kept, and I0 multiplies the sums instead of their terms.
+// half gradient (px, py) = (qa dx + qb dy / 2, qb dx / 2 + qc dy) of R^2 = dx px + dy py,
+// dI/d(dx, dy) = s (px, py), s = I0 (-b_n / n) E rho / R^2. The sums over the ellipticity terms
+// are combinations of s dx^2, s dx dy and s dy^2 (s R^2 itself is one), so only these three are
+// kept, and I0 multiplies the sums instead of their terms.
 __device__ __forceinline__ float sersic_adj(const LightC& L, float dx, float dy, float px,
                                             float py, float sb, float* acc) {
   const float q0 = fmaf(dx, px, dy * py);
-  const float q = fmaxf(q0, L.fls);  // a NaN offset has made log L non-finite already
-  const float l2rho = log2_f32(q) * L.inv2n;
+  const float q = fmaxf(q0, kR2Floor);  // a NaN offset has made log L non-finite already
+  const float l2rho = fmaf(log2_f32(q), L.inv2n, -L.l2re_n);
   const float rho = exp2_f32(l2rho);
   const float sE = sb * exp2_f32(fmaf(-L.bnl, rho, L.bnl)), sEr = sE * rho;
-  const float s = q0 < L.fls ? 0.0f : sEr * L.kqi * rcp_f32(q);
+  const float s = q0 < kR2Floor ? 0.0f : sEr * L.kqi * rcp_f32(q);
   acc[L_E] += sE;
   acc[L_RHO] += sEr;
   acc[L_RHOLN] = fmaf(sEr, l2rho, acc[L_RHOLN]);
@@ -848,20 +843,19 @@ GL_HD void source_light_grad(const PConst& c, int nmax, double sdx, double sdy, 
 // ------------------------------------------------------------------------------------------
 // offsets: the centre slots hold s dx, s dy (lens light) instead of the gradient itself (source).
 GL_HD void light_grad(const LightC& L, const double* a, bool offsets, float* g) {
-  const double i0 = L.i0, n = L.n, re2 = double(L.re) * L.re;
-  const double rho = i0 * a[L_RHO], rho1 = i0 * (a[L_RHO] - a[L_E]);
-  g[0] = float(rho * L.bn / (n * L.re));                                       // R_eff
-  g[1] = float(-1.9992 * rho1 + L.bn / n * kLn2 * i0 * a[L_RHOLN]);            // n
-  // sum s R^2 / R_eff^2 (as, bs, cs) and the two eccentricity sums, over R_eff^2
-  const double xx = a[L_XX] / re2, xy = a[L_XY] / re2, yy = a[L_YY] / re2;
-  const double r2q = xx + yy + re2 * (L.as * xx + 2.0 * L.bs * xy + L.cs * yy);
+  const double i0 = L.i0, bnn = L.bn / double(L.n);
+  g[0] = float(i0 * a[L_RHO] * (bnn / L.re));                                  // R_eff
+  g[1] = float(i0 * (bnn * kLn2 * a[L_RHOLN] - 1.9992 * (a[L_RHO] - a[L_E])));  // n
+  // sum s R^2 and the two eccentricity sums
+  const double xx = a[L_XX], xy = a[L_XY], yy = a[L_YY];
+  const double r2q = xx + yy + L.qa * xx + L.qb * xy + L.qc * yy;
   const double ge1 = L.inv1me2 * (L.e1 * r2q + yy - xx);
   const double ge2 = L.inv1me2 * (L.e2 * r2q - 2.0 * xy);
   g[2] = float(L.j11 * ge1 + L.j12 * ge2);                                     // eps1
   g[3] = float(L.j12 * ge1 + L.j22 * ge2);                                     // eps2
   const double dx = a[L_DX], dy = a[L_DY];
-  g[4] = float(offsets ? -(L.as * dx + L.bs * dy) : -dx);                      // x
-  g[5] = float(offsets ? -(L.bs * dx + L.cs * dy) : -dy);                      // y
+  g[4] = float(offsets ? -(L.qa * dx + L.qbh * dy) : -dx);                     // x
+  g[5] = float(offsets ? -(L.qbh * dx + L.qc * dy) : -dy);                     // y
   g[6] = float(a[L_E]);                                                        // I0
 }
 

@@ -744,15 +744,15 @@ __device__ __forceinline__ void adj_pixels(const SysDesc& s, const PConst& c,
       const float zi = float(y - c.yc), ly = float(y - c.lys);
       // alpha = x - alpha_ext - x_s - (beta - x_s): its part of this row
       const double cx = -c.g2 * y - c.sxs, cy = c.opg1 * y - c.sys;
-      const float lpx = c.lens.bs * ly, lpy = c.lens.cs * ly;
+      const float lpx = c.lens.qbh * ly, lpy = c.lens.qc * ly;
       double x = xj;
       for (int b = 0; b < k; ++b, x += dxs, bp += HW * sizeof(float2)) {
         const float* p = reinterpret_cast<const float*>(bp + off);
         const float sdx = __builtin_nontemporal_load(p);
         const float sdy = __builtin_nontemporal_load(p + 1);
         // g: sb d(source light)/d(beta)
-        const float px = fmaf(c.src.as, sdx, c.src.bs * sdy);
-        const float py = fmaf(c.src.cs, sdy, c.src.bs * sdx);
+        const float px = fmaf(c.src.qa, sdx, c.src.qbh * sdy);
+        const float py = fmaf(c.src.qc, sdy, c.src.qbh * sdx);
         const float sv = sersic_adj(c.src, sdx, sdy, px, py, sb, acc + A_SRC);
         Cx g;
         if (NMAX >= 0) {
@@ -765,8 +765,8 @@ __device__ __forceinline__ void adj_pixels(const SysDesc& s, const PConst& c,
         acc[A_SRC + L_DY] += g.i;
         if (LL) {
           const float lx = float(x - c.lxs);
-          const float lv = sersic_adj(c.lens, lx, ly, fmaf(c.lens.as, lx, lpx),
-                                      fmaf(c.lens.bs, lx, lpy), sb, acc + A_LENS);
+          const float lv = sersic_adj(c.lens, lx, ly, fmaf(c.lens.qa, lx, lpx),
+                                      fmaf(c.lens.qbh, lx, lpy), sb, acc + A_LENS);
           acc[A_LENS + L_DX] = fmaf(lv, lx, acc[A_LENS + L_DX]);
           acc[A_LENS + L_DY] = fmaf(lv, ly, acc[A_LENS + L_DY]);
         }

@@ -51,8 +51,7 @@ enum AccSlot {
   A_SHP_C = 32,   // kMaxShp slots
 };
 // Sums of one light profile, with E = I / I0, rho = (R / R_eff)^(1/n) and s the weighted
-// (R_eff^2 / R^2) d I / d ln R^2 times 2: E, E rho, E rho log2(rho) (all weighted), s dx^2,
-// s dx dy, s dy^2; L_DX, L_DY: the source's gradient in the offset, the lens light's s dx, s dy.
+// 2 dI/dR^2: E, E rho, E rho log2(rho) (all weighted), s dx^2, s dx dy, s dy^2; L_DX, L_DY: the source's gradient in the offset, the lens light's s dx, s dy.
 enum LightSlot { L_E = 0, L_RHO = 1, L_RHOLN = 2, L_XX = 3, L_XY = 4, L_YY = 5, L_DX = 6, L_DY = 7 };
 static_assert(A_SHP_C + kMaxShp <= kNAcc, "accumulator slots");
 
@@ -68,9 +67,6 @@ struct LightC {
   float n, re;         // Sersic index, R_eff
   float e1, e2;        // clamped eccentricities
   float inv1me2;       // 1 / (1 - |eps|^2)
-  // the adjoint's form of the profile: R^2 / R_eff^2 = as dx^2 + 2 bs dx dy + cs dy^2
-  float as, bs, cs;
-  float fls;           // the R^2 floor over R_eff^2
   float kqi;           // kq I0
   float j11, j12, j22; // d eps_clamped / d eps (symmetric)
 };
