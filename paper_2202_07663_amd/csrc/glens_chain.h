@@ -377,7 +377,7 @@ GL_HD void shapelet_adj(const PConst& c, float sdx, float sdy, const float* shp,
 }
 
 // ------------------------------------------------------------------------------------------
-// Accumulators -> d logL / d theta in the parameter order of gl.h. Returns d.
+// Accumulators -> d logL / d theta in the parameter order of gl.h.
 // ------------------------------------------------------------------------------------------
 GL_HD void light_grad(const LightC& L, const double* a, float* g) {
   g[0] = float(a[L_RHO] * L.bn / (double(L.n) * L.re));                 // R_eff
@@ -390,31 +390,11 @@ GL_HD void light_grad(const LightC& L, const double* a, float* g) {
   g[6] = float(a[L_E]);                                                  // I0
 }
 
-GL_HD int map_gradient(const PConst& c, const double* a, int mass, int shear, int lens_light,
-                       int nmax, float* gr) {
-  int j = 0;
-  gr[j++] = float(-double(c.t) / c.theta_e * a[A_M_ALPHA]);
-  if (mass == 1) gr[j++] = float(-a[A_M_T]);
-  gr[j++] = float(-(c.mj11 * a[A_M_E1] + c.mj12 * a[A_M_E2]));
-  gr[j++] = float(-(c.mj12 * a[A_M_E1] + c.mj22 * a[A_M_E2]));
-  gr[j++] = float(a[A_M_X]);
-  gr[j++] = float(a[A_M_Y]);
-  if (shear) {
-    gr[j++] = float(-a[A_M_G1]);
-    gr[j++] = float(-a[A_M_G2]);
-  }
-  if (lens_light) {
-    chain::light_grad(c.lens, a + A_LENS, gr + j);
-    j += 7;
-  }
-  chain::light_grad(c.src, a + A_SRC, gr + j);
-  j += 7;
-  if (nmax >= 0) gr[j++] = float(a[A_SHP_BETA]);
-  return j;
+GL_HD MassSums mass_sums(const double* a) {
+  return {a[A_M_ALPHA], a[A_M_T], a[A_M_E1], a[A_M_E2], a[A_M_X], a[A_M_Y], a[A_M_G1], a[A_M_G2]};
 }
 
-// Gradient component of shapelet coefficient q (0 <= q < M), whose slot in the gradient
-// follows those of map_gradient.
+// Gradient component of shapelet coefficient q (0 <= q < M).
 GL_HD float shapelet_coef_grad(const PConst& c, const double* a, int q) {
   int n1, n2;
   shapelet_orders(q, n1, n2);

@@ -107,7 +107,7 @@ GL_HD int mass_param_count(int mass, int shear) { return 5 + (mass == 1) + 2 * s
 
 // Mass constants of one parameter vector (layout of gl.h): everything but the series
 // coefficients, whose term counts it sets.
-GL_HD void decode_mass(const float* th, int mass, int shear, PConst& c) {
+GL_HD void decode_mass(const float* th, int mass, int shear, MassC& c) {
   int p = 0;
   const double theta_e = th[p++];
   const double t = (mass == 1) ? double(th[p++]) - 1.0 : 1.0;
@@ -192,10 +192,10 @@ GL_HD void series_step(int n, double t, double& ratio, double& dlog) {
 
 // Stores term n of the value series (c_n), of the derivative series n c_n (at n - 1) and
 // of dc_n / dt = c_n sum_k dlog_k, given the running product and sum.
-GL_HD void series_store(PConst& c, int n, double cn, double dsum) {
-  c.c[n] = n < c.nterms ? cn : 0.0;
-  c.dc[n] = n < c.nterms_d ? float(cn * dsum) : 0.f;
-  if (n > 0) c.nc[n - 1] = n < c.nterms_d ? float(n * cn) : 0.f;
+GL_HD void series_store(const MassC& m, PConst& c, int n, double cn, double dsum) {
+  c.c[n] = n < m.nterms ? cn : 0.0;
+  c.dc[n] = n < m.nterms_d ? float(cn * dsum) : 0.f;
+  if (n > 0) c.nc[n - 1] = n < m.nterms_d ? float(n * cn) : 0.f;
   if (n == kMaxTerms - 1) c.nc[kMaxTerms - 1] = 0.f;
 }
 
@@ -283,7 +283,7 @@ GL_HD double subpix_coord(double x0, int n, double dxs) { return fma(double(n), 
 //     phi = atan2(eps2, eps1) / 2): alpha_l = b / q' (atan(q' x_l / R_f), atanh(q' y_l / R_f)),
 //     b = theta_E sqrt(q), q' = sqrt(1 - q^2); at |eps| = 0 the SIS limit b z / R_f.
 // |eps| has no derivative at eps = 0: there the eps-derivatives of |eps| are taken as 0.
-GL_HD void floored_deflection(const PConst& c, int mass, double x, double y, D5& ar, D5& ai) {
+GL_HD void floored_deflection(const MassC& c, int mass, double x, double y, D5& ar, D5& ai) {
   const double rf = 1e-6;
   const D5 e1 = d5(c.e1, 1), e2 = d5(c.e2, 2);
   const D5 zr = d5(x) - d5(c.xc, 3), zi = d5(y) - d5(c.yc, 4);
@@ -330,24 +330,24 @@ GL_HD void floored_deflection(const PConst& c, int mass, double x, double y, D5&
 
 // Finds the floored sub-pixel of one particle (fills c.fl_*; after decode_mass). Only the
 // sub-pixel nearest the lens centre can have R below the floor. xs: the source centre.
-GL_HD void decode_floor(const SysDesc& s, const float* xs, PConst& c) {
+GL_HD void decode_floor(const SysDesc& s, const float* xs, const MassC& m, PConst& c) {
   c.fl_i = c.fl_j = c.fl_pix = c.fl_sub = -1;
   c.fl_a[0] = c.fl_a[1] = 0.0;
-  const double fj = rint((c.xc - s.x0) / s.dxs), fi = rint((c.yc - s.y0) / s.dxs);
+  const double fj = rint((m.xc - s.x0) / s.dxs), fi = rint((m.yc - s.y0) / s.dxs);
   if (!(fj >= 0.0 && fj < double(s.W * s.k) && fi >= 0.0 && fi < double(s.H * s.k))) return;
   const int jj = int(fj), ii = int(fi);
   const double x = subpix_coord(s.x0, jj, s.dxs), y = subpix_coord(s.y0, ii, s.dxs);
-  const double zr = x - c.xc, zi = y - c.yc;
-  const double wr = zr - c.e1 * zr - c.e2 * zi, wi = zi - c.e2 * zr + c.e1 * zi;
-  if (!(wr * wr + wi * wi < c.w2floor)) return;
+  const double zr = x - m.xc, zi = y - m.yc;
+  const double wr = zr - m.e1 * zr - m.e2 * zi, wi = zi - m.e2 * zr + m.e1 * zi;
+  if (!(wr * wr + wi * wi < m.w2floor)) return;
   D5 ar, ai;
-  floored_deflection(c, s.mass, x, y, ar, ai);
+  floored_deflection(m, s.mass, x, y, ar, ai);
   c.fl_i = ii;
   c.fl_j = jj;
   c.fl_pix = (ii / s.k) * s.W + jj / s.k;
   c.fl_sub = (ii % s.k) * s.k + jj % s.k;
-  c.fl_s[0] = float(x - ar.v - (c.g1 * x + c.g2 * y) - double(xs[0]));
-  c.fl_s[1] = float(y - ai.v - (c.g2 * x - c.g1 * y) - double(xs[1]));
+  c.fl_s[0] = float(x - ar.v - (m.g1 * x + m.g2 * y) - double(xs[0]));
+  c.fl_s[1] = float(y - ai.v - (m.g2 * x - m.g1 * y) - double(xs[1]));
   c.fl_a[0] = ar.v;
   c.fl_a[1] = ai.v;
   for (int k = 0; k < 5; ++k) {
@@ -374,17 +374,15 @@ GL_HD void decode_lights_lane(const float* th, int mass, int shear, int lens_lig
   const int pl = mass_param_count(mass, shear);        // lens light
   const int ps = pl + (lens_light ? 7 : 0);            // source Sersic
   const int pb = ps + 7;                               // shapelet scale, then coefficients
-  if (lane == 1) {
+  // the two profiles side by side: one pass over the decode's code for both lanes
+  if (lane == 2 || (lane == 1 && lens_light)) {
+    const float* p = th + (lane == 1 ? pl : ps);
+    decode_light(p, lane == 1 ? c.lens : c.src);
+    double* xs = lane == 1 ? &c.lxs : &c.sxs;
+    xs[0] = p[4];
+    xs[1] = p[5];
+  } else if (lane == 1) {
     c.lxs = c.lys = 0.0;
-    if (lens_light) {
-      decode_light(th + pl, c.lens);
-      c.lxs = th[pl + 4];
-      c.lys = th[pl + 5];
-    }
-  } else if (lane == 2) {
-    decode_light(th + ps, c.src);
-    c.sxs = th[ps + 4];
-    c.sys = th[ps + 5];
   }
   if (nmax < 0) return;
   const int q = lane - 3, M = (nmax + 1) * (nmax + 2) / 2;
@@ -906,8 +904,8 @@ GL_HD MassSums mass_sums(const PConst& c, const double* a) {
   return m;
 }
 
-GL_HD int map_gradient(const PConst& c, const MassSums& m, const double* a, int mass, int shear,
-                       int lens_light, int nmax, float* gr) {
+// The mass's part of the gradient, in the order of gl.h.
+GL_HD void mass_grad(const MassC& c, const MassSums& m, int mass, int shear, float* gr) {
   int j = 0;
   gr[j++] = float(-double(c.t) / c.theta_e * m.alpha);
   if (mass == 1) gr[j++] = float(-m.t);
@@ -919,18 +917,9 @@ GL_HD int map_gradient(const PConst& c, const MassSums& m, const double* a, int 
     gr[j++] = float(-m.g1);
     gr[j++] = float(-m.g2);
   }
-  if (lens_light) {
-    light_grad(c.lens, a + A_LENS, true, gr + j);
-    j += 7;
-  }
-  light_grad(c.src, a + A_SRC, false, gr + j);
-  j += 7;
-  if (nmax >= 0) gr[j++] = float(-double(c.inv_beta) * a[A_SHP_BETA]);
-  return j;
 }
 
-// Gradient component of shapelet coefficient q (0 <= q < M), whose slot in the gradient
-// follows those of map_gradient.
+// Gradient component of shapelet coefficient q (0 <= q < M).
 GL_HD float shapelet_coef_grad(const PConst& c, const double* a, int q) {
   int n1, n2;
   shapelet_orders(q, n1, n2);

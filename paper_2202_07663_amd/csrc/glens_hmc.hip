@@ -85,11 +85,33 @@ __device__ __forceinline__ float step_size(const HmcArgs& a) {
   return a.eps_fixed > 0.f ? a.eps_fixed : *a.eps;
 }
 
-// Copies the d x d factor m to LDS (the per-chain products read every entry in dependent
-// chains, where LDS reads wait far less than L2 ones); the caller synchronises the block.
-__device__ __forceinline__ void stage_factor(const float* m, int d, float* s_m) {
-  for (int q = threadIdx.x; q < d * d; q += kHmcThreads) s_m[q] = m[q];
-}
+// The d x d factor m on its way to LDS (the per-chain products read every entry in dependent
+// chains, where LDS reads wait far less than L2 ones): all its loads go out together, before
+// work that does not need it, and are stored after; the caller synchronises the block. One at
+// a time they took longer than everything else of a leapfrog step's per-chain work.
+struct Factor {
+  static constexpr int kLoads = (kMaxParams * kMaxParams / 4 + kHmcThreads - 1) / kHmcThreads;
+  float4 v[kLoads];
+  float tail;
+  __device__ __forceinline__ void load(const float* m, int d) {
+    const int n4 = d * d / 4, rem = d * d - 4 * n4;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int q = threadIdx.x + i * kHmcThreads;
+      if (q < n4) v[i] = reinterpret_cast<const float4*>(m)[q];
+    }
+    if (threadIdx.x < rem) tail = m[4 * n4 + threadIdx.x];
+  }
+  __device__ __forceinline__ void store(float* s_m, int d) const {
+    const int n4 = d * d / 4, rem = d * d - 4 * n4;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int q = threadIdx.x + i * kHmcThreads;
+      if (q < n4) reinterpret_cast<float4*>(s_m)[q] = v[i];
+    }
+    if (threadIdx.x < rem) s_m[4 * n4 + threadIdx.x] = tail;
+  }
+};
 
 // v = chol^T x for one chain (chol, x in LDS, v to LDS); lanes own output coordinates.
 __device__ __forceinline__ void chol_t_times(const float* chol, int d, const float* x, float* v) {
@@ -101,52 +123,88 @@ __device__ __forceinline__ void chol_t_times(const float* chol, int d, const flo
   }
 }
 
-// p += scale eps g (scale 0: no kick); then, if drift, z += eps chol (chol^T p). p is
-// mirrored in s_p. One block per chain; the caller has synchronised the block.
+// Coordinates of one chain held by a lane: j = threadIdx.x and j + 64 (d <= 68).
+constexpr int kOwn = (kMaxParams + kHmcThreads - 1) / kHmcThreads;
+
+// p += scale eps g (scale 0: no kick); then, if drift, z += eps chol (chol^T p), with p0 and z0
+// this lane's coordinates of p and z before and chol in LDS. p is mirrored in s_p, the new z
+// (FP32) in s_z. One block per chain; the caller has synchronised the block.
 __device__ __forceinline__ void kick_drift(const HmcArgs& a, const float* s_g, float scale,
-                                           int drift, float* s_p, float* s_v) {
-  const int c = blockIdx.x;
-  const float eps = step_size(a);
-  const size_t row = size_t(c) * a.d;
+                                           int drift, float eps, const float* p0,
+                                           const double* z0, const float* s_chol, float* s_p,
+                                           float* s_v, float* s_z) {
+  const size_t row = size_t(blockIdx.x) * a.d;
   if (scale != 0.f) {
-    for (int j = threadIdx.x; j < a.d; j += kHmcThreads) {
-      const float pn = a.p[row + j] + scale * eps * s_g[j];
+#pragma unroll
+    for (int u = 0; u < kOwn; ++u) {
+      const int j = threadIdx.x + u * kHmcThreads;
+      if (j >= a.d) break;
+      const float pn = p0[u] + scale * eps * s_g[j];
       a.p[row + j] = pn;
       s_p[j] = pn;
     }
   }
   if (!drift) return;
-  __shared__ float s_chol[kMaxParams * kMaxParams];
-  stage_factor(a.chol, a.d, s_chol);
   __syncthreads();
   chol_t_times(s_chol, a.d, s_p, s_v);
   __syncthreads();
-  for (int j = threadIdx.x; j < a.d; j += kHmcThreads) {
+#pragma unroll
+  for (int u = 0; u < kOwn; ++u) {
+    const int j = threadIdx.x + u * kHmcThreads;
+    if (j >= a.d) break;
     float s = 0.f;
 #pragma unroll 4
     for (int i = 0; i <= j; ++i) s += s_chol[j * a.d + i] * s_v[i];
-    const double zn = a.z[row + j] + double(eps) * s;
+    const double zn = z0[u] + double(eps) * s;
     a.z[row + j] = zn;
-    a.z32[row + j] = float(zn);
+    a.z32[row + j] = s_z[j] = float(zn);
   }
 }
 
-// log p~(z | I) and its gradient from the pipeline outputs (terms summed in parameter
-// order by lane 0), then the kick and drift of the leapfrog step.
-__device__ __forceinline__ void grad_move(const HmcArgs& a, float scale, int drift) {
+// One block per chain: the pipeline's finalize (log L and its gradient), log p~(z | I) and its
+// gradient (terms summed in parameter order by lane 0), the kick and, with a drift, the decode of
+// the new position for the next step's pipeline (prologue), which then starts at the sub-pixel
+// forward pass. Two launches fewer per leapfrog step than finalize, kick/drift and prologue
+// apart, with the same arithmetic. Bound by latency: what the chain's state and the factor hold
+// is loaded at the start, and the gradient and the new position pass through LDS: 21.4 -> 16.7 us
+// (60 x 60 system, d = 51, 64 chains).
+__global__ void __launch_bounds__(kHmcThreads) hmc_finalize_move_kernel(SysDesc s, HmcArgs a,
+                                                                        float scale, int drift) {
   __shared__ double s_t[kMaxParams];
-  __shared__ float s_g[kMaxParams], s_p[kMaxParams], s_v[kMaxParams];
+  __shared__ float s_g[kMaxParams], s_p[kMaxParams], s_v[kMaxParams], s_z[kMaxParams];
+  __shared__ __align__(16) float s_chol[kMaxParams * kMaxParams];
   __shared__ int s_bad;
   const int c = blockIdx.x;
   const size_t row = size_t(c) * a.d;
-  for (int j = threadIdx.x; j < a.d; j += kHmcThreads) {
-    float dlp, dth;
-    s_t[j] = log_prior_z(a.prior[j], a.z32[row + j], a.theta[row + j], dlp, dth);
-    s_g[j] = a.grad[row + j] * dth + dlp;
+  Factor f;
+  if (drift) f.load(a.chol, a.d);
+  Prior pr[kOwn];
+  float z32[kOwn], th[kOwn], p0[kOwn];
+  double z0[kOwn];
+#pragma unroll
+  for (int u = 0; u < kOwn; ++u) {
+    const int j = threadIdx.x + u * kHmcThreads;
+    if (j >= a.d) break;
+    pr[u] = a.prior[j];
+    z32[u] = a.z32[row + j];
+    th[u] = a.theta[row + j];
+    p0[u] = a.p[row + j];
+    z0[u] = a.z[row + j];
   }
+  const float eps = step_size(a);
+  const FinalGrad fg = finalize_particle<true>(s, c);
+#pragma unroll
+  for (int u = 0; u < kOwn; ++u) {
+    const int j = threadIdx.x + u * kHmcThreads;
+    if (j >= a.d) break;
+    float dlp, dth;
+    s_t[j] = log_prior_z(pr[u], z32[u], th[u], dlp, dth);
+    s_g[j] = (fg.ok ? fg.g[j] : 0.f) * dth + dlp;
+  }
+  if (drift) f.store(s_chol, a.d);
   __syncthreads();
   if (threadIdx.x == 0) {
-    double lp = a.logl[c];
+    double lp = fg.ok ? fg.logl : -INFINITY;
     for (int j = 0; j < a.d; ++j) lp += s_t[j];
     const int bad = !isfinite(lp);
     if (bad) {
@@ -158,36 +216,39 @@ __device__ __forceinline__ void grad_move(const HmcArgs& a, float scale, int dri
   }
   __syncthreads();
   const int bad = s_bad;
-  for (int j = threadIdx.x; j < a.d; j += kHmcThreads) {
+#pragma unroll
+  for (int u = 0; u < kOwn; ++u) {
+    const int j = threadIdx.x + u * kHmcThreads;
+    if (j >= a.d) break;
     if (bad) s_g[j] = 0.f;
     a.g[row + j] = s_g[j];
   }
-  kick_drift(a, s_g, scale, drift, s_p, s_v);
-}
-
-// One block per chain: the pipeline's finalize (log L and its gradient), log p~ and its
-// gradient, the kick and, with a drift, the decode of the new position for the next step's
-// pipeline (prologue), which then starts at the sub-pixel forward pass. Two launches fewer
-// per leapfrog step than finalize, kick/drift and prologue apart, with the same arithmetic.
-__global__ void __launch_bounds__(kHmcThreads) hmc_finalize_move_kernel(SysDesc s, HmcArgs a,
-                                                                        float scale, int drift) {
-  finalize_particle<true>(s, blockIdx.x);
-  __syncthreads();  // this chain's log L and gradient are written
-  grad_move(a, scale, drift);
+  kick_drift(a, s_g, scale, drift, eps, p0, z0, s_chol, s_p, s_v, s_z);
   if (!drift) return;
-  __syncthreads();  // this chain's new position is written
-  prologue_particle(s, blockIdx.x);
+  __syncthreads();
+  prologue_particle(s, c, s_z);
 }
 
 // New momentum p = chol^-T n, saved trajectory start and kinetic energy |n|^2 / 2, then the
 // first half kick and drift.
 __global__ void __launch_bounds__(kHmcThreads) hmc_begin_kernel(HmcArgs a) {
   __shared__ float s_n[kMaxParams], s_g[kMaxParams], s_p[kMaxParams], s_v[kMaxParams];
-  __shared__ float s_cit[kMaxParams * kMaxParams];
+  __shared__ float s_z[kMaxParams];
+  __shared__ __align__(16) float s_cit[kMaxParams * kMaxParams];
+  __shared__ __align__(16) float s_chol[kMaxParams * kMaxParams];
   const int c = blockIdx.x;
-  const int traj = *a.traj;
   const size_t row = size_t(c) * a.d;
-  stage_factor(a.chol_it, a.d, s_cit);
+  Factor fi, f;
+  fi.load(a.chol_it, a.d);
+  f.load(a.chol, a.d);
+  double z0[kOwn];
+#pragma unroll
+  for (int u = 0; u < kOwn; ++u) {
+    const int j = threadIdx.x + u * kHmcThreads;
+    if (j < a.d) z0[u] = a.z[row + j];
+  }
+  const int traj = *a.traj;
+  const float eps = step_size(a);
   for (int j = threadIdx.x; j < a.d; j += kHmcThreads) {
     uint32_t w[4] = {uint32_t(c), uint32_t(j), uint32_t(traj), 0x6d6f6d65u};
     philox4x32_10(w, a.seed_lo, a.seed_hi);
@@ -196,11 +257,17 @@ __global__ void __launch_bounds__(kHmcThreads) hmc_begin_kernel(HmcArgs a) {
     a.zs[row + j] = a.z[row + j];
     s_g[j] = a.gs[row + j] = a.g[row + j];
   }
+  fi.store(s_cit, a.d);
+  f.store(s_chol, a.d);
   __syncthreads();
-  for (int i = threadIdx.x; i < a.d; i += kHmcThreads) {
+  float p0[kOwn];
+#pragma unroll
+  for (int u = 0; u < kOwn; ++u) {
+    const int i = threadIdx.x + u * kHmcThreads;
+    if (i >= a.d) break;
     float s = 0.f;
     for (int j = i; j < a.d; ++j) s += s_cit[i * a.d + j] * s_n[j];
-    a.p[row + i] = s;
+    p0[u] = s;
   }
   if (threadIdx.x == 0) {
     double k = 0.0;
@@ -210,7 +277,7 @@ __global__ void __launch_bounds__(kHmcThreads) hmc_begin_kernel(HmcArgs a) {
     a.bad[c] = 0;
   }
   __syncthreads();
-  kick_drift(a, s_g, 0.5f, 1, s_p, s_v);
+  kick_drift(a, s_g, 0.5f, 1, eps, p0, z0, s_chol, s_p, s_v, s_z);
 }
 
 // Chain means of the trajectory starts and of the proposals (one lane per parameter, chains
@@ -235,9 +302,11 @@ __global__ void __launch_bounds__(kHmcThreads) hmc_finish_kernel(HmcArgs a) {
   const int c = blockIdx.x;
   const int traj = *a.traj;
   const size_t row = size_t(c) * a.d;
-  __shared__ float s_chol[kMaxParams * kMaxParams];
-  stage_factor(a.chol, a.d, s_chol);
+  __shared__ __align__(16) float s_chol[kMaxParams * kMaxParams];
+  Factor f;
+  f.load(a.chol, a.d);
   for (int j = threadIdx.x; j < a.d; j += kHmcThreads) s_p[j] = a.p[row + j];
+  f.store(s_chol, a.d);
   __syncthreads();
   chol_t_times(s_chol, a.d, s_p, s_v);
   __syncthreads();

@@ -14,14 +14,19 @@
 namespace glens {
 
 // ------------------------------------------------------------------------------------------
-// prologue: one 64-lane block per particle. Lane 0 decodes the mass, lanes 1 and 2 the
-// light profiles and lanes 3 .. one shapelet coefficient each, while lane n (1 <= n <
-// kMaxTerms) computes the series ratio c_n / c_(n-1) and the increment of d log c_n / dt;
-// inclusive scans across the wave (product and sum) then give every lane its c_n and
-// d log c_n / dt; lane 63 looks for the floored sub-pixel while the others fill the power
-// tables; last, the lanes store the series coefficients.
+// prologue: one 64-lane block per particle. Every lane decodes the mass (the same instructions
+// that one lane would take, and its constants are then in registers: passed through the
+// particle's constants in memory they cost two L2 round trips), lane 0 stores it; lanes 1 and 2
+// decode the light profiles and lanes 3 .. one shapelet coefficient each, while lane n
+// (1 <= n < kMaxTerms) computes the series ratio c_n / c_(n-1) and the increment of
+// d log c_n / dt; inclusive scans across the wave (product and sum) then give every lane its
+// c_n and d log c_n / dt; lane 63 looks for the floored sub-pixel while the others fill the
+// power tables; last, the lanes store the series coefficients. Bound by latency: 9.0 -> 7.8 us (60 x 60 EPL, 64
+// vectors), 18.6 -> 16.6 us (4096).
+// z_lds (or null): the particle's unconstrained parameters, in LDS, instead of s.z.
 // ------------------------------------------------------------------------------------------
-__device__ __forceinline__ void prologue_particle(const SysDesc& s, int p) {
+__device__ __forceinline__ void prologue_particle(const SysDesc& s, int p,
+                                                  const float* z_lds = nullptr) {
   static_assert(kMaxTerms <= 63, "one lane per series term, lane 63 free");
   static_assert(3 + kMaxShp <= 64, "one lane per shapelet coefficient");
   __shared__ float th[kMaxParams];
@@ -29,7 +34,7 @@ __device__ __forceinline__ void prologue_particle(const SysDesc& s, int p) {
   for (int j = lane; j < d; j += blockDim.x) {
     const size_t i = (size_t)p * d + j;
     if (s.z) {
-      th[j] = bijector_fwd(s.prior[j], s.z[i]);
+      th[j] = bijector_fwd(s.prior[j], z_lds ? z_lds[j] : s.z[i]);
       s.theta_out[i] = th[j];
     } else {
       th[j] = s.theta[i];
@@ -37,13 +42,12 @@ __device__ __forceinline__ void prologue_particle(const SysDesc& s, int p) {
   }
   __syncthreads();
   PConst& c = s.pc[p];
-  // the decode, spread over lanes: the mass on lane 0, the lights and shapelet coefficients
-  // on lanes 1 ..; the series ratios on lanes 1 .. kMaxTerms - 1
-  if (lane == 0) decode_mass(th, s.mass, s.shear, c);
+  MassC m;
+  decode_mass(th, s.mass, s.shear, m);
+  if (lane == 0) static_cast<MassC&>(c) = m;
   decode_lights_lane(th, s.mass, s.shear, s.lens_light, s.nmax, c, lane);
-  const double t = (s.mass == 1) ? double(th[1]) - 1.0 : 1.0;
   double cn = 1.0, dsum = 0.0;  // lane n: c_n / c_(n-1) and its d log / dt increment (n >= 1)
-  if (lane > 0 && lane < kMaxTerms) series_step(lane, t, cn, dsum);
+  if (lane > 0 && lane < kMaxTerms) series_step(lane, m.t, cn, dsum);
   for (int o = 1; o < 64; o <<= 1) {  // inclusive scans: c_n and d log c_n / dt on lane n
     const double pc = __shfl_up(cn, o, 64), pd = __shfl_up(dsum, o, 64);
     if (lane >= o) {
@@ -51,101 +55,107 @@ __device__ __forceinline__ void prologue_particle(const SysDesc& s, int p) {
       dsum += pd;
     }
   }
-  __syncthreads();
-  // lane 63 looks for the floored sub-pixel; the others fill the power tables (both from
-  // decode_mass's constants, written before the barrier)
   if (lane == 63)
-    decode_floor(s, th + mass_param_count(s.mass, s.shear) + (s.lens_light ? 7 : 0) + 4, c);
+    decode_floor(s, th + mass_param_count(s.mass, s.shear) + (s.lens_light ? 7 : 0) + 4, m, c);
   else
-    pow_tables_lane(c.t, log2(c.bmass), lane, 63, c.pw);
-  if (lane < kMaxTerms) series_store(c, lane, cn, dsum);
+    pow_tables_lane(m.t, log2(m.bmass), lane, 63, c.pw);
+  if (lane < kMaxTerms) series_store(m, c, lane, cn, dsum);
 }
 
 // ------------------------------------------------------------------------------------------
 // finalize: one 64-lane block (a single wave) per particle; lanes sum the tiles' partial
-// accumulators (in tile order), lane 0 maps them to the parameter gradient (the shapelet
-// coefficients' components one per lane); a vector whose log L or gradient is not finite
-// gets log L = -inf and a zero gradient
-// ------------------------------------------------------------------------------------------
+// accumulators (in tile order); lane 0 maps the mass's sums to the parameter gradient, lanes 1
+// and 2 the light profiles' (one pass over the code for both), the other lanes one shapelet
+// coefficient each; a vector whose log L or gradient is not finite gets log L = -inf and a zero
+// gradient. Returns the gradient's components (in LDS, before that check), and whether it
+// passed, to every lane. Bound by latency: 5.9 -> 4.3 us (60 x 60, 64 vectors of 15 tiles, whose
+// partial sums were loaded one after the other past the eighth).
 // CHAIN: the accumulators are those of the sampler's adjoint (glens_chain.h).
+// ------------------------------------------------------------------------------------------
+struct FinalGrad {
+  const float* g;
+  bool ok;
+  double logl;
+};
 template <bool CHAIN>
-__device__ __forceinline__ void finalize_particle(const SysDesc& s, int p) {
+__device__ __forceinline__ FinalGrad finalize_particle(const SysDesc& s, int p) {
   __shared__ double a[kNAcc];
+  __shared__ float gr[kMaxParams];
+  const PConst& c = s.pc[p];
+  const int lane = threadIdx.x, nmax = s.nmax;
   const int beta0 = CHAIN ? int(chain::A_SHP_BETA) : int(A_SHP_BETA);
-  const int ns = beta0 + (s.nmax < 0 ? 0 : 1 + (s.nmax + 1) * (s.nmax + 2) / 2);
+  const int lens0 = CHAIN ? int(chain::A_LENS) : int(A_LENS);
+  const int src0 = CHAIN ? int(chain::A_SRC) : int(A_SRC);
+  const int ns = beta0 + (nmax < 0 ? 0 : 1 + (nmax + 1) * (nmax + 2) / 2);
+  const double logl = s.logl[p];
+  const LightC L = lane == 1 ? c.lens : c.src;  // on its way while the sums are taken
   const double* acc = s.acc + (size_t)p * s.tiles * kNAcc;
-  for (int q = threadIdx.x; q < ns; q += blockDim.x) {
+  for (int q = lane; q < ns; q += blockDim.x) {
     double v = 0.0;
-#pragma unroll 8
-    for (int t = 0; t < s.tiles; ++t) v += acc[t * kNAcc + q];
+    for (int t0 = 0; t0 < s.tiles; t0 += 16) {  // sixteen loads in flight, added in tile order
+      double b[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) b[u] = t0 + u < s.tiles ? acc[(t0 + u) * kNAcc + q] : 0.0;
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v += b[u];
+    }
     a[q] = v;
   }
   __syncthreads();
-  const PConst& c = s.pc[p];
-  // the floored sub-pixel (if any): g = sbar d(source light)/d(beta) there (FP64), contracted
-  // with the prologue's exact deflection derivatives; shear terms as the main loop forms them
-  double gx = 0.0, gy = 0.0;
-  const bool floored = threadIdx.x == 0 && c.fl_i >= 0;
-  if (floored) {
-    const int k = s.k, HW = s.H * s.W;
-    const int pi = c.fl_i / k, pj = c.fl_j / k, sub = (c.fl_i - pi * k) * k + (c.fl_j - pj * k);
-    const int pix = pi * s.W + pj;
-    const double sb = s.sbar[(size_t)p * HW + pix];
-    const float2 bs = s.beta[((size_t)p * k * k + sub) * HW + pix];
-    source_light_grad(c, s.nmax, bs.x, bs.y, gx, gy);
-    gx *= sb;
-    gy *= sb;
+  // the layout of gl.h: mass, lens light, source, shapelet scale and coefficients
+  const int jl = mass_param_count(s.mass, s.shear), js = jl + (s.lens_light ? 7 : 0), jb = js + 7;
+  const int M = nmax < 0 ? 0 : (nmax + 1) * (nmax + 2) / 2, d = jb + (nmax < 0 ? 0 : 1 + M);
+  if (lane == 2 || (lane == 1 && s.lens_light)) {
+    const double* al = a + (lane == 1 ? lens0 : src0);
+    float* g = gr + (lane == 1 ? jl : js);
+    if (CHAIN)
+      chain::light_grad(L, al, g);
+    else
+      light_grad(L, al, lane == 1, g);
   }
-  MassSums ms;  // lane 0
-  if (!CHAIN && threadIdx.x == 0) {
-    ms = mass_sums(c, a);
-    if (floored) {
+  for (int q = lane - 3; q >= 0 && q < M; q += 61)
+    gr[jb + 1 + q] = CHAIN ? chain::shapelet_coef_grad(c, a, q) : shapelet_coef_grad(c, a, q);
+  if (lane == 0) {
+    if (nmax >= 0)
+      gr[jb] = CHAIN ? float(a[chain::A_SHP_BETA]) : float(-double(c.inv_beta) * a[A_SHP_BETA]);
+    MassSums ms = CHAIN ? chain::mass_sums(a) : mass_sums(c, a);
+    if (c.fl_i >= 0) {
+      // the floored sub-pixel: g = sbar d(source light)/d(beta) there (FP64), contracted with
+      // the prologue's exact deflection derivatives; shear terms as the main loop forms them
+      const int k = s.k, HW = s.H * s.W;
+      const double sb = s.sbar[(size_t)p * HW + c.fl_pix];
+      const float2 bs = s.beta[((size_t)p * k * k + c.fl_sub) * HW + c.fl_pix];
+      double gx, gy;
+      source_light_grad(c, nmax, bs.x, bs.y, gx, gy);
+      gx *= sb;
+      gy *= sb;
       ms.alpha += gx * c.fl_a[0] + gy * c.fl_a[1];
       ms.t += gx * c.fl_d[0][0] + gy * c.fl_d[0][1];
       ms.e1 += gx * c.fl_d[1][0] + gy * c.fl_d[1][1];
       ms.e2 += gx * c.fl_d[2][0] + gy * c.fl_d[2][1];
       ms.x -= gx * c.fl_d[3][0] + gy * c.fl_d[3][1];  // d/dx = -d/dx_c
       ms.y -= gx * c.fl_d[4][0] + gy * c.fl_d[4][1];
-      // the sums of g in mass_sums hold this sub-pixel's, those of g z do not
-      const double zr = subpix_coord(s.x0, c.fl_j, s.dxs) - c.xc;
-      const double zi = subpix_coord(s.y0, c.fl_i, s.dxs) - c.yc;
-      ms.g1 += gx * zr - gy * zi;
-      ms.g2 += gx * zi + gy * zr;
+      double x = subpix_coord(s.x0, c.fl_j, s.dxs), y = subpix_coord(s.y0, c.fl_i, s.dxs);
+      if (CHAIN) {
+        x = float(x);
+        y = float(y);
+      } else {  // the sums of g in mass_sums hold this sub-pixel's, those of g z do not
+        x -= c.xc;
+        y -= c.yc;
+      }
+      ms.g1 += gx * x - gy * y;
+      ms.g2 += gx * y + gy * x;
     }
-  }
-  if (CHAIN && floored) {
-    a[chain::A_M_ALPHA] += gx * c.fl_a[0] + gy * c.fl_a[1];
-    a[chain::A_M_T] += gx * c.fl_d[0][0] + gy * c.fl_d[0][1];
-    a[chain::A_M_E1] += gx * c.fl_d[1][0] + gy * c.fl_d[1][1];
-    a[chain::A_M_E2] += gx * c.fl_d[2][0] + gy * c.fl_d[2][1];
-    a[chain::A_M_X] -= gx * c.fl_d[3][0] + gy * c.fl_d[3][1];
-    a[chain::A_M_Y] -= gx * c.fl_d[4][0] + gy * c.fl_d[4][1];
-    const double x = float(subpix_coord(s.x0, c.fl_j, s.dxs));
-    const double y = float(subpix_coord(s.y0, c.fl_i, s.dxs));
-    a[chain::A_M_G1] += gx * x - gy * y;
-    a[chain::A_M_G2] += gx * y + gy * x;
+    mass_grad(c, ms, s.mass, s.shear, gr);
   }
   __syncthreads();
-  // lane 0 maps the sums (to LDS, not to a lane-private array the compiler would spill);
-  // the lanes then check and store the components
-  __shared__ float gr[kMaxParams];
-  // the shapelet coefficients' components (if any) follow the others, one per lane
-  __shared__ int s_j0;
-  if (threadIdx.x == 0)
-    s_j0 = CHAIN ? chain::map_gradient(c, a, s.mass, s.shear, s.lens_light, s.nmax, gr)
-                 : map_gradient(c, ms, a, s.mass, s.shear, s.lens_light, s.nmax, gr);
-  __syncthreads();
-  const int M = s.nmax < 0 ? 0 : (s.nmax + 1) * (s.nmax + 2) / 2;
-  for (int q = threadIdx.x; q < M; q += blockDim.x) 
-    gr[s_j0 + q] = CHAIN ? chain::shapelet_coef_grad(c, a, q) : shapelet_coef_grad(c, a, q);
-  __syncthreads();
-  const int j = s_j0 + M;
   int bad = 0;
-  for (int q = threadIdx.x; q < j; q += blockDim.x) bad |= !isfinite(gr[q]);
-  const bool ok = isfinite(s.logl[p]) && !__any(bad);
+  for (int q = lane; q < d; q += blockDim.x) bad |= !isfinite(gr[q]);
+  const bool ok = isfinite(logl) && !__any(bad);
   float* out = s.grad + (size_t)p * s.d;
-  for (int q = threadIdx.x; q < j; q += blockDim.x) out[q] = ok ? gr[q] : 0.f;
-  if (threadIdx.x == 0 && !ok) s.logl[p] = -INFINITY;
+  for (int q = lane; q < d; q += blockDim.x) out[q] = ok ? gr[q] : 0.f;
+  if (lane == 0 && !ok) s.logl[p] = -INFINITY;
+  return {gr, ok, logl};
 }
 
 }  // namespace glens

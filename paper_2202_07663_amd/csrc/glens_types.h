@@ -71,12 +71,11 @@ struct LightC {
   float j11, j12, j22; // d eps_clamped / d eps (symmetric)
 };
 
-// Per-particle constants written by the prologue and read (uniformly) by every sub-pixel
-// lane of that particle.
-struct PConst {
+// Constants of the mass model of one particle.
+struct MassC {
   int nterms;          // EPL / SIE series terms
   int nterms_d;        // terms of the derivative series (adjoint), <= nterms
-  int sie_closed;      // SIE: 1 = closed form, 0 = series
+  int sie_closed;      // SIE: 1 = closed form, 0 = series (the sampler's ray trace)
   // FP64 part: positions and the deflection are evaluated in double precision, because the
   // ray-traced source offset beta - x_s must be accurate to far below the FP32 resolution
   // of arcsecond-scale coordinates near a cuspy source.
@@ -90,6 +89,25 @@ struct PConst {
   double w2floor;      // R^2 floor expressed on |w|^2: 1e-12 (1 + |eps|)^2
   double sr, si;       // SIE closed form: s = sqrt(conj(eps))
   double epsabs;
+  // FP32 part
+  float theta_e;       // Einstein radius
+  float hp, hm;        // 1 - t/2, -t/2
+  float omt;           // 1 - t
+  float w2floorf;      // R^2 floor on |w|^2 (FP32)
+  float tlnb2;         // t log2 B
+  float l2b2;          // 2 log2 B
+  float hb;            // B / 2
+  float e1f, e2f, eef; // clamped eccentricities, |eps|^2
+  float mj11, mj12, mj22;  // d eps_clamped / d eps (symmetric)
+  float tf, lnb;       // t, ln B, and below the constants of the chains' adjoint (glens_chain.h):
+  float xcf, ycf;      // lens centre
+  float iebr, iebi;    // 1 / conj(eps) for |eps| >= kSxClosedMin, else 0
+  float tfac;          // t / (2 (1 - |eps|^2))
+};
+
+// Per-particle constants written by the prologue and read (uniformly) by every sub-pixel
+// lane of that particle.
+struct PConst : MassC {
   double c[kMaxTerms]; // series coefficients c_n(t)
   // A = B^t |w|^-t of the ray trace, with |w|^2 = 2^e m, m in [1, 2):
   //   pw[e + kPowExp/2] = B^t 2^(-t e / 2) (e clamped to the table),
@@ -110,20 +128,6 @@ struct PConst {
   double fl_d[5][2];
   double sxs, sys;     // source centre
   double lxs, lys;     // lens-light centre
-  // FP32 part
-  float theta_e;       // Einstein radius
-  float hp, hm;        // 1 - t/2, -t/2
-  float omt;           // 1 - t
-  float w2floorf;      // R^2 floor on |w|^2 (FP32)
-  float tlnb2;         // t log2 B
-  float l2b2;          // 2 log2 B
-  float hb;            // B / 2
-  float e1f, e2f, eef; // clamped eccentricities, |eps|^2
-  float tf, lnb;       // t, ln B, and below the constants of the chains' adjoint (glens_chain.h):
-  float xcf, ycf;      // lens centre
-  float iebr, iebi;    // 1 / conj(eps) for |eps| >= kSxClosedMin, else 0
-  float tfac;          // t / (2 (1 - |eps|^2))
-  float mj11, mj12, mj22;
   LightC lens, src;
   float beta, inv_beta;
   float rt2_ib;        // sqrt(2) / beta

@@ -103,7 +103,8 @@ __device__ __forceinline__ double chol_entry(const double* v, int i, int j) {
 __device__ __forceinline__ void draw_sample(const double* mu, const double* v, int d, int s,
                                             int k, uint32_t tag, uint32_t seed_lo,
                                             uint32_t seed_hi, double* s_eps, double* eps_out,
-                                            float* z32_out, double* z64_out) {
+                                            float* z32_out, double* z64_out,
+                                            float* s_z = nullptr) {
   __shared__ double s_l[kMaxParams * (kMaxParams + 1) / 2];
   const int nc = d * (d + 1) / 2;
   for (int q = threadIdx.x; q < nc; q += kViThreads) s_l[q] = v[q];
@@ -125,7 +126,7 @@ __device__ __forceinline__ void draw_sample(const double* mu, const double* v, i
     double zi = mu[i];
     const double* li = s_l + i * (i + 1) / 2;
     for (int j = 0; j <= i; ++j) zi += li[j] * s_eps[j];
-    if (z32_out) z32_out[size_t(s) * d + i] = float(zi);
+    if (z32_out) z32_out[size_t(s) * d + i] = s_z[i] = float(zi);
     if (z64_out) z64_out[size_t(s) * d + i] = zi;
   }
 }
@@ -134,10 +135,11 @@ __device__ __forceinline__ void draw_sample(const double* mu, const double* v, i
 // (prologue): one launch instead of two.
 __global__ void __launch_bounds__(kViThreads) vi_draw_decode_kernel(SysDesc s, ViArgs a) {
   __shared__ double s_eps[kMaxParams];
+  __shared__ float s_z[kMaxParams];
   draw_sample(a.x, a.x + a.d, a.d, blockIdx.x, a.k, kViDrawTag, a.seed_lo, a.seed_hi, s_eps,
-              a.eps, a.z32, nullptr);
-  __syncthreads();  // this sample's z is written
-  prologue_particle(s, blockIdx.x);
+              a.eps, a.z32, nullptr, s_z);
+  __syncthreads();  // this sample's z is in LDS
+  prologue_particle(s, blockIdx.x, s_z);
 }
 
 // f = -log p~(z | I) and its gradient for one sample (terms summed in parameter order).
