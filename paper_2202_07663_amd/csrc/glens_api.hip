@@ -328,7 +328,7 @@ SysDesc make_sys(const SystemData& sd, const Workspace& ws, int P, int tiles) {
   s.seed = ws.seed;
   s.beta = ws.beta;
   s.lpart = ws.lpart;
-  conv_bands(P, c.H, c.W, &s.bands, &s.band_rows, &s.band_split);
+  conv_bands(P, c.H, c.W, c.K, &s.bands, &s.band_rows, &s.band_split, &s.band_threads);
   // matrix-core PSF pass for whole-image launches when the image's tiles and LDS fit; the
   // choice depends on this system alone, so its results do not depend on its launch partners
   const MfmaGeom q = mfma_geom(c.H, c.W, c.K);
@@ -342,22 +342,40 @@ SysDesc make_sys(const SystemData& sd, const Workspace& ws, int P, int tiles) {
   return s;
 }
 
-void conv_bands(int P, int H, int W, int* bands, int* band_rows, int* split) {
-  // aim at >= 512 workgroups in the PSF pass; bands of whole strips, at most kConvMaxBands
+void conv_bands(int P, int H, int W, int K, int* bands, int* band_rows, int* split,
+                int* threads) {
+  // one band from 512 particles on, and for an image of one strip
   const int nstrip = (H + kConvRows - 1) / kConvRows;
-  const int want = P >= 512 ? 1 : (512 + std::max(P, 1) - 1) / std::max(P, 1);
-  const int b = std::max(1, std::min({want, nstrip, kConvMaxBands}));
-  const int spb = (nstrip + b - 1) / b;  // strip rows per band
-  *band_rows = spb * kConvRows;
-  *bands = (H + *band_rows - 1) / *band_rows;
+  const bool whole = P >= 512 || nstrip == 1;
   // small batches: split each strip's PSF columns over 2 or 4 lanes until the pass has about
   // one work item per lane of the GPU (256 CUs x 256 lanes), so that the per-lane chains of
   // K^2 kConvRows FMAs shorten; a one-band system keeps 1 (its bits then equal the whole-image
   // kernel's)
   const size_t items = size_t(P) * nstrip * W;
   int g = 1;
-  while (*bands > 1 && g < 4 && items * g < size_t(256) * 256) g *= 2;
+  while (!whole && g < 4 && items * g < size_t(256) * 256) g *= 2;
   *split = g;
+  const auto waves = [&](int spb) { return (spb * W * g + 63) / 64; };
+  int best = nstrip;
+  if (!whole) {
+    // strips per band: the fewest cycles on the fullest CU, for the products (whole waves, spread
+    // over four SIMDs) and for loading each band with its halo (about 16 instructions per 64
+    // values); a sum does not depend on its band
+    double least = 0.0;
+    for (int spb = (nstrip + kConvMaxBands - 1) / kConvMaxBands; spb < nstrip; ++spb) {
+      const int nb = (nstrip + spb - 1) / spb, per_cu = (P * nb + 255) / 256;
+      const double columns = (K + g - 1) / g, per_column = 4.0 * (kConvRows * K + kConvRows + K);
+      const double cost = (per_cu * waves(spb) + 3) / 4 * columns * per_column +
+                          per_cu * (spb * kConvRows + K) * (W + K) / 64.0 * 16.0;
+      if (least == 0.0 || cost < least) {
+        least = cost;
+        best = spb;
+      }
+    }
+  }
+  *band_rows = best * kConvRows;
+  *bands = (H + *band_rows - 1) / *band_rows;
+  *threads = 64 * std::max(1, std::min(kBandMaxThreads / 64, waves(best)));
 }
 
 int subpix_key(const ModelCfg& c) { return (c.mass * 2 + c.lens_light) * 16 + (c.nmax + 1); }
@@ -524,16 +542,18 @@ int launch_conv(int K, const Group& g, size_t lds, hipStream_t st) {
 // The banded PSF pass (small batches): block offsets are set here for each kernel.
 static int launch_conv_band(int K, Group& g, int mode, bool chain, hipStream_t st) {
   size_t lds = 0;
+  int threads = 64;
   for (int i = 0; i < g.nsys; ++i) {
     const SysDesc& s = g.sys[i];
     if (s.conv_mfma) continue;
-    const int nsr = s.band_rows / kConvRows;
-    lds = std::max(lds, sizeof(float) * size_t((nsr * kConvRows + K - 1) | 1) * (s.W + K - 1));
+    lds = std::max(lds, sizeof(float) * (band_tile_floats(s.band_rows, s.W, K) +
+                                         size_t(K) * ((K + 3) & ~3)));
+    threads = std::max(threads, s.band_threads);
   }
   int rc = conv_lds_limit(lds);
   if (rc) return rc;
   set_blocks(g, [](const SysDesc& s) { return s.conv_mfma ? 0 : blocks_conv_band(s); });
-  if ((rc = launch(conv_table().band[(K - 1) / 2], g.block0[g.nsys], kConvThreads, lds, g, st)))
+  if ((rc = launch(conv_table().band[(K - 1) / 2], g.block0[g.nsys], threads, lds, g, st)))
     return rc;
   if (mode == 2) {
     // the sampler's chains keep the VALU sums (glens_chain.h)
@@ -543,8 +563,7 @@ static int launch_conv_band(int K, Group& g, int mode, bool chain, hipStream_t s
     set_blocks(g, [&](const SysDesc& s) {
       return s.conv_mfma || on_mfma(s) ? 0 : blocks_conv_band(s);
     });
-    if ((rc = launch(conv_table().band_adj[(K - 1) / 2], g.block0[g.nsys], kConvThreads, lds, g,
-                     st)))
+    if ((rc = launch(conv_table().band_adj[(K - 1) / 2], g.block0[g.nsys], threads, lds, g, st)))
       return rc;
     if (!any_mfma) return GL_OK;
     for (int i = 0; i < g.nsys; ++i) g.sys[i].mode = 3;

@@ -23,8 +23,8 @@
 namespace glens {
 
 constexpr int kConvThreads = 256;
+constexpr int kBandMaxThreads = 512;  // banded PSF pass
 constexpr int kMfmaMaxThreads = 1024;
-constexpr int kConvRows = 8;  // output rows per lane in the PSF pass
 constexpr int kConvMaxStrips = 8;  // strips per lane: (H/8 rounded up) * W <= 8 * 256
 
 // prologue: one 64-lane block per particle (prologue_particle)
@@ -147,12 +147,12 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 template <int K>
 __device__ __forceinline__ void correlate_strip(const float* __restrict__ buf, int Hs, int i0,
                                                 int j, const float* __restrict__ taps,
-                                                float* acc, int b0 = 0, int bstep = 1) {
+                                                float* acc) {
   constexpr int R = kConvRows;
 #pragma unroll
   for (int r = 0; r < R; ++r) acc[r] = 0.f;
 #pragma unroll 1
-  for (int b = b0; b < K; b += bstep) {
+  for (int b = 0; b < K; ++b) {
     const float* colp = buf + (j + b) * Hs + i0;
     float col[R + K - 1];
 #pragma unroll
@@ -577,7 +577,7 @@ conv_mfma_kernel(Group g) {
 // adjacent lanes (columns g, g + G, ...), whose partial sums are then added by an xor
 // butterfly: more lanes in flight and K^2 kConvRows / G FMAs in each lane's chain.
 // ------------------------------------------------------------------------------------------
-static_assert(kConvThreads % 4 == 0, "whole lane groups of the split PSF columns");
+static_assert(kBandMaxThreads % 64 == 0, "whole lane groups of the split PSF columns");
 struct Band {
   int part, band, r0, r1, nsr, Hs;
 };
@@ -602,32 +602,89 @@ __device__ __forceinline__ Band band_of(const SysDesc& s, int local, int K) {
   return b;
 }
 
-// Rows [r0 - C, r1 + C) of src (zero outside the image) into the column-major LDS tile.
+// Taps of one PSF column in LDS: a multiple of four, so that they are read four at a time.
 template <int K>
-__device__ __forceinline__ void load_band(const float* __restrict__ src, const SysDesc& s,
-                                          const Band& b, float* A) {
-  constexpr int C = (K - 1) / 2;
-  const int W = s.W, Wp = W + K - 1;
-  for (int idx = threadIdx.x; idx < b.Hs * Wp; idx += blockDim.x) A[idx] = 0.f;
-  __syncthreads();
-  const int lo = max(0, b.r0 - C), hi = min(s.H, b.r1 + C);
-  for (int idx = threadIdx.x; idx < (hi - lo) * W; idx += blockDim.x) {
-    const int i = lo + idx / W, j = idx - (idx / W) * W;
-    A[(j + C) * b.Hs + (i - b.r0) + C] = src[(size_t)i * W + j];
+constexpr int tap_pitch() {
+  return (K + 3) & ~3;
+}
+
+// Rows [r0 - C, r0 - C + Hs) of src (zero outside the image) into the column-major LDS tile A, and
+// the PSF's taps column by column into T (read from there, they need neither 21 scalar loads a
+// column nor, where lanes take different columns, as many vector loads from memory). One pass,
+// several loads in flight.
+template <int K>
+__device__ __forceinline__ void load_band(const float* __restrict__ src,
+                                          const float* __restrict__ taps, const SysDesc& s,
+                                          const Band& b, float* A, float* T) {
+  constexpr int C = (K - 1) / 2, U = 4;
+  const int H = s.H, W = s.W, Wp = W + K - 1, n = b.Hs * Wp;
+  for (int idx = threadIdx.x; idx < K * K; idx += blockDim.x)
+    T[(idx % K) * tap_pitch<K>() + idx / K] = taps[idx];
+  PixelWalk w(Wp);
+  for (int idx = threadIdx.x; idx < n; idx += U * blockDim.x) {
+    float v[U];
+    int o[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = b.r0 + w.i - C, j = w.j - C;
+      o[u] = w.j * b.Hs + w.i;
+      v[u] = 0.f;
+      if (unsigned(i) < unsigned(H) && unsigned(j) < unsigned(W)) v[u] = src[i * W + j];
+      w.next();
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (idx + u * int(blockDim.x) < n) A[o[u]] = v[u];
   }
   __syncthreads();
 }
 
+// correlate_strip with the taps in LDS (load_band), columns b0, b0 + bstep, ...; the same sums in
+// the same order.
 template <int K>
-__global__ void __launch_bounds__(kConvThreads) conv_band_kernel(Group g) {
-  extern __shared__ float lds[];
-  __shared__ double red[kConvThreads / 64];
+__device__ __forceinline__ void band_strip(const float* __restrict__ A,
+                                           const float* __restrict__ T, int Hs, int i0, int j,
+                                           float* acc, int b0, int bstep) {
+  constexpr int R = kConvRows, Kp = tap_pitch<K>();
+#pragma unroll
+  for (int r = 0; r < R; ++r) acc[r] = 0.f;
+#pragma unroll 1
+  for (int b = b0; b < K; b += bstep) {
+    const float* colp = A + (j + b) * Hs + i0;
+    float col[R + K - 1], kv[Kp];
+#pragma unroll
+    for (int q = 0; q < Kp; q += 4) {
+      const float4 t = *reinterpret_cast<const float4*>(T + b * Kp + q);
+      kv[q] = t.x;
+      kv[q + 1] = t.y;
+      kv[q + 2] = t.z;
+      kv[q + 3] = t.w;
+    }
+#pragma unroll
+    for (int rr = 0; rr < R + K - 1; ++rr) col[rr] = colp[rr];
+#pragma unroll
+    for (int a = 0; a < K; ++a) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) acc[r] = fmaf(kv[a], col[r + a], acc[r]);
+    }
+  }
+}
+
+// Bound by VALU issue where the batch fills the chip, by latency below. Bands and block size
+// follow the waves on the fullest CU (conv_bands); the taps come from LDS. Measured: 47.5 -> 39.2 us
+// (80 x 80, K = 21, 300 vectors; products alone 21.5), 56.0 -> 50.9 us (500), 12.9 -> 11.2 us (60 x 60,
+// 64 vectors, columns over four lanes).
+template <int K>
+__global__ void __launch_bounds__(kBandMaxThreads) conv_band_kernel(Group g) {
+  extern __shared__ __align__(16) float lds[];
+  __shared__ double red[kBandMaxThreads / 64];
   const int si = find_sys(g, blockIdx.x);
   const SysDesc& s = g.sys[si];
   const Band b = band_of(s, blockIdx.x - g.block0[si], K);
   constexpr int R = kConvRows;
   const int W = s.W, HW = s.H * W, mode = s.mode;
-  load_band<K>(s.m0 + (size_t)b.part * HW, s, b, lds);
+  float* T = lds + band_tile_floats(s.band_rows, W, K);
+  load_band<K>(s.m0 + (size_t)b.part * HW, s.psf_flip, s, b, lds, T);
   double ll = 0.0, c2 = 0.0;
   // work items (strip, column, PSF-column share); the G lanes of one strip are adjacent, and
   // blockDim and the item count are multiples of G, so they run the loop together
@@ -636,13 +693,9 @@ __global__ void __launch_bounds__(kConvThreads) conv_band_kernel(Group g) {
     const int item = sidx >> gs, g0 = sidx & (G - 1);
     const int st = item / W, j = item - st * W, i0 = st * R;
     float acc[R];
-    if (G == 1) {
-      correlate_strip<K>(lds, b.Hs, i0, j, s.psf_flip, acc);
-    } else {
-      correlate_strip<K>(lds, b.Hs, i0, j, s.psf_flip, acc, g0, G);
-      split_sum(acc, G);
-      if (g0 != 0) continue;
-    }
+    band_strip<K>(lds, T, b.Hs, i0, j, acc, g0, G);
+    split_sum(acc, G);
+    if (g0 != 0) continue;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int i = b.r0 + i0 + r;
@@ -677,27 +730,24 @@ __global__ void __launch_bounds__(kConvThreads) conv_band_kernel(Group g) {
 }
 
 template <int K>
-__global__ void __launch_bounds__(kConvThreads) conv_band_adj_kernel(Group g) {
-  extern __shared__ float lds[];
+__global__ void __launch_bounds__(kBandMaxThreads) conv_band_adj_kernel(Group g) {
+  extern __shared__ __align__(16) float lds[];
   const int si = find_sys(g, blockIdx.x);
   const SysDesc& s = g.sys[si];
   const Band b = band_of(s, blockIdx.x - g.block0[si], K);
   constexpr int R = kConvRows;
   const int W = s.W, HW = s.H * W;
   if (b.band == 0 && threadIdx.x == 0) band_totals(s, b.part);
-  load_band<K>(s.seed + (size_t)b.part * HW, s, b, lds);
+  float* T = lds + band_tile_floats(s.band_rows, W, K);
+  load_band<K>(s.seed + (size_t)b.part * HW, s.psf, s, b, lds, T);
   const int G = s.band_split, gs = G >> 1;  // G = 1, 2, 4: log2 G = G / 2
   for (int sidx = threadIdx.x; sidx < b.nsr * W * G; sidx += blockDim.x) {
     const int item = sidx >> gs, g0 = sidx & (G - 1);
     const int st = item / W, j = item - st * W, i0 = st * R;
     float acc[R];
-    if (G == 1) {
-      correlate_strip<K>(lds, b.Hs, i0, j, s.psf, acc);
-    } else {
-      correlate_strip<K>(lds, b.Hs, i0, j, s.psf, acc, g0, G);
-      split_sum(acc, G);
-      if (g0 != 0) continue;
-    }
+    band_strip<K>(lds, T, b.Hs, i0, j, acc, g0, G);
+    split_sum(acc, G);
+    if (g0 != 0) continue;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int i = b.r0 + i0 + r;

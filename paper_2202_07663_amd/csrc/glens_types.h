@@ -159,6 +159,7 @@ struct SysDesc {
   int bands;           // banded PSF pass: row bands per particle (1: whole image)
   int band_rows;       // rows per band (a multiple of the strip height)
   int band_split;      // banded pass: lanes that share one strip's PSF columns (1, 2 or 4)
+  int band_threads;    // banded pass: threads per block
   const float* obs;
   const float* psf;      // K*K
   const float* psf_flip; // K*K, flipped in both axes
@@ -236,6 +237,13 @@ __host__ __device__ inline MfmaGeom mfma_geom(int H, int W, int K) {
 __host__ __device__ inline int mfma_lds_bytes(const MfmaGeom& q, int H, int W) {
   const int over = 2 * (q.TR * 16 - H) * q.pitch;
   return 4 * q.Hq * q.pitch + (4 * H * W > over ? 4 * H * W : over);
+}
+
+constexpr int kConvRows = 8;  // output rows per lane in the VALU PSF passes
+// Floats of the banded pass's image tile (column-major, odd pitch), rounded up to a multiple of
+// four: the PSF's taps follow.
+__host__ __device__ inline int band_tile_floats(int band_rows, int W, int K) {
+  return ((((band_rows + K - 1) | 1) * (W + K - 1)) + 3) & ~3;
 }
 
 constexpr int kMaxGroup = 10;
