@@ -210,6 +210,13 @@ static int choose_fwd_tiles(int P, int HW) {
   return std::max(1, std::min(want, maxt));
 }
 
+// Tiles of the batched calls' adjoint (at most choose_tiles, which sizes the accumulators). At
+// n_max = 8 a CU holds two blocks instead of three or more, and a tile's fixed part (the sums of
+// up to 77 values across its lanes) weighs as much as two sub-pixels: half as many tiles.
+static int choose_adj_tiles(const ModelCfg& c, int P, int tiles) {
+  return c.nmax >= 8 ? std::min(tiles, std::max(1, (1024 + P - 1) / P)) : tiles;
+}
+
 int beta_per_particle(const ModelCfg& c) { return c.k * c.k * c.H * c.W; }
 
 // Accumulator rows (particle x tile) that calls of up to P vectors need: the tile count
@@ -314,6 +321,8 @@ SysDesc make_sys(const SystemData& sd, const Workspace& ws, int P, int tiles) {
   s.tiles = tiles;
   const int HW = c.H * c.W;
   s.pix_per_tile = (HW + tiles - 1) / tiles;
+  s.adj_tiles = choose_adj_tiles(c, P, tiles);
+  s.adj_pix_per_tile = (HW + s.adj_tiles - 1) / s.adj_tiles;
   s.ftiles = choose_fwd_tiles(P, HW);
   s.fpix_per_tile = (HW + s.ftiles - 1) / s.ftiles;
   s.obs = sd.obs;
@@ -342,6 +351,11 @@ SysDesc make_sys(const SystemData& sd, const Workspace& ws, int P, int tiles) {
   return s;
 }
 
+// LDS of a band's block: its image tile and the PSF's taps.
+static size_t band_lds_bytes(int band_rows, int W, int K) {
+  return sizeof(float) * (band_tile_floats(band_rows, W, K) + size_t(K) * ((K + 3) & ~3));
+}
+
 void conv_bands(int P, int H, int W, int K, int* bands, int* band_rows, int* split,
                 int* threads) {
   // one band from 512 particles on, and for an image of one strip
@@ -359,13 +373,16 @@ void conv_bands(int P, int H, int W, int K, int* bands, int* band_rows, int* spl
   int best = nstrip;
   if (!whole) {
     // strips per band: the fewest cycles on the fullest CU, for the products (whole waves, spread
-    // over four SIMDs) and for loading each band with its halo (about 16 instructions per 64
-    // values); a sum does not depend on its band
+    // over four SIMDs, as many blocks at a time as its LDS holds) and for loading each band with
+    // its halo (about 16 instructions per 64 values); a sum does not depend on its band
     double least = 0.0;
     for (int spb = (nstrip + kConvMaxBands - 1) / kConvMaxBands; spb < nstrip; ++spb) {
       const int nb = (nstrip + spb - 1) / spb, per_cu = (P * nb + 255) / 256;
       const double columns = (K + g - 1) / g, per_column = 4.0 * (kConvRows * K + kConvRows + K);
-      const double cost = (per_cu * waves(spb) + 3) / 4 * columns * per_column +
+      const int kb = int((band_lds_bytes(spb * kConvRows, W, K) + 512) / 2048) + 1;  // of 156 KB
+      const int fit = std::max(1, 78 / kb), w = waves(spb);
+      const int turns = per_cu / fit * ((fit * w + 3) / 4) + (per_cu % fit * w + 3) / 4;
+      const double cost = turns * columns * per_column +
                           per_cu * (spb * kConvRows + K) * (W + K) / 64.0 * 16.0;
       if (least == 0.0 || cost < least) {
         least = cost;
@@ -375,7 +392,9 @@ void conv_bands(int P, int H, int W, int K, int* bands, int* band_rows, int* spl
   }
   *band_rows = best * kConvRows;
   *bands = (H + *band_rows - 1) / *band_rows;
-  *threads = 64 * std::max(1, std::min(kBandMaxThreads / 64, waves(best)));
+  // waves for the strips, and enough to load the tile in two batches of loads
+  const int load = band_tile_floats(*band_rows, W, K) / (64 * 8);
+  *threads = 64 * std::max(1, std::min(kBandMaxThreads / 64, std::max(waves(best), load)));
 }
 
 int subpix_key(const ModelCfg& c) { return (c.mass * 2 + c.lens_light) * 16 + (c.nmax + 1); }
@@ -546,8 +565,7 @@ static int launch_conv_band(int K, Group& g, int mode, bool chain, hipStream_t s
   for (int i = 0; i < g.nsys; ++i) {
     const SysDesc& s = g.sys[i];
     if (s.conv_mfma) continue;
-    lds = std::max(lds, sizeof(float) * (band_tile_floats(s.band_rows, s.W, K) +
-                                         size_t(K) * ((K + 3) & ~3)));
+    lds = std::max(lds, band_lds_bytes(s.band_rows, s.W, K));
     threads = std::max(threads, s.band_threads);
   }
   int rc = conv_lds_limit(lds);
@@ -619,7 +637,7 @@ int run_group(Group& g, int key, int K, int mode, hipStream_t st, hipEvent_t* ev
   }
   GL_HIP(mark(3));
   if (mode != 2) return GL_OK;
-  set_blocks(g, blocks_subpix);
+  set_blocks(g, chain ? blocks_subpix : blocks_subpix_adj);
   if ((rc = chain ? launch_chain_adj(key, g, st) : launch_subpix_adj(key, g, st))) return rc;
   GL_HIP(mark(4));
   if (!finalize) return GL_OK;
@@ -698,7 +716,7 @@ int gl_model_plan(const gl_model* m, int P, gl_plan* out) {
   const int tiles = choose_tiles(P, HW);
   const SysDesc s = make_sys(m->sys, m->ws, P, tiles);
   out->psf_path = s.conv_mfma ? GL_PSF_MFMA : (s.bands > 1 ? GL_PSF_BANDED : GL_PSF_VALU);
-  out->tiles = s.tiles;
+  out->tiles = s.adj_tiles;
   out->fwd_tiles = s.ftiles;
   out->bands = s.bands;
   out->workspace_bytes = workspace_bytes(P, acc_rows_upto(P, HW), HW, c.d, false,

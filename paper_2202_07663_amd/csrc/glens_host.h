@@ -70,7 +70,8 @@ int workspace_reserve(Workspace& ws, int P, int tiles, int HW, int d, bool fit_b
                       int beta_pp);
 void workspace_free(Workspace& ws);
 
-// Number of sub-pixel work tiles per particle for P particles of an H x W image.
+// Number of sub-pixel work tiles per particle for P particles of an H x W image (the chains'
+// adjoint; the batched one takes as many or fewer).
 int choose_tiles(int P, int HW);
 
 // Device copy of the fixed inputs of one system (one allocation, laid out by system_image).
@@ -118,7 +119,8 @@ constexpr size_t kConvLdsMax = 160 * 1024 - 256;  // dynamic LDS allowed to the 
 
 // Block counts of one system per stage.
 inline int blocks_prologue(const SysDesc& s) { return s.P; }  // prologue, finalize
-inline int blocks_subpix(const SysDesc& s) { return s.P * s.tiles; }
+inline int blocks_subpix(const SysDesc& s) { return s.P * s.tiles; }  // the chains' adjoint
+inline int blocks_subpix_adj(const SysDesc& s) { return s.P * s.adj_tiles; }
 inline int blocks_subpix_fwd(const SysDesc& s) { return s.P * s.ftiles; }
 inline int blocks_conv(const SysDesc& s) { return s.P; }
 inline int blocks_conv_band(const SysDesc& s) { return s.P * s.bands; }

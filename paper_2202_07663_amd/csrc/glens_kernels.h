@@ -767,11 +767,6 @@ __global__ void __launch_bounds__(64) conv_band_sum_kernel(Group g) {
 // ------------------------------------------------------------------------------------------
 // sub-pixel adjoint
 // ------------------------------------------------------------------------------------------
-template <int NMAX>
-constexpr int n_slots() {
-  return NMAX < 0 ? A_SHP_BETA : A_SHP_C + (NMAX + 1) * (NMAX + 2) / 2;
-}
-
 // The sub-pixels of pixels [p0, p1) of one particle into the per-lane accumulators.
 // GENERAL = false: the particle has no floored sub-pixel and |eps| >= kSxClosedMin.
 template <int MASS, int LL, int NMAX, bool GENERAL>
@@ -816,9 +811,9 @@ __device__ __forceinline__ void adj_pixels(const SysDesc& s, const PConst& c,
         if (LL) {
           const float lx = float(x - c.lxs);
           const float lv = sersic_adj(c.lens, lx, ly, fmaf(c.lens.qa, lx, lpx),
-                                      fmaf(c.lens.qbh, lx, lpy), sb, acc + A_LENS);
-          acc[A_LENS + L_DX] = fmaf(lv, lx, acc[A_LENS + L_DX]);
-          acc[A_LENS + L_DY] = fmaf(lv, ly, acc[A_LENS + L_DY]);
+                                      fmaf(c.lens.qbh, lx, lpy), sb, acc + lens_slot(NMAX));
+          acc[lens_slot(NMAX) + L_DX] = fmaf(lv, lx, acc[lens_slot(NMAX) + L_DX]);
+          acc[lens_slot(NMAX) + L_DY] = fmaf(lv, ly, acc[lens_slot(NMAX) + L_DY]);
         }
         // the floored sub-pixel's mass terms are added by finalize from the prologue's
         // exact derivatives
@@ -835,28 +830,28 @@ __device__ __forceinline__ void adj_pixels(const SysDesc& s, const PConst& c,
 // is instructions per sub-pixel: about 385 with every sum of the gradient taken per sub-pixel,
 // 320 with the sums of mass_adjoint, sersic_adj and shapelet_adj. Measured: 543 -> 463 us (60 x 60,
 // n_max 6, 4096 vectors), 67 -> 53 us (80 x 80 without shapelets, 300), 122 -> 90 us (53 x 37 SIE,
-// k = 3, n_max 3, 777). From n_max = 7 the accumulators and coefficients (up to 122 registers) do
-// not fit three waves per SIMD (168 registers: 60 spilled in the loop); two waves hide the
-// latencies of this instruction mix as well, and the 100 x 100, n_max 8 system went
-// 1510 -> 879 us at 2048 vectors.
+// k = 3, n_max 3, 777). At n_max = 8 the accumulators and coefficients (122 registers) do not
+// fit three waves per SIMD (168 registers: 76 spilled in the loop); two waves hide the latencies
+// of this instruction mix as well: 1510 -> 890 us (100 x 100, 2048 vectors). n_max = 7 keeps three
+// (101 -> 93 us at 47 x 35, k = 4, 317 vectors; with two 111).
 template <int MASS, int LL, int NMAX>
 __global__ void __launch_bounds__(kSubThreads)
-__attribute__((amdgpu_waves_per_eu(NMAX >= 7 ? 2 : 3)))
+__attribute__((amdgpu_waves_per_eu(NMAX >= 8 ? 2 : 3)))
 subpix_adj_kernel(Group g) {
-  constexpr int NS = n_slots<NMAX>();
+  constexpr int NS = lens_slot(NMAX) + (LL ? 8 : 0);
   __shared__ double red[kSubThreads / 64][NS];
   const int si = find_sys(g, blockIdx.x);
   const SysDesc& s = g.sys[si];
   const int lb = blockIdx.x - g.block0[si];
-  const int part = lb / s.tiles, tile = lb - part * s.tiles;
+  const int part = lb / s.adj_tiles, tile = lb - part * s.adj_tiles;
   const PConst& c = s.pc[part];
   __shared__ float s_nc[kMaxTerms], s_dc[kMaxTerms];
   stage_series(c, -2.8853900817779268f, s_nc, s_dc);  // mass_adjoint's -2 / ln 2
   // beta - x_s from the forward pass (kept there for gradient calls)
   const float2* beta = s.beta + (size_t)part * s.k * s.k * s.H * s.W;
   const int HW = s.H * s.W;
-  const int p0 = tile * s.pix_per_tile;
-  const int p1 = min(HW, p0 + s.pix_per_tile);
+  const int p0 = tile * s.adj_pix_per_tile;
+  const int p1 = min(HW, p0 + s.adj_pix_per_tile);
   const float* sbar = s.sbar + (size_t)part * HW;
   float acc[NS];
 #pragma unroll
@@ -878,7 +873,7 @@ subpix_adj_kernel(Group g) {
     adj_pixels<MASS, LL, NMAX, false>(s, c, s_nc, s_dc, shp, beta, sbar, p0, p1, acc);
   else
     adj_pixels<MASS, LL, NMAX, true>(s, c, s_nc, s_dc, shp, beta, sbar, p0, p1, acc);
-  block_sums<NS>(acc, red, s.acc + ((size_t)part * s.tiles + tile) * kNAcc);
+  block_sums<NS>(acc, red, s.acc + ((size_t)part * s.adj_tiles + tile) * kNAcc);
 }
 
 // finalize: one 64-lane block per particle (finalize_particle)

@@ -83,19 +83,20 @@ __device__ __forceinline__ FinalGrad finalize_particle(const SysDesc& s, int p) 
   __shared__ float gr[kMaxParams];
   const PConst& c = s.pc[p];
   const int lane = threadIdx.x, nmax = s.nmax;
-  const int beta0 = CHAIN ? int(chain::A_SHP_BETA) : int(A_SHP_BETA);
-  const int lens0 = CHAIN ? int(chain::A_LENS) : int(A_LENS);
+  const int lens0 = CHAIN ? int(chain::A_LENS) : lens_slot(nmax);
   const int src0 = CHAIN ? int(chain::A_SRC) : int(A_SRC);
-  const int ns = beta0 + (nmax < 0 ? 0 : 1 + (nmax + 1) * (nmax + 2) / 2);
+  const int ns = CHAIN ? int(chain::A_SHP_BETA) + (nmax < 0 ? 0 : 1 + (nmax + 1) * (nmax + 2) / 2)
+                       : lens0 + (s.lens_light ? 8 : 0);
+  const int tiles = CHAIN ? s.tiles : s.adj_tiles;
   const double logl = s.logl[p];
   const LightC L = lane == 1 ? c.lens : c.src;  // on its way while the sums are taken
-  const double* acc = s.acc + (size_t)p * s.tiles * kNAcc;
+  const double* acc = s.acc + (size_t)p * tiles * kNAcc;
   for (int q = lane; q < ns; q += blockDim.x) {
     double v = 0.0;
-    for (int t0 = 0; t0 < s.tiles; t0 += 16) {  // sixteen loads in flight, added in tile order
+    for (int t0 = 0; t0 < tiles; t0 += 16) {  // sixteen loads in flight, added in tile order
       double b[16];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) b[u] = t0 + u < s.tiles ? acc[(t0 + u) * kNAcc + q] : 0.0;
+      for (int u = 0; u < 16; ++u) b[u] = t0 + u < tiles ? acc[(t0 + u) * kNAcc + q] : 0.0;
 #pragma unroll
       for (int u = 0; u < 16; ++u) v += b[u];
     }

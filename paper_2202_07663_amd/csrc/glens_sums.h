@@ -11,13 +11,17 @@ namespace glens {
 constexpr int kSubThreads = 256;
 
 // Row and column of the pixels p0 + threadIdx.x + n blockDim.x of a W-column image, stepped
-// without a division per pixel.
+// without a division per pixel. The first row and the step come from a float reciprocal: with
+// fewer than 2^15 pixels and W <= 158 columns (p + 1/2) / W is 1/316 or more from an integer,
+// and its rounding error below 1e-4, so that the integer part is exact.
 struct PixelWalk {
   int i, j, di, dj, W;
   __device__ __forceinline__ PixelWalk(int W_, int p0 = 0) : W(W_) {
-    i = (p0 + int(threadIdx.x)) / W;
-    j = p0 + int(threadIdx.x) - i * W;
-    di = int(blockDim.x) / W;
+    const float inv = rcp_f32(float(W));
+    const int p = p0 + int(threadIdx.x);
+    i = int((float(p) + 0.5f) * inv);
+    j = p - i * W;
+    di = int((float(blockDim.x) + 0.5f) * inv);
     dj = int(blockDim.x) - di * W;
   }
   __device__ __forceinline__ void next() {
@@ -65,38 +69,36 @@ __device__ __forceinline__ void wave_sum_step(double* v, int off, int lane) {
 // lane keeps one half of its values, sends the other half to lane ^ o and adds what it
 // receives, so each step halves the values a lane holds. Every sum pairs lanes in the same
 // order as a separate xor butterfly per value would, with about N shuffles instead of
-// 6 NS. The first step shuffles the FP32 values and adds them in FP64.
+// 6 NS. The first step shuffles the FP32 values and adds them in FP64. More than 64 values go in
+// two parts (64 and the rest, padded to its own power of two: with 68 padded to 128 the sums cost
+// as much as two sub-pixels).
 template <int NS>
 __device__ __forceinline__ void wave_sums(const float* acc, double* out) {
-  constexpr int N = NS <= 32 ? 32 : (NS <= 64 ? 64 : 128);
-  static_assert(NS <= 128, "too many accumulators");
-  const int lane = threadIdx.x & 63;
-  double v[N / 2];
-  {
-    const bool up = lane & 32;
+  if constexpr (NS > 64) {
+    wave_sums<64>(acc, out);
+    wave_sums<NS - 64>(acc + 64, out + 64);
+  } else {
+    constexpr int N = NS <= 4 ? 4 : (NS <= 8 ? 8 : (NS <= 16 ? 16 : (NS <= 32 ? 32 : 64)));
+    const int lane = threadIdx.x & 63;
+    double v[N / 2];
+    {
+      const bool up = lane & 32;
 #pragma unroll
-    for (int i = 0; i < N / 2; ++i) {
-      const float lo = i < NS ? acc[i] : 0.f, hi = i + N / 2 < NS ? acc[i + N / 2] : 0.f;
-      const float send = up ? lo : hi;
-      v[i] = double(up ? hi : lo) + double(__shfl_xor(send, 32, 64));
+      for (int i = 0; i < N / 2; ++i) {
+        const float lo = i < NS ? acc[i] : 0.f, hi = i + N / 2 < NS ? acc[i + N / 2] : 0.f;
+        const float send = up ? lo : hi;
+        v[i] = double(up ? hi : lo) + double(__shfl_xor(send, 32, 64));
+      }
     }
-  }
-  constexpr int n1 = N / 2, n2 = halved(n1), n3 = halved(n2), n4 = halved(n3), n5 = halved(n4);
-  wave_sum_step<n1>(v, 16, lane);
-  wave_sum_step<n2>(v, 8, lane);
-  wave_sum_step<n3>(v, 4, lane);
-  wave_sum_step<n4>(v, 2, lane);
-  wave_sum_step<n5>(v, 1, lane);
-  // lane l now holds value (l * N / 64) + i for i < N / 64 (N = 32: lanes 2q and 2q + 1
-  // both hold value q)
-  if (N >= 64) {
-#pragma unroll
-    for (int i = 0; i < N / 64; ++i) {
-      const int q = lane * (N / 64) + i;
-      if (q < NS) out[q] = v[i];
-    }
-  } else if ((lane & 1) == 0 && (lane >> 1) < NS) {
-    out[lane >> 1] = v[0];
+    constexpr int n1 = N / 2, n2 = halved(n1), n3 = halved(n2), n4 = halved(n3), n5 = halved(n4);
+    wave_sum_step<n1>(v, 16, lane);
+    wave_sum_step<n2>(v, 8, lane);
+    wave_sum_step<n3>(v, 4, lane);
+    wave_sum_step<n4>(v, 2, lane);
+    wave_sum_step<n5>(v, 1, lane);
+    // the 64 / N lanes from q 64 / N on hold value q
+    constexpr int per = 64 / N;
+    if (lane % per == 0 && lane / per < NS) out[lane / per] = v[0];
   }
 }
 

@@ -45,15 +45,18 @@ enum AccSlot {
   A_M_HZR = 9, A_M_HZI = 10, // sum Hx z
   A_M_G1 = 11, A_M_G2 = 12,  // sum g.(zr, -zi), g.(zi, zr)
   A_M_WR = 13, A_M_WI = 14,  // sum gb A w u2 dS/dX (|eps| < kSxClosedMin only)
-  A_LENS = 15,    // 8 slots, see LightSlot
-  A_SRC = 23,     // 8 slots; the centre slots also collect the shapelet gradient
-  A_SHP_BETA = 31,
-  A_SHP_C = 32,   // kMaxShp slots
+  A_SRC = 15,     // 8 slots, see LightSlot; the centre slots also collect the shapelet gradient
+  A_SHP_BETA = 23,
+  A_SHP_C = 24,   // one slot per shapelet coefficient, then the lens light's 8 (lens_slot)
 };
+// First slot of the lens light, which comes last so that systems without one do not sum it.
+__host__ __device__ constexpr int lens_slot(int nmax) {
+  return nmax < 0 ? int(A_SHP_BETA) : int(A_SHP_C) + (nmax + 1) * (nmax + 2) / 2;
+}
 // Sums of one light profile, with E = I / I0, rho = (R / R_eff)^(1/n) and s the weighted
 // 2 dI/dR^2: E, E rho, E rho log2(rho) (all weighted), s dx^2, s dx dy, s dy^2; L_DX, L_DY: the source's gradient in the offset, the lens light's s dx, s dy.
 enum LightSlot { L_E = 0, L_RHO = 1, L_RHOLN = 2, L_XX = 3, L_XY = 4, L_YY = 5, L_DX = 6, L_DY = 7 };
-static_assert(A_SHP_C + kMaxShp <= kNAcc, "accumulator slots");
+static_assert(lens_slot(kMaxNmax) + 8 <= kNAcc, "accumulator slots");
 
 // Elliptical Sersic constants of one particle.
 struct LightC {
@@ -153,6 +156,8 @@ struct SysDesc {
   int P;
   int tiles;           // sub-pixel work tiles per particle (adjoint; its accumulator rows)
   int pix_per_tile;
+  int adj_tiles;       // the same for the batched calls' adjoint
+  int adj_pix_per_tile;
   int ftiles;          // the same for the forward pass
   int fpix_per_tile;
   int mode;            // conv kernel: 0 image, 1 log L, 2 log L + adjoint seed
