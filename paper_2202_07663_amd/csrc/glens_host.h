@@ -46,7 +46,7 @@ struct Workspace {
   size_t cap_rows = 0;     // accumulator rows (particle x tile) of acc
   PConst* pc = nullptr;
   float* m0 = nullptr;
-  float* sbar = nullptr;
+  float* sbar = nullptr;   // shares the memory of m0
   double* acc = nullptr;
   double* logl = nullptr;  // internal log L (fits)
   float* grad = nullptr;   // internal gradient (fits)
