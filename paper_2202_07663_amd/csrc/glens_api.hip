@@ -476,7 +476,9 @@ static int launch(GroupKernel k, int blocks, int threads, size_t lds, const Grou
 }
 
 int launch_prologue(const Group& g, hipStream_t st) {
-  return launch(prologue_kernel, g.block0[g.nsys], 64, 0, g, st);
+  const int n = g.block0[g.nsys], waves = prologue_waves(n);
+  return launch(waves == 1 ? prologue_kernel<1> : prologue_kernel<kPrologueMaxWaves>, n, 64 * waves,
+                0, g, st);
 }
 int launch_subpix_fwd(int key, const Group& g, hipStream_t st) {
   return launch(sub_table().fwd[key], g.block0[g.nsys], kSubThreads, 0, g, st);

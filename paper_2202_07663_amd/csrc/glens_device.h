@@ -429,27 +429,15 @@ constexpr float kLog2e = 1.44269504088896341f;
 
 constexpr double kLn2 = 0.6931471805599453;  // nearest double to ln 2
 
-// Entries of the power tables (PConst::pw) at table index i: i < kPowExp gives B^t 2^(-t e/2)
-// for e = i - kPowExp/2; i = kPowExp + 8 j + k the Taylor coefficient k of m^(-t/2) about
-// m_j = 1 + (j + 1/2)/16: a_0 = m_j^(-t/2), a_k = a_(k-1) (-t/2 - k + 1) / (k m_j).
-GL_HD double pow_table_entry(double t, double log2B, int i) {
-  if (i < kPowExp) return exp2(t * (log2B - 0.5 * (i - kPowExp / 2)));
-  const int j = (i - kPowExp) / 8, k = (i - kPowExp) % 8;
-  if (k > kPowDeg) return 0.0;
-  const double mj = 1.0 + (j + 0.5) / kPowSeg;
-  double a = exp2(-0.5 * t * log2(mj));
-  for (int q = 1; q <= k; ++q) a *= (-0.5 * t - (q - 1)) / (q * mj);
-  return a;
+// The power tables (PConst::pw): entry i < kPowExp is B^t 2^(-t e/2) for e = i - kPowExp/2 ...
+GL_HD double pow_exponent_entry(double t, double log2B, int i) {
+  return exp2(t * (log2B - 0.5 * (i - kPowExp / 2)));
 }
-
-// The power tables shared by `nl` lanes (this one is lane l of them): the exponent entries
-// round-robin, and the sixteen segments' Taylor coefficients one segment per lane on the last
-// kPowSeg lanes (each segment's coefficients by the recursion of pow_table_entry, the same
-// operations in the same order).
-GL_HD void pow_tables_lane(double t, double log2B, int l, int nl, double* pw) {
-  for (int i = l; i < kPowExp; i += nl) pw[i] = pow_table_entry(t, log2B, i);
-  const int j = l - (nl - kPowSeg);
-  if (j < 0) return;
+// ... and kPowExp + 8 j + k the Taylor coefficient k (zero above kPowDeg) of m^(-t/2) about
+// m_j = 1 + (j + 1/2)/16: a_0 = m_j^(-t/2), a_k = a_(k-1) (-t/2 - k + 1) / (k m_j). Segment j (no
+// segment: nothing).
+GL_HD void pow_segments_lane(double t, int j, double* pw) {
+  if (j < 0 || j >= kPowSeg) return;
   double* seg = pw + kPowExp + 8 * j;
   const double mj = 1.0 + (j + 0.5) / kPowSeg;
   double a = exp2(-0.5 * t * log2(mj));
@@ -458,6 +446,14 @@ GL_HD void pow_tables_lane(double t, double log2B, int l, int nl, double* pw) {
     if (q <= kPowDeg) a *= (-0.5 * t - (q - 1)) / (q * mj);
     seg[q] = q <= kPowDeg ? a : 0.0;
   }
+}
+
+// The power tables shared by `nl` lanes (this one is lane l of them): the exponent entries
+// round-robin, and the sixteen segments' Taylor coefficients one segment per lane on the last
+// kPowSeg lanes.
+GL_HD void pow_tables_lane(double t, double log2B, int l, int nl, double* pw) {
+  for (int i = l; i < kPowExp; i += nl) pw[i] = pow_exponent_entry(t, log2B, i);
+  pow_segments_lane(t, l - (nl - kPowSeg), pw);
 }
 
 // A = B^t |w|^-t = B^t (|w|^2)^(-t/2) from the particle's power tables (staged in LDS): with

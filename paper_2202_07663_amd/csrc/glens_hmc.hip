@@ -145,9 +145,9 @@ __device__ __forceinline__ void kick_drift(const HmcArgs& a, const float* s_g, f
     }
   }
   if (!drift) return;
-  __syncthreads();
+  wave_sync();
   chol_t_times(s_chol, a.d, s_p, s_v);
-  __syncthreads();
+  wave_sync();
 #pragma unroll
   for (int u = 0; u < kOwn; ++u) {
     const int j = threadIdx.x + u * kHmcThreads;
@@ -166,12 +166,13 @@ __device__ __forceinline__ void kick_drift(const HmcArgs& a, const float* s_g, f
 // the new position for the next step's pipeline (prologue), which then starts at the sub-pixel
 // forward pass. Two launches fewer per leapfrog step than finalize, kick/drift and prologue
 // apart, with the same arithmetic. Bound by latency: what the chain's state and the factor hold
-// is loaded at the start, and the gradient and the new position pass through LDS: 21.4 -> 16.7 us
+// is loaded at the start, the gradient and the new position pass through LDS, and up to 768 chains
+// the decode is that of four waves (the rest is the first wave alone): 21.4 -> 14.0 us
 // (60 x 60 system, d = 51, 64 chains).
-__global__ void __launch_bounds__(kHmcThreads) hmc_finalize_move_kernel(SysDesc s, HmcArgs a,
-                                                                        float scale, int drift) {
+__device__ __forceinline__ void finalize_move(const SysDesc& s, const HmcArgs& a, float scale,
+                                              int drift, float* s_z) {
   __shared__ double s_t[kMaxParams];
-  __shared__ float s_g[kMaxParams], s_p[kMaxParams], s_v[kMaxParams], s_z[kMaxParams];
+  __shared__ float s_g[kMaxParams], s_p[kMaxParams], s_v[kMaxParams];
   __shared__ __align__(16) float s_chol[kMaxParams * kMaxParams];
   __shared__ int s_bad;
   const int c = blockIdx.x;
@@ -202,7 +203,7 @@ __global__ void __launch_bounds__(kHmcThreads) hmc_finalize_move_kernel(SysDesc 
     s_g[j] = (fg.ok ? fg.g[j] : 0.f) * dth + dlp;
   }
   if (drift) f.store(s_chol, a.d);
-  __syncthreads();
+  wave_sync();
   if (threadIdx.x == 0) {
     double lp = fg.ok ? fg.logl : -INFINITY;
     for (int j = 0; j < a.d; ++j) lp += s_t[j];
@@ -214,7 +215,7 @@ __global__ void __launch_bounds__(kHmcThreads) hmc_finalize_move_kernel(SysDesc 
     a.lp[c] = lp;
     s_bad = bad;
   }
-  __syncthreads();
+  wave_sync();
   const int bad = s_bad;
 #pragma unroll
   for (int u = 0; u < kOwn; ++u) {
@@ -224,9 +225,16 @@ __global__ void __launch_bounds__(kHmcThreads) hmc_finalize_move_kernel(SysDesc 
     a.g[row + j] = s_g[j];
   }
   kick_drift(a, s_g, scale, drift, eps, p0, z0, s_chol, s_p, s_v, s_z);
+}
+
+template <int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) hmc_finalize_move_kernel(SysDesc s, HmcArgs a,
+                                                                       float scale, int drift) {
+  __shared__ float s_z[kMaxParams];
+  if (WAVES == 1 || threadIdx.x < kHmcThreads) finalize_move(s, a, scale, drift, s_z);
   if (!drift) return;
   __syncthreads();
-  prologue_particle(s, c, s_z);
+  prologue_particle<WAVES>(s, blockIdx.x, s_z);
 }
 
 // New momentum p = chol^-T n, saved trajectory start and kinetic energy |n|^2 / 2, then the
@@ -603,8 +611,10 @@ static int hmc_gradient(gl_hmc* h, float scale, int drift, hipStream_t st) {
   rc = run_group(g, subpix_key(c), c.K, 2, st, nullptr, !h->pc_ready, false, true);
   h->pc_ready = false;
   if (rc) return rc;
-  hipLaunchKernelGGL(hmc_finalize_move_kernel, dim3(h->C), dim3(kHmcThreads), 0, st, g.sys[0],
-                     h->a, scale, drift);
+  const int waves = prologue_waves(h->C);
+  hipLaunchKernelGGL(waves == 1 ? hmc_finalize_move_kernel<1>
+                                : hmc_finalize_move_kernel<kPrologueMaxWaves>,
+                     dim3(h->C), dim3(64 * waves), 0, st, g.sys[0], h->a, scale, drift);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return set_error(GL_E_DEVICE, "launch: %s", hipGetErrorString(e));
   h->pc_ready = drift != 0;

@@ -27,10 +27,11 @@ constexpr int kBandMaxThreads = 512;  // banded PSF pass
 constexpr int kMfmaMaxThreads = 1024;
 constexpr int kConvMaxStrips = 8;  // strips per lane: (H/8 rounded up) * W <= 8 * 256
 
-// prologue: one 64-lane block per particle (prologue_particle)
-__global__ void __launch_bounds__(64) prologue_kernel(Group g) {
+// prologue: one block per particle (prologue_particle)
+template <int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) prologue_kernel(Group g) {
   const int si = find_sys(g, blockIdx.x);
-  prologue_particle(g.sys[si], blockIdx.x - g.block0[si]);
+  prologue_particle<WAVES>(g.sys[si], blockIdx.x - g.block0[si]);
 }
 
 // ------------------------------------------------------------------------------------------

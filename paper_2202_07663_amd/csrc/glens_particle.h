@@ -13,25 +13,44 @@
 
 namespace glens {
 
+// Orders the LDS accesses of one wave's lanes (LDS serves a wave in order, so nothing is waited
+// for): the barrier of code that one wave of a block runs alone.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // ------------------------------------------------------------------------------------------
-// prologue: one 64-lane block per particle. Every lane decodes the mass (the same instructions
-// that one lane would take, and its constants are then in registers: passed through the
-// particle's constants in memory they cost two L2 round trips), lane 0 stores it; lanes 1 and 2
-// decode the light profiles and lanes 3 .. one shapelet coefficient each, while lane n
-// (1 <= n < kMaxTerms) computes the series ratio c_n / c_(n-1) and the increment of
-// d log c_n / dt; inclusive scans across the wave (product and sum) then give every lane its
-// c_n and d log c_n / dt; lane 63 looks for the floored sub-pixel while the others fill the
-// power tables; last, the lanes store the series coefficients. Bound by latency: 9.0 -> 7.8 us (60 x 60 EPL, 64
-// vectors), 18.6 -> 16.6 us (4096).
+// prologue: one block of WAVES = 1 or 4 waves per particle. Bound by latency (one chain of FP64
+// logarithms, square roots and divisions, its code fetched once per wave), so four waves take one
+// part each, and decode for themselves what it needs of the mass (passed through the particle's
+// constants in memory it would cost two L2 round trips):
+//   0  the mass, and the series: lane n (1 <= n < kMaxTerms) computes the ratio c_n / c_(n-1)
+//      and the increment of d log c_n / dt; inclusive scans across the wave (product and sum)
+//      give every lane its c_n and d log c_n / dt;
+//   1  lanes 1 and 2 the light profiles, lanes 3 .. one shapelet coefficient each;
+//   2  the power tables' first half and their polynomial segments;
+//   3  the second half; its lane 63 looks for the floored sub-pixel.
+// One wave (a kernel that works on the particle with one wave before) takes them in turn.
 // z_lds (or null): the particle's unconstrained parameters, in LDS, instead of s.z.
 // ------------------------------------------------------------------------------------------
+constexpr int kPrologueMaxWaves = 4;
+// Waves per particle of a launch over n particles: four while the chip runs them all at once
+// (three blocks per CU); beyond, the sum of their work counts, which one wave has less of (60 x 60
+// EPL: 64 particles 7.7 us with one wave, 5.5 with four; 512: 11.0 and 8.8, 1024: 11.7 and 12.6
+// between events; 4096: 16.6 and 28.2 us).
+inline int prologue_waves(int n) { return n <= 768 ? kPrologueMaxWaves : 1; }
+template <int WAVES>
 __device__ __forceinline__ void prologue_particle(const SysDesc& s, int p,
                                                   const float* z_lds = nullptr) {
+  static_assert(WAVES == 1 || WAVES == 4, "one wave for all parts, or one per part");
+  static_assert(kPowExp == 128, "one exponent entry per lane of two waves");
   static_assert(kMaxTerms <= 63, "one lane per series term, lane 63 free");
   static_assert(3 + kMaxShp <= 64, "one lane per shapelet coefficient");
   __shared__ float th[kMaxParams];
-  const int d = s.d, lane = threadIdx.x;
-  for (int j = lane; j < d; j += blockDim.x) {
+  const int d = s.d, lane = threadIdx.x & 63;
+  const int wave = WAVES == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int j = threadIdx.x; j < d; j += 64 * WAVES) {
     const size_t i = (size_t)p * d + j;
     if (s.z) {
       th[j] = bijector_fwd(s.prior[j], z_lds ? z_lds[j] : s.z[i]);
@@ -42,10 +61,25 @@ __device__ __forceinline__ void prologue_particle(const SysDesc& s, int p,
   }
   __syncthreads();
   PConst& c = s.pc[p];
+  const float* xs = th + mass_param_count(s.mass, s.shear) + (s.lens_light ? 7 : 0) + 4;
+  if (WAVES == 4 && wave == 1) {
+    decode_lights_lane(th, s.mass, s.shear, s.lens_light, s.nmax, c, lane);
+    return;
+  }
   MassC m;
   decode_mass(th, s.mass, s.shear, m);
+  if (WAVES == 4 && wave >= 2) {
+    const int i = lane + 64 * (wave - 2);
+    const double log2B = log2(m.bmass);
+    c.pw[i] = pow_exponent_entry(m.t, log2B, i);
+    if (wave == 2)
+      pow_segments_lane(m.t, lane - (64 - kPowSeg), c.pw);
+    else if (lane == 63)
+      decode_floor(s, xs, m, c);
+    return;
+  }
   if (lane == 0) static_cast<MassC&>(c) = m;
-  decode_lights_lane(th, s.mass, s.shear, s.lens_light, s.nmax, c, lane);
+  if (WAVES == 1) decode_lights_lane(th, s.mass, s.shear, s.lens_light, s.nmax, c, lane);
   double cn = 1.0, dsum = 0.0;  // lane n: c_n / c_(n-1) and its d log / dt increment (n >= 1)
   if (lane > 0 && lane < kMaxTerms) series_step(lane, m.t, cn, dsum);
   for (int o = 1; o < 64; o <<= 1) {  // inclusive scans: c_n and d log c_n / dt on lane n
@@ -55,15 +89,17 @@ __device__ __forceinline__ void prologue_particle(const SysDesc& s, int p,
       dsum += pd;
     }
   }
-  if (lane == 63)
-    decode_floor(s, th + mass_param_count(s.mass, s.shear) + (s.lens_light ? 7 : 0) + 4, m, c);
-  else
-    pow_tables_lane(m.t, log2(m.bmass), lane, 63, c.pw);
+  if (WAVES == 1) {
+    if (lane == 63)
+      decode_floor(s, xs, m, c);
+    else
+      pow_tables_lane(m.t, log2(m.bmass), lane, 63, c.pw);
+  }
   if (lane < kMaxTerms) series_store(m, c, lane, cn, dsum);
 }
 
 // ------------------------------------------------------------------------------------------
-// finalize: one 64-lane block (a single wave) per particle; lanes sum the tiles' partial
+// finalize: one wave per particle (the first of its block); lanes sum the tiles' partial
 // accumulators (in tile order); lane 0 maps the mass's sums to the parameter gradient, lanes 1
 // and 2 the light profiles' (one pass over the code for both), the other lanes one shapelet
 // coefficient each; a vector whose log L or gradient is not finite gets log L = -inf and a zero
@@ -91,7 +127,7 @@ __device__ __forceinline__ FinalGrad finalize_particle(const SysDesc& s, int p) 
   const double logl = s.logl[p];
   const LightC L = lane == 1 ? c.lens : c.src;  // on its way while the sums are taken
   const double* acc = s.acc + (size_t)p * tiles * kNAcc;
-  for (int q = lane; q < ns; q += blockDim.x) {
+  for (int q = lane; q < ns; q += 64) {
     double v = 0.0;
     for (int t0 = 0; t0 < tiles; t0 += 16) {  // sixteen loads in flight, added in tile order
       double b[16];
@@ -102,7 +138,7 @@ __device__ __forceinline__ FinalGrad finalize_particle(const SysDesc& s, int p) 
     }
     a[q] = v;
   }
-  __syncthreads();
+  wave_sync();
   // the layout of gl.h: mass, lens light, source, shapelet scale and coefficients
   const int jl = mass_param_count(s.mass, s.shear), js = jl + (s.lens_light ? 7 : 0), jb = js + 7;
   const int M = nmax < 0 ? 0 : (nmax + 1) * (nmax + 2) / 2, d = jb + (nmax < 0 ? 0 : 1 + M);
@@ -149,12 +185,12 @@ __device__ __forceinline__ FinalGrad finalize_particle(const SysDesc& s, int p) 
     }
     mass_grad(c, ms, s.mass, s.shear, gr);
   }
-  __syncthreads();
+  wave_sync();
   int bad = 0;
-  for (int q = lane; q < d; q += blockDim.x) bad |= !isfinite(gr[q]);
+  for (int q = lane; q < d; q += 64) bad |= !isfinite(gr[q]);
   const bool ok = isfinite(logl) && !__any(bad);
   float* out = s.grad + (size_t)p * s.d;
-  for (int q = lane; q < d; q += blockDim.x) out[q] = ok ? gr[q] : 0.f;
+  for (int q = lane; q < d; q += 64) out[q] = ok ? gr[q] : 0.f;
   if (lane == 0 && !ok) s.logl[p] = -INFINITY;
   return {gr, ok, logl};
 }

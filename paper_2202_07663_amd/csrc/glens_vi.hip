@@ -107,8 +107,8 @@ __device__ __forceinline__ void draw_sample(const double* mu, const double* v, i
                                             float* s_z = nullptr) {
   __shared__ double s_l[kMaxParams * (kMaxParams + 1) / 2];
   const int nc = d * (d + 1) / 2;
-  for (int q = threadIdx.x; q < nc; q += kViThreads) s_l[q] = v[q];
-  for (int j = threadIdx.x; j < d; j += kViThreads) {
+  for (int q = threadIdx.x; q < nc; q += blockDim.x) s_l[q] = v[q];
+  for (int j = threadIdx.x; j < d; j += blockDim.x) {
     uint32_t w[4] = {uint32_t(s), uint32_t(j), uint32_t(k), tag};
     philox4x32_10(w, seed_lo, seed_hi);
     const double u1 = u01(w[0], w[1]), u2 = u01(w[2], w[3]);
@@ -117,12 +117,12 @@ __device__ __forceinline__ void draw_sample(const double* mu, const double* v, i
     if (eps_out) eps_out[size_t(s) * d + j] = e;
   }
   __syncthreads();  // the raw factor is in LDS
-  for (int i = threadIdx.x; i < d; i += kViThreads) {
+  for (int i = threadIdx.x; i < d; i += blockDim.x) {
     const int q = i * (i + 1) / 2 + i;
     s_l[q] = exp(s_l[q]);
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < d; i += kViThreads) {
+  for (int i = threadIdx.x; i < d; i += blockDim.x) {
     double zi = mu[i];
     const double* li = s_l + i * (i + 1) / 2;
     for (int j = 0; j <= i; ++j) zi += li[j] * s_eps[j];
@@ -133,13 +133,14 @@ __device__ __forceinline__ void draw_sample(const double* mu, const double* v, i
 
 // This iteration's draw of sample s = blockIdx.x, then the pipeline's decode of it
 // (prologue): one launch instead of two.
-__global__ void __launch_bounds__(kViThreads) vi_draw_decode_kernel(SysDesc s, ViArgs a) {
+template <int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) vi_draw_decode_kernel(SysDesc s, ViArgs a) {
   __shared__ double s_eps[kMaxParams];
   __shared__ float s_z[kMaxParams];
   draw_sample(a.x, a.x + a.d, a.d, blockIdx.x, a.k, kViDrawTag, a.seed_lo, a.seed_hi, s_eps,
               a.eps, a.z32, nullptr, s_z);
   __syncthreads();  // this sample's z is in LDS
-  prologue_particle(s, blockIdx.x, s_z);
+  prologue_particle<WAVES>(s, blockIdx.x, s_z);
 }
 
 // f = -log p~(z | I) and its gradient for one sample (terms summed in parameter order).
@@ -460,7 +461,10 @@ static int vi_iteration(gl_vi* v, hipStream_t st) {
   g.sys[0].grad = m->ws.grad;
   g.sys[0].mode = 2;
   // draw + decode, the pipeline without its first and last stages, finalize + objective
-  hipLaunchKernelGGL(vi_draw_decode_kernel, dim3(v->n), dim3(kViThreads), 0, st, g.sys[0], a);
+  const int waves = prologue_waves(v->n);
+  hipLaunchKernelGGL(waves == 1 ? vi_draw_decode_kernel<1>
+                                : vi_draw_decode_kernel<kPrologueMaxWaves>,
+                     dim3(v->n), dim3(64 * waves), 0, st, g.sys[0], a);
   if ((rc = vi_check_launch())) return rc;
   if ((rc = run_group(g, subpix_key(c), c.K, 2, st, nullptr, false, false))) return rc;
   hipLaunchKernelGGL(vi_finalize_objective_kernel, dim3(v->n), dim3(kViThreads), 0, st,
