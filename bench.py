@@ -76,7 +76,7 @@ def flops_model(H, W, k, K, nmax, lens_light, N_mean, sie=False):
 # includes: a change to any of them can change the profiled kernels' code
 KERNEL_SOURCES = ["paper_2202_07663_amd/csrc/" + f for f in (
     "glens_api.hip", "glens_kernels.h", "glens_particle.h", "glens_device.h",
-    "glens_fit_device.h", "glens_types.h", "glens_host.h")] + ["include/gl.h"]
+    "glens_fit_device.h", "glens_types.h", "glens_host.h", "glens_sums.h", "glens_chain.h")] + ["include/gl.h"]
 
 
 def csrc_hash() -> str:
@@ -646,7 +646,7 @@ def c4_bench(G, spec):
 def trace_summary(path, gap_split_s=0.1, min_dispatches=200):
     """Phases of a rocprofv3 kernel trace (the `*_kernel_trace.csv` of `--kernel-trace`), as
     markdown. A phase is a maximal run of this library's dispatches from one host thread with
-    one driver family (fit: fit_/adam_/logpost_ kernels; vi_; hmc_; the likelihood kernels
+    one driver family (fit: fit_/finalize_adam_/logpost_ kernels; vi_; hmc_; the likelihood kernels
     belong to the family around them) and no idle gap above gap_split_s. Per phase: span,
     busy (the union of all kernels' execution intervals in the span, over the span), the gaps
     between consecutive kernels, and the kernels taking the most time."""
@@ -664,7 +664,8 @@ def trace_summary(path, gap_split_s=0.1, min_dispatches=200):
         return name.split("glens::", 1)[1].split("(")[0].split("<")[0]
 
     def family(k):
-        for pre, fam in (("hmc_", "hmc"), ("vi_", "vi"), ("fit_", "fit"), ("adam_", "fit"),
+        for pre, fam in (("hmc_", "hmc"), ("vi_", "vi"), ("fit_", "fit"),
+                         ("finalize_adam_", "fit"),
                          ("logpost_", "fit")):
             if k.startswith(pre):
                 return fam

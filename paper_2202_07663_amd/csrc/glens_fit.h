@@ -36,7 +36,9 @@ void fit_buffers_layout(FitBuffers& fb, char* base, int P, int d);
 void fit_buffers_free(FitBuffers& fb);
 void attach_fit(SysDesc& s, const FitBuffers& fb, const FitParams& fp, const Workspace& ws);
 int launch_fit_init(Group& g, hipStream_t st);
-int launch_adam(Group& g, hipStream_t st);
+// Last kernel of a fit step (after run_group without its finalize); decode: with the prologue of
+// the next step.
+int launch_finalize_adam(Group& g, bool decode, hipStream_t st);
 int launch_logpost(Group& g, hipStream_t st);
 // The best particle of each system into its s.fit_out (after launch_logpost).
 int launch_fit_best(Group& g, hipStream_t st);

@@ -352,8 +352,8 @@ static void run_grouped(gl_server* s, const std::vector<Active*>& sys, int mode)
         attach_fit(g.sys[i], a->fb, a->req->fp, a->ws);
         g.sys[i].fit_out = a->out_dev;
       }
-      int rc = run_group(g, kv.first.first, kv.first.second, mode, s->stream);
-      if (!rc && mode == 2) rc = launch_adam(g, s->stream);
+      int rc = run_group(g, kv.first.first, kv.first.second, mode, s->stream, nullptr, true, false);
+      if (!rc && mode == 2) rc = launch_finalize_adam(g, false, s->stream);
       if (!rc && mode == 1) rc = launch_logpost(g, s->stream);
       if (!rc && mode == 1) rc = launch_fit_best(g, s->stream);
       if (rc)
