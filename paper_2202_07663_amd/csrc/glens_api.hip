@@ -354,7 +354,7 @@ SysDesc make_sys(const SystemData& sd, const Workspace& ws, int P, int tiles) {
   // choice depends on this system alone, so its results do not depend on its launch partners
   const MfmaGeom q = mfma_geom(c.H, c.W, c.K);
   const bool fits = sd.psf_mfma && q.T <= kMfmaMaxTiles &&
-                    size_t(mfma_lds_bytes(q, c.H, c.W)) <= kConvLdsMax;
+                    size_t(mfma_lds_bytes(q, c.H)) <= kConvLdsMax;
   s.conv_mfma = fits && s.bands == 1;
   // the adjoint half of a banded pass: from about 2e8 products the matrix cores win over the VALU
   // kernel's shorter latency (60 x 60, K = 21: 64 vectors, 1.0e8, 13.2 us against 10.2; 80 x 80, 300
@@ -543,7 +543,7 @@ static int launch_conv_mfma(Group& g, F take, hipStream_t st) {
     const SysDesc& s = g.sys[i];
     if (!take(s)) continue;
     const MfmaGeom q = mfma_geom(s.H, s.W, s.K);
-    lds = std::max(lds, size_t(mfma_lds_bytes(q, s.H, s.W)));
+    lds = std::max(lds, size_t(mfma_lds_bytes(q, s.H)));
     tiles = std::max(tiles, q.T);
   }
   set_blocks(g, [&](const SysDesc& s) { return take(s) ? blocks_conv(s) : 0; });

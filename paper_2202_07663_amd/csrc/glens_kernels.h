@@ -401,8 +401,8 @@ struct MfmaPass {
   int H, W, mode;
   float s2b, inv_gt, inv_k2;
   const float* obs;   // [H][W]
-  float* out;         // this particle's model image (mode 0) or sbar (adjoint pass)
-  float* seed;        // LDS [H][W]
+  float* out;         // this particle's model image (mode 0), or its seed and then sbar
+  float mx;           // largest seed magnitude of this lane's pixels
   double ll, c2;
 };
 
@@ -435,11 +435,50 @@ __device__ __forceinline__ void mfma_pixels(MfmaPass& P, int t0, const f32x4* ac
         const float chi = res * res * is2;
         P.c2 += double(chi);
         P.ll += double(chi + kLn2f * log2_f32(6.283185307179586f * s2));
-        const float sp = m > 0.f ? P.inv_gt : 0.f;
-        P.seed[px] = res * is2 + 0.5f * sp * (res * res * is2 * is2 - is2);
+        if (P.mode == 2) {
+          const float sp = m > 0.f ? P.inv_gt : 0.f;
+          const float sd = res * is2 + 0.5f * sp * (res * res * is2 * is2 - is2);
+          P.out[px] = sd;
+          P.mx = fmaxf(P.mx, fabsf(sd));
+        }
       }
     }
   }
+}
+
+// This lane's index, hidden from the compiler: what the image's load and the seed's compute from
+// it would otherwise be shared, and held in registers throughout the products between them.
+__device__ __forceinline__ int own_thread() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+// This lane's first kMfmaKeep pixels of src, all loads in flight.
+constexpr int kMfmaKeep = 16;
+__device__ __forceinline__ void mfma_load(const float* src, int HW, float* v) {
+  const int t = own_thread();
+#pragma unroll
+  for (int u = 0; u < kMfmaKeep; ++u) {
+    const int idx = t + u * int(blockDim.x);
+    v[u] = 0.f;
+    if (idx < HW) v[u] = src[idx];
+  }
+}
+
+// The interior of the padded LDS image: src 2^sx as two fp16 parts (v: mfma_load's).
+__device__ __forceinline__ void mfma_fill(const float* src, const float* v, int HW, int W, int C,
+                                          int sx, uint16_t* x, int pitch, int nel) {
+  const int t = own_thread();
+  PixelWalk w(W, t - int(threadIdx.x));
+  x += C * pitch + C;
+#pragma unroll
+  for (int u = 0; u < kMfmaKeep; ++u, w.next())
+    if (t + u * int(blockDim.x) < HW)
+      split2_f16(ldexpf(v[u], sx), x + w.i * pitch + w.j, nel);
+  for (int idx = t + kMfmaKeep * blockDim.x; idx < HW; idx += blockDim.x, w.next())
+    split2_f16(ldexpf(src[idx], sx), x + w.i * pitch + w.j, nel);
+  __syncthreads();
 }
 
 // G tiles of the wave: correlate, then the per-pixel step.
@@ -510,28 +549,23 @@ conv_mfma_kernel(Group g) {
   const int H = s.H, W = s.W, HW = H * W, K = s.K, C = (K - 1) / 2, mode = s.mode;
   const MfmaGeom q = mfma_geom(H, W, K);
   const int nel = q.Hq * q.pitch;  // fp16 per part (a multiple of 4)
-  float* seed = reinterpret_cast<float*>(xlds + 2 * nel);
   for (int i = threadIdx.x; i < nel / 4; i += blockDim.x)
     reinterpret_cast<uint4*>(xlds)[i] = make_uint4(0u, 0u, 0u, 0u);
   const bool adj_only = mode == 3;
-  // the image goes through the (still unused) seed area: one coalesced pass over global
-  // memory with many loads in flight, its largest magnitude found on the way
+  // a lane's pixels wait in registers (those of a large image past the sixteenth are read again,
+  // from L2) for the image's largest magnitude: in LDS they would take as much room again
   const float* src = (adj_only ? s.seed : s.m0) + (size_t)part * HW;
-  float mx = 0.f;
-#pragma unroll 8
-  for (int idx = threadIdx.x; idx < HW; idx += blockDim.x) {
-    const float v = src[idx];
-    seed[idx] = v;
-    mx = fmaxf(mx, fabsf(v));
-  }
+  float v[kMfmaKeep], mx = 0.f;
+  mfma_load(src, HW, v);
+#pragma unroll
+  for (int u = 0; u < kMfmaKeep; ++u) mx = fmaxf(mx, fabsf(v[u]));
+  for (int idx = threadIdx.x + kMfmaKeep * blockDim.x; idx < HW; idx += blockDim.x)
+    mx = fmaxf(mx, fabsf(src[idx]));
   // the block_max barriers also end the zero fill
   int sx = f16_scale_exp(block_max(mx, redf));
-  PixelWalk w0(W);
-  for (int idx = threadIdx.x; idx < HW; idx += blockDim.x, w0.next())
-    split2_f16(ldexpf(seed[idx], sx), xlds + (w0.i + C) * q.pitch + w0.j + C, nel);
-  __syncthreads();
+  mfma_fill(src, v, HW, W, C, sx, xlds, q.pitch, nel);
   MfmaPass P{q, int(blockDim.x) >> 6, -(sx + s.psf_mfma_exp), H, W, mode, s.s2b, s.inv_gt,
-             s.inv_k2, s.obs, (mode == 0 ? s.img : s.sbar) + (size_t)part * HW, seed, 0.0, 0.0};
+             s.inv_k2, s.obs, (mode == 0 ? s.img : s.sbar) + (size_t)part * HW, 0.f, 0.0, 0.0};
   if (adj_only) {
     if (threadIdx.x == 0) band_totals(s, part);
   } else {
@@ -539,23 +573,19 @@ conv_mfma_kernel(Group g) {
     if (mode == 0) return;
     const double tot = block_sum(P.ll, red);
     if (threadIdx.x == 0) {
-      const double v = -0.5 * tot;
-      s.logl[part] = isfinite(v) ? v : -INFINITY;
+      const double l = -0.5 * tot;
+      s.logl[part] = isfinite(l) ? l : -INFINITY;
     }
     if (s.chi2) {
       const double ctot = block_sum(P.c2, red);
       if (threadIdx.x == 0) s.chi2[part] = ctot;
     }
     if (mode != 2) return;
-    // every wave is done with the image (block_max below starts with a barrier): its interior
-    // takes the scaled seed
-    mx = 0.f;
-    for (int idx = threadIdx.x; idx < HW; idx += blockDim.x) mx = fmaxf(mx, fabsf(seed[idx]));
-    sx = f16_scale_exp(block_max(mx, redf));
-    PixelWalk w1(W);
-    for (int idx = threadIdx.x; idx < HW; idx += blockDim.x, w1.next())
-      split2_f16(ldexpf(seed[idx], sx), xlds + (w1.i + C) * q.pitch + w1.j + C, nel);
-    __syncthreads();
+    // every wave is done with the image and has written its part of the seed to sbar (block_max
+    // starts with a barrier): the image's interior takes the scaled seed
+    sx = f16_scale_exp(block_max(P.mx, redf));
+    mfma_load(P.out, HW, v);
+    mfma_fill(P.out, v, HW, W, C, sx, xlds, q.pitch, nel);
     P.unscale = -(sx + s.psf_mfma_exp);
   }
   // d logL / d m0 = correlation of the pixel seed with the (unflipped) PSF

@@ -235,13 +235,10 @@ __host__ __device__ inline MfmaGeom mfma_geom(int H, int W, int K) {
   q.pitch = ((q.TC - 1) * q.N + 32 + 3) & ~3;  // the last tile's 32-column window
   return q;
 }
-// LDS bytes of the pass: the padded image as two fp16 parts, and the FP32 pixel seed. The
-// tiles' last 16 - H % 16 rows (outputs past the image, never used) read up to 16 TR - H
-// rows past each part; past the second part those reads fall in the seed area, which is
-// made at least that long.
-__host__ __device__ inline int mfma_lds_bytes(const MfmaGeom& q, int H, int W) {
-  const int over = 2 * (q.TR * 16 - H) * q.pitch;
-  return 4 * q.Hq * q.pitch + (4 * H * W > over ? 4 * H * W : over);
+// LDS bytes of the pass: the padded image as two fp16 parts, and room for the rows that the
+// tiles' last 16 - H % 16 rows (outputs past the image, never used) read past each part.
+__host__ __device__ inline int mfma_lds_bytes(const MfmaGeom& q, int H) {
+  return 4 * q.Hq * q.pitch + 2 * (q.TR * 16 - H) * q.pitch;
 }
 
 constexpr int kConvRows = 8;  // output rows per lane in the VALU PSF passes
