@@ -261,7 +261,7 @@ __global__ void __launch_bounds__(kConvThreads) conv_kernel(Group g) {
 }
 
 // ------------------------------------------------------------------------------------------
-// PSF pass on matrix cores. One workgroup (4 waves) per particle. Each operand is scaled by a
+// PSF pass on matrix cores. One workgroup (4 to 16 waves) per particle. Each operand is scaled by a
 // power of two (exact) so that its largest magnitude lies in [2^14, 2^15), then split into two
 // fp16 parts, x = h + l with h = f16(x) and l = f16(x - h) (the difference is exact in FP32),
 // which represents it to about 2^-22 of itself: the scaled padded image sits in LDS as two
@@ -525,19 +525,22 @@ __device__ __forceinline__ void band_totals(const SysDesc& s, int part) {
   if (s.chi2) s.chi2[part] = ctot;
 }
 
-// One block per particle. Its size (launch_conv_mfma) is what fills a CU: 256 threads where four
-// blocks fit a CU's LDS (four waves per SIMD at the 128 registers allowed here), 512 or 1024
-// where the image leaves room for two or one, or where the batch has too few particles for
-// more; a tile's sums do not depend on the wave that takes it. 256 threads throughout against
-// this rule: 100 x 100 (103 KB of LDS: one block per CU), 2048 vectors 720 -> 443 us; 80 x 80,
-// 512 vectors (images) 37 -> 30 us; 60 x 60, 512 vectors 42 -> 37 us. At 60 x 60 and 4096 vectors
-// (193 us) the fill and split of the image take 35 us of the forward half's 119, the products 64
-// (matrix cores 34, row shifts and LDS reads of the new rows the rest: reloading either part of
-// the fragments from LDS instead of shifting it measured 278 us for the kernel, both 394), the
-// likelihood terms 22.
+// One block per particle. Its size (launch_conv_mfma) is what fills a CU: four waves per SIMD at
+// the 128 registers allowed here, from 256 threads where four blocks fit, 512 or 1024 where the
+// image leaves room in LDS for fewer or the batch has too few particles for more; a tile's sums
+// do not depend on the wave that takes it. LDS holds the image's two fp16 parts only: with the
+// pixels and the seed in FP32 beside them one block of 1024 threads fitted at 100 x 100, and its
+// phases followed each other with nothing to fill the gaps (2048 vectors: 720 us at 256 threads
+// throughout, 443 at 1024, 354 now with two blocks of 512); 80 x 80, 512 vectors (images) 37 ->
+// 30 -> 28 us; 60 x 60: 512 vectors 42 -> 37 -> 34.7 us, 4096 193 -> 183 us (log L only 115 ->
+// 104). Bound there by the fill and split of the image (about 35 us of the forward half) and by
+// the row shifts and the LDS reads of the new rows beside the products (matrix cores 34 us a
+// half): reloading either part of the fragments from LDS instead of shifting it measured 278 us
+// for the kernel, both 394; five waves per SIMD, at most four or three tiles a group, 180 against
+// 176 at the same clocks; four tiles a group at four waves 189.
 // mode 3: only the adjoint pass, from the seed that the banded forward kernel left in memory (and
-// log L from its bands' partial sums). Against the banded VALU
-// adjoint: 43 -> 33 us (80 x 80, 300 vectors), 52 -> 35 us (500).
+// log L from its bands' partial sums). Against the banded VALU adjoint: 43 -> 33 us (80 x 80, 300
+// vectors), 52 -> 33.6 us (500).
 __global__ void __launch_bounds__(kMfmaMaxThreads) __attribute__((amdgpu_waves_per_eu(4)))
 conv_mfma_kernel(Group g) {
   extern __shared__ __align__(16) uint16_t xlds[];
