@@ -210,11 +210,31 @@ static int choose_fwd_tiles(int P, int HW) {
   return std::max(1, std::min(want, maxt));
 }
 
-// Tiles of the batched calls' adjoint (at most choose_tiles, which sizes the accumulators). At
-// n_max = 8 a CU holds two blocks instead of three or more, and a tile's fixed part (the sums of
-// up to 77 values across its lanes) weighs as much as two sub-pixels: half as many tiles.
+// Tiles of the batched calls' adjoint (at most choose_tiles, which sizes the accumulators): the
+// fewest cycles by the blocks of a CU (up to six, those of the fullest one; beyond, their mean, as
+// CUs then even out) and one more for the last to end, each as long as its waves' pixels, 256 at a
+// time, and a fixed part (the sums across its lanes) of about 1.65 sub-pixels. Against as many
+// tiles as choose_tiles allows, between events: 60 x 60, n_max = 6, k = 2: 200 vectors 49 -> 44.5
+// us, 300 (5 tiles for 7) 61.3 -> 52.7, 512 (3 for 4) 79.4 -> 76.6; 80 x 80 without shapelets, 300
+// (5 for 7) 51.0 -> 46.3; 60 x 60, k = 1, 64: 15.6 -> 13.3. 700 vectors (three tiles, two: 104.8
+// -> 106.8) and 1024 (two, one: 144.4 -> 150.5) keep theirs. At n_max = 8 a CU holds two blocks
+// instead of three or more: half as many at most.
 static int choose_adj_tiles(const ModelCfg& c, int P, int tiles) {
-  return c.nmax >= 8 ? std::min(tiles, std::max(1, (1024 + P - 1) / P)) : tiles;
+  const int most = c.nmax >= 8 ? std::min(tiles, std::max(1, (1024 + P - 1) / P)) : tiles;
+  const double fixed = 1.65 / (c.k * c.k);
+  int best = 1;
+  double least = 0.0;
+  for (int t = 1; t <= most; ++t) {
+    const double mean = P * (t / 256.0), blocks = mean > 6.0 ? mean : std::ceil(mean);
+    // a block's last pixels leave some of its waves idle, for others to use in part
+    const int pixels = (c.H * c.W + t - 1) / t, turns = (pixels + kSubThreads - 1) / kSubThreads;
+    const double cost = (blocks + 1.0) * (0.5 * (turns + double(pixels) / kSubThreads) + fixed);
+    if (t == 1 || cost <= 1.01 * least) {
+      least = cost;
+      best = t;
+    }
+  }
+  return best;
 }
 
 int beta_per_particle(const ModelCfg& c) { return c.k * c.k * c.H * c.W; }
