@@ -398,9 +398,11 @@ SysDesc make_sys(const SystemData& sd, const Workspace& ws, int P, int tiles) {
   return s;
 }
 
-// LDS of a band's block: its image tile and the PSF's taps.
-static size_t band_lds_bytes(int band_rows, int W, int K) {
-  return sizeof(float) * (band_tile_floats(band_rows, W, K) + size_t(K) * ((K + 3) & ~3));
+// LDS of a band's block: its image tile, the PSF's taps, and the likelihood sums of each 64 of its
+// work items (strips times the lanes, split, that share one).
+static size_t band_lds_bytes(int band_rows, int W, int K, int split) {
+  return sizeof(float) * (band_tile_floats(band_rows, W, K) + size_t(K) * ((K + 3) & ~3)) +
+         2 * sizeof(double) * ((size_t(band_rows) / kConvRows * W * split + 63) / 64);
 }
 
 void conv_bands(int P, int H, int W, int K, int* bands, int* band_rows, int* split,
@@ -426,7 +428,7 @@ void conv_bands(int P, int H, int W, int K, int* bands, int* band_rows, int* spl
     for (int spb = (nstrip + kConvMaxBands - 1) / kConvMaxBands; spb < nstrip; ++spb) {
       const int nb = (nstrip + spb - 1) / spb, per_cu = (P * nb + 255) / 256;
       const double columns = (K + g - 1) / g, per_column = 4.0 * (kConvRows * K + kConvRows + K);
-      const int kb = int((band_lds_bytes(spb * kConvRows, W, K) + 512) / 2048) + 1;  // of 156 KB
+      const int kb = int((band_lds_bytes(spb * kConvRows, W, K, g) + 512) / 2048) + 1;  // of 156 KB
       const int fit = std::max(1, 78 / kb), w = waves(spb);
       const int turns = per_cu / fit * ((fit * w + 3) / 4) + (per_cu % fit * w + 3) / 4;
       const double cost = turns * columns * per_column +
@@ -566,8 +568,8 @@ static int conv_lds_limit(size_t lds) {
   return GL_OK;
 }
 
-// Static LDS of the matrix-core kernel (the reduction buffers), rounded up.
-constexpr int kMfmaStaticLds = 256;
+// Static LDS of the matrix-core kernel (the tiles' sums), rounded up.
+constexpr int kMfmaStaticLds = 1280;
 
 // Systems with take(s): block offsets are set here.
 template <class F>
@@ -614,7 +616,7 @@ static int launch_conv_band(int K, Group& g, int mode, bool chain, hipStream_t s
   for (int i = 0; i < g.nsys; ++i) {
     const SysDesc& s = g.sys[i];
     if (s.conv_mfma) continue;
-    lds = std::max(lds, band_lds_bytes(s.band_rows, s.W, K));
+    lds = std::max(lds, band_lds_bytes(s.band_rows, s.W, K, s.band_split));
     threads = std::max(threads, s.band_threads);
   }
   int rc = conv_lds_limit(lds);

@@ -115,7 +115,7 @@ int launch_chain_fwd(int key, const Group& g, hipStream_t st);
 int launch_chain_adj(int key, const Group& g, hipStream_t st);
 int launch_finalize(const Group& g, hipStream_t st);
 size_t conv_lds_bytes(int H, int W, int K, int mode);
-constexpr size_t kConvLdsMax = 160 * 1024 - 256;  // dynamic LDS allowed to the PSF kernels
+constexpr size_t kConvLdsMax = 160 * 1024 - 2048;  // dynamic LDS allowed to the PSF kernels
 
 // Block counts of one system per stage.
 inline int blocks_prologue(const SysDesc& s) { return s.P; }  // prologue, finalize

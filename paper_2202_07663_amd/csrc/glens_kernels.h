@@ -128,17 +128,15 @@ __attribute__((amdgpu_waves_per_eu(NMAX >= 7 ? 5 : 6))) subpix_fwd_kernel(Group 
 // per tap column it loads kConvRows + K - 1 values and does K * kConvRows FMAs with the taps
 // as wave-uniform (scalar) operands.
 // ------------------------------------------------------------------------------------------
-__device__ __forceinline__ double block_sum(double v, double* red) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
-  __syncthreads();
-  if (lane == 0) red[wave] = v;
-  __syncthreads();
-  double tot = 0.0;
-  if (threadIdx.x == 0)
-    for (int w = 0; w < nw; ++w) tot += red[w];
-  return tot;  // valid on lane 0 of wave 0
+// The likelihood sums are taken in an order that the block's size does not enter (a block of a
+// group takes the size that suits all its systems, and a system's log L is the same bits in any
+// company): the pixels in parts that one wave sums whatever the block (64 work items, or a tile
+// of the matrix-core pass), then the parts by this sum.
+// The total of the n parts in LDS, on every lane of the wave that calls it.
+__device__ __forceinline__ double parts_sum(const double* part, int n) {
+  double v = 0.0;
+  for (int m = threadIdx.x & 63; m < n; m += 64) v += part[m];
+  return wave_sum(v);
 }
 
 // The padded image sits in LDS column-major (column pitch Hs, odd so that the lanes of a wave,
@@ -170,7 +168,9 @@ __device__ __forceinline__ void correlate_strip(const float* __restrict__ buf, i
 template <int K>
 __global__ void __launch_bounds__(kConvThreads) conv_kernel(Group g) {
   extern __shared__ float lds[];
-  __shared__ double red[kConvThreads / 64];
+  // parts of 64 consecutive strips, as conv_band_kernel takes them
+  __shared__ double part_ll[kConvMaxStrips * kConvThreads / 64];
+  __shared__ double part_c2[kConvMaxStrips * kConvThreads / 64];
   const int si = find_sys(g, blockIdx.x);
   const SysDesc& s = g.sys[si];
   const int part = blockIdx.x - g.block0[si];
@@ -188,23 +188,27 @@ __global__ void __launch_bounds__(kConvThreads) conv_kernel(Group g) {
     A[(j + C) * Hs + i + C] = m0[idx];
   }
   __syncthreads();
-  double ll = 0.0, c2 = 0.0;
   const float* obs = s.obs;
+  const int nitem = nstrip * W;
   // A lane owns at most kConvMaxStrips strips (checked on the host); their pixel seeds stay
   // in registers until every lane has finished reading the image.
   float seed[kConvMaxStrips][R];
 #pragma unroll
   for (int t = 0; t < kConvMaxStrips; ++t) {
-    const int sidx = threadIdx.x + t * blockDim.x;
-    if (sidx >= nstrip * W) break;
+    const int base = (threadIdx.x & ~63) + t * kConvThreads;
+    if (base >= nitem) break;  // the whole wave
+    // lanes past the last strip repeat it, without a result
+    const int sidx = min(base + int(threadIdx.x & 63), nitem - 1);
+    const bool mine = sidx == base + int(threadIdx.x & 63);
     const int st = sidx / W, j = sidx - st * W, i0 = st * R;
     float acc[R];
     correlate_strip<K>(A, Hs, i0, j, s.psf_flip, acc);
+    double ll = 0.0, c2 = 0.0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int i = i0 + r;
       seed[t][r] = 0.f;
-      if (i >= H) continue;
+      if (i >= H || !mine) continue;
       const float m = acc[r];
       if (mode == 0) {
         s.img[(size_t)part * HW + i * W + j] = m;
@@ -220,19 +224,27 @@ __global__ void __launch_bounds__(kConvThreads) conv_kernel(Group g) {
         seed[t][r] = res * is2 + 0.5f * sp * (res * res * is2 * is2 - is2);
       }
     }
+    if (mode != 0) {
+      ll = wave_sum(ll);
+      c2 = wave_sum(c2);
+      if ((threadIdx.x & 63) == 0) {
+        part_ll[base / 64] = ll;
+        part_c2[base / 64] = c2;
+      }
+    }
   }
   if (mode == 0) return;
-  const double tot = block_sum(ll, red);
-  if (threadIdx.x == 0) {
-    const double v = -0.5 * tot;
-    s.logl[part] = isfinite(v) ? v : -INFINITY;
-  }
-  if (s.chi2) {
-    const double ctot = block_sum(c2, red);
-    if (threadIdx.x == 0) s.chi2[part] = ctot;
+  __syncthreads();  // the parts are there, and every lane is done with the image
+  if (threadIdx.x < 64) {
+    const int np = (nitem + 63) / 64;
+    const double v = -0.5 * parts_sum(part_ll, np), ctot = parts_sum(part_c2, np);
+    if (threadIdx.x == 0) {
+      s.logl[part] = isfinite(v) ? v : -INFINITY;
+      if (s.chi2) s.chi2[part] = ctot;
+    }
   }
   if (mode != 2) return;
-  __syncthreads();  // every lane is done with the image: overwrite its interior with the seed
+  // overwrite the image's interior with the seed
 #pragma unroll
   for (int t = 0; t < kConvMaxStrips; ++t) {
     const int sidx = threadIdx.x + t * blockDim.x;
@@ -394,6 +406,7 @@ __device__ __forceinline__ void mfma_tiles(const uint16_t* x, int nel, const Mfm
 // Per-pixel state of the matrix-core PSF kernel. The launch descriptor's fields are copied
 // here once: read through the descriptor (a dynamically indexed kernel argument) they were
 // loaded again for every pixel.
+constexpr int kMfmaGroup = 5;  // most tiles that a wave takes at a time (mfma_pass)
 struct MfmaPass {
   const MfmaGeom& q;
   int nw;             // waves of the block
@@ -403,7 +416,7 @@ struct MfmaPass {
   const float* obs;   // [H][W]
   float* out;         // this particle's model image (mode 0), or its seed and then sbar
   float mx;           // largest seed magnitude of this lane's pixels
-  double ll, c2;
+  double ll[kMfmaGroup], c2[kMfmaGroup];  // this lane's likelihood sums of each tile of a group
 };
 
 // Pixels of tiles t0 + v nw, v < G: element r of acc[v] is pixel (i0 + r, j).
@@ -433,8 +446,8 @@ __device__ __forceinline__ void mfma_pixels(MfmaPass& P, int t0, const f32x4* ac
         const float res = P.obs[px] - m;
         const float is2 = rcp_f32(s2);
         const float chi = res * res * is2;
-        P.c2 += double(chi);
-        P.ll += double(chi + kLn2f * log2_f32(6.283185307179586f * s2));
+        P.c2[v] += double(chi);
+        P.ll[v] += double(chi + kLn2f * log2_f32(6.283185307179586f * s2));
         if (P.mode == 2) {
           const float sp = m > 0.f ? P.inv_gt : 0.f;
           const float sd = res * is2 + 0.5f * sp * (res * res * is2 * is2 - is2);
@@ -491,22 +504,37 @@ __device__ __forceinline__ void mfma_group(MfmaPass& P, const uint16_t* x, int n
 }
 
 // The wave's tiles wave, wave + nw, .. in groups of at most five, as even as possible: a group's
-// products hide the latency of the PSF fragment loads only when it has several tiles.
+// products hide the latency of the PSF fragment loads only when it has several tiles. The forward
+// pass of a likelihood leaves its sums of each tile in tile_ll and, if not null, tile_c2 (LDS).
 template <bool ADJ>
 __device__ __forceinline__ void mfma_pass(MfmaPass& P, const uint16_t* x, int nel,
-                                          const uint4* tab, int K) {
+                                          const uint4* tab, int K, double* tile_ll = nullptr,
+                                          double* tile_c2 = nullptr) {
   // wave-uniform: kept in scalar registers
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ntw = wave < P.q.T ? (P.q.T - wave + P.nw - 1) / P.nw : 0;
-  const int ng = (ntw + 4) / 5;
+  const int ng = (ntw + kMfmaGroup - 1) / kMfmaGroup;
   for (int gi = 0, u = 0; gi < ng; ++gi) {
     const int n = (ntw - u + ng - gi - 1) / (ng - gi), t0 = wave + u * P.nw;
+    if (!ADJ)
+#pragma unroll
+      for (int v = 0; v < kMfmaGroup; ++v) P.ll[v] = P.c2[v] = 0.0;
     switch (n) {
       case 1: mfma_group<1, ADJ>(P, x, nel, tab, K, t0); break;
       case 2: mfma_group<2, ADJ>(P, x, nel, tab, K, t0); break;
       case 3: mfma_group<3, ADJ>(P, x, nel, tab, K, t0); break;
       case 4: mfma_group<4, ADJ>(P, x, nel, tab, K, t0); break;
       default: mfma_group<5, ADJ>(P, x, nel, tab, K, t0); break;
+    }
+    if (!ADJ && P.mode != 0) {  // one copy of the sums' code for every group size
+      const int lane = threadIdx.x & 63;  // lane 8 v holds tile v's
+      const bool holds = lane % 8 == 0 && lane / 8 < n;
+      const double tl = wave_sums_f64<kMfmaGroup>(P.ll);
+      if (holds) tile_ll[t0 + lane / 8 * P.nw] = tl;
+      if (tile_c2) {
+        const double tc = wave_sums_f64<kMfmaGroup>(P.c2);
+        if (holds) tile_c2[t0 + lane / 8 * P.nw] = tc;
+      }
     }
     u += n;
   }
@@ -544,7 +572,7 @@ __device__ __forceinline__ void band_totals(const SysDesc& s, int part) {
 __global__ void __launch_bounds__(kMfmaMaxThreads) __attribute__((amdgpu_waves_per_eu(4)))
 conv_mfma_kernel(Group g) {
   extern __shared__ __align__(16) uint16_t xlds[];
-  __shared__ double red[kMfmaMaxThreads / 64];
+  __shared__ double tile_ll[kMfmaMaxTiles], tile_c2[kMfmaMaxTiles];
   __shared__ float redf[kMfmaMaxThreads / 64];
   const int si = find_sys(g, blockIdx.x);
   const SysDesc& s = g.sys[si];
@@ -568,24 +596,24 @@ conv_mfma_kernel(Group g) {
   int sx = f16_scale_exp(block_max(mx, redf));
   mfma_fill(src, v, HW, W, C, sx, xlds, q.pitch, nel);
   MfmaPass P{q, int(blockDim.x) >> 6, -(sx + s.psf_mfma_exp), H, W, mode, s.s2b, s.inv_gt,
-             s.inv_k2, s.obs, (mode == 0 ? s.img : s.sbar) + (size_t)part * HW, 0.f, 0.0, 0.0};
+             s.inv_k2, s.obs, (mode == 0 ? s.img : s.sbar) + (size_t)part * HW, 0.f, {}, {}};
   if (adj_only) {
     if (threadIdx.x == 0) band_totals(s, part);
   } else {
-    mfma_pass<false>(P, xlds, nel, s.psf_mfma, K);
+    mfma_pass<false>(P, xlds, nel, s.psf_mfma, K, tile_ll, s.chi2 ? tile_c2 : nullptr);
     if (mode == 0) return;
-    const double tot = block_sum(P.ll, red);
-    if (threadIdx.x == 0) {
-      const double l = -0.5 * tot;
-      s.logl[part] = isfinite(l) ? l : -INFINITY;
-    }
-    if (s.chi2) {
-      const double ctot = block_sum(P.c2, red);
-      if (threadIdx.x == 0) s.chi2[part] = ctot;
+    __syncthreads();  // the tiles' sums are there
+    if (threadIdx.x < 64) {
+      const double l = -0.5 * parts_sum(tile_ll, q.T);
+      if (threadIdx.x == 0) s.logl[part] = isfinite(l) ? l : -INFINITY;
+      if (s.chi2) {
+        const double ctot = parts_sum(tile_c2, q.T);
+        if (threadIdx.x == 0) s.chi2[part] = ctot;
+      }
     }
     if (mode != 2) return;
-    // every wave is done with the image and has written its part of the seed to sbar (block_max
-    // starts with a barrier): the image's interior takes the scaled seed
+    // every wave is done with the image and has written its part of the seed to sbar (the barrier
+    // above): the image's interior takes the scaled seed
     sx = f16_scale_exp(block_max(P.mx, redf));
     mfma_load(P.out, HW, v);
     mfma_fill(P.out, v, HW, W, C, sx, xlds, q.pitch, nel);
@@ -711,7 +739,6 @@ __device__ __forceinline__ void band_strip(const float* __restrict__ A,
 template <int K>
 __global__ void __launch_bounds__(kBandMaxThreads) conv_band_kernel(Group g) {
   extern __shared__ __align__(16) float lds[];
-  __shared__ double red[kBandMaxThreads / 64];
   const int si = find_sys(g, blockIdx.x);
   const SysDesc& s = g.sys[si];
   const Band b = band_of(s, blockIdx.x - g.block0[si], K);
@@ -719,21 +746,25 @@ __global__ void __launch_bounds__(kBandMaxThreads) conv_band_kernel(Group g) {
   const int W = s.W, HW = s.H * W, mode = s.mode;
   float* T = lds + band_tile_floats(s.band_rows, W, K);
   load_band<K>(s.m0 + (size_t)b.part * HW, s.psf_flip, s, b, lds, T);
-  double ll = 0.0, c2 = 0.0;
-  // work items (strip, column, PSF-column share); the G lanes of one strip are adjacent, and
-  // blockDim and the item count are multiples of G, so they run the loop together
+  // work items (strip, column, PSF-column share); the G lanes of one strip are adjacent, and 64
+  // and the item count are multiples of G, so they run the loop together. Lanes past the last
+  // item repeat it, without a result.
   const int G = s.band_split, gs = G >> 1;  // G = 1, 2, 4: log2 G = G / 2
-  for (int sidx = threadIdx.x; sidx < b.nsr * W * G; sidx += blockDim.x) {
-    const int item = sidx >> gs, g0 = sidx & (G - 1);
+  const int nitem = b.nsr * W * G, lane = threadIdx.x & 63, np = (nitem + 63) / 64;
+  double* parts = reinterpret_cast<double*>(T + K * tap_pitch<K>());  // log L terms, then chi^2
+  for (int base = threadIdx.x & ~63; base < nitem; base += blockDim.x) {
+    const int sidx = min(base + lane, nitem - 1);
+    const int item = sidx >> gs, g0 = (base + lane) & (G - 1);
     const int st = item / W, j = item - st * W, i0 = st * R;
     float acc[R];
     band_strip<K>(lds, T, b.Hs, i0, j, acc, g0, G);
     split_sum(acc, G);
-    if (g0 != 0) continue;
+    const bool mine = g0 == 0 && base + lane < nitem;
+    double ll = 0.0, c2 = 0.0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int i = b.r0 + i0 + r;
-      if (i >= b.r1) break;
+      if (i >= b.r1 || !mine) break;
       const float m = acc[r];
       const size_t o = (size_t)b.part * HW + i * W + j;
       if (mode == 0) {
@@ -752,14 +783,24 @@ __global__ void __launch_bounds__(kBandMaxThreads) conv_band_kernel(Group g) {
         s.seed[o] = res * is2 + 0.5f * sp * (res * res * is2 * is2 - is2);
       }
     }
+    if (mode != 0) {
+      ll = wave_sum(ll);
+      c2 = wave_sum(c2);
+      if (lane == 0) {
+        parts[base / 64] = ll;
+        parts[np + base / 64] = c2;
+      }
+    }
   }
   if (mode == 0) return;
-  const double tot = block_sum(ll, red);
-  const double ctot = block_sum(c2, red);
-  if (threadIdx.x == 0) {
-    double* lp = s.lpart + ((size_t)b.part * kConvMaxBands + b.band) * 2;
-    lp[0] = tot;
-    lp[1] = ctot;
+  __syncthreads();  // the parts are there
+  if (threadIdx.x < 64) {
+    const double tot = parts_sum(parts, np), ctot = parts_sum(parts + np, np);
+    if (threadIdx.x == 0) {
+      double* lp = s.lpart + ((size_t)b.part * kConvMaxBands + b.band) * 2;
+      lp[0] = tot;
+      lp[1] = ctot;
+    }
   }
 }
 

@@ -45,6 +45,13 @@ __device__ __forceinline__ void stage_series(const PConst& c, float scale, float
   __syncthreads();
 }
 
+// Sum over a wave's lanes, on every lane (the pairing of wave_sums).
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
 constexpr int halved(int n) { return n > 1 ? n / 2 : 1; }
 
 // One step of the transposed butterfly below for a lane holding NV values (all indices
@@ -100,6 +107,26 @@ __device__ __forceinline__ void wave_sums(const float* acc, double* out) {
     constexpr int per = 64 / N;
     if (lane % per == 0 && lane / per < NS) out[lane / per] = v[0];
   }
+}
+
+// Wave sums of the NS per-lane values v (at most 8), value q in the lanes from 64 q / N on: the
+// transposed butterfly again, with the pairing of wave_sum for each value.
+template <int NS>
+__device__ __forceinline__ double wave_sums_f64(const double* v) {
+  static_assert(NS <= 8, "three steps halve the values");
+  constexpr int N = NS == 1 ? 1 : (NS == 2 ? 2 : (NS <= 4 ? 4 : 8));
+  const int lane = threadIdx.x & 63;
+  double w[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) w[i] = i < NS ? v[i] : 0.0;
+  constexpr int n1 = halved(N), n2 = halved(n1), n3 = halved(n2);
+  wave_sum_step<N>(w, 32, lane);
+  wave_sum_step<n1>(w, 16, lane);
+  wave_sum_step<n2>(w, 8, lane);
+  wave_sum_step<n3>(w, 4, lane);
+  wave_sum_step<1>(w, 2, lane);
+  wave_sum_step<1>(w, 1, lane);
+  return w[0];
 }
 
 // FP64 sums of the block's accumulators, across each wave, then across the waves, to out[0 .. NS).
