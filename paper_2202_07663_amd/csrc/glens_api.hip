@@ -455,7 +455,7 @@ using GroupKernel = void (*)(Group);
 
 template <int MASS, int LL, int NMAX>
 struct SubKernels {
-  static constexpr GroupKernel fwd = subpix_fwd_kernel<LL, NMAX>;
+  static constexpr GroupKernel fwd = subpix_fwd_kernel<MASS, LL, NMAX>;
   static constexpr GroupKernel adj = subpix_adj_kernel<MASS, LL, NMAX>;
 };
 

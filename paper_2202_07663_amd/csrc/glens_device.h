@@ -2,7 +2,7 @@
 //
 // Forward model (Gu et al. 2022, Sec. 2.1.1): deflection by an elliptical power law (EPL,
 // deflection through the Gauss hypergeometric series of Tessore & Metcalf 2015) or its
-// slope-2 case the SIE (closed form), plus external shear; ray trace beta = x - alpha;
+// slope-2 case the SIE, plus external shear; ray trace beta = x - alpha;
 // elliptical Sersic source plus Cartesian shapelets at beta; elliptical Sersic lens light
 // at x.
 //
@@ -162,9 +162,10 @@ GL_HD void decode_mass(const float* th, int mass, int shear, MassC& c) {
   c.mj22 = float(j22);
   // series: terms until the tail bound |eps|^N / (1 - |eps|) drops below the tolerance
   // (FP64 value series), and below the looser derivative tolerance (adjoint series)
+  c.sie_closed = (mass == 0 && eabs >= kSieClosedMin) ? 1 : 0;
   int nt = 1, ntd = 1;
   if (eabs > 1e-30) {
-    nt = int(ceil(log(kSeriesTol * (1.0 - eabs)) / log(eabs)));
+    nt = int(ceil(log((c.sie_closed ? kSeriesTolSie : kSeriesTol) * (1.0 - eabs)) / log(eabs)));
     nt = nt < 1 ? 1 : (nt > kMaxTerms ? kMaxTerms : nt);
     ntd = int(ceil(log(kSeriesTolDeriv * (1.0 - eabs)) / log(eabs))) + 1;
     ntd = ntd < 1 ? 1 : (ntd > nt ? nt : ntd);
@@ -172,7 +173,6 @@ GL_HD void decode_mass(const float* th, int mass, int shear, MassC& c) {
   c.nterms = nt;
   c.nterms_d = ntd;
   // SIE closed form: s = sqrt(conj(eps)), S_1(X) = atan(s u) / (s u), u = w / |w|
-  c.sie_closed = (mass == 0 && eabs >= kSieClosedMin) ? 1 : 0;
   if (c.sie_closed) {
     const double ang = -0.5 * atan2(e2, e1), rs = sqrt(eabs);
     c.sr = rs * cos(ang);
@@ -413,6 +413,12 @@ __device__ __forceinline__ double rcp_f64(double x) {
   return fma(fma(-x, r, 1.0), r, r);
 }
 __host__ inline double rcp_f64(double x) { return 1.0 / x; }
+// 1 / sqrt(x): hardware estimate and one Newton step, as rcp
+__device__ __forceinline__ double rsq_f64(double x) {
+  const double r = __builtin_amdgcn_rsq(x);
+  return fma(0.5 * r, fma(-x * r, r, 1.0), r);
+}
+__host__ inline double rsq_f64(double x) { return 1.0 / sqrt(x); }
 
 // Single-precision hardware transcendentals in base 2 (about 1 ulp), for normal, finite
 // arguments; callers fold log2(e) into their per-particle constants.
@@ -495,9 +501,12 @@ GL_HD float cdot(Cx g, Cx v) { return g.r * v.r + g.i * v.i; }  // real dot prod
 
 // EPL / SIE deflection plus shear at image position x, in FP64: beta - x_s with beta = x - alpha
 // - alpha_ext. The row's y enters through RayRow, so that w takes one FMA per component. Both
-// masses take the series (the SIE is t = 1, its power table's A = B / |w|): the closed form of
-// the SIE, a complex arctangent, costs three times the instructions of the longest series kept
-// (|eps| = 0.6) and is kept for the sampler's launches only (glens_chain.h).
+// masses take the series. The SIE is t = 1: A = B / |w| takes a reciprocal square root instead of
+// the power table, and the series goes on to kSeriesTolSie (its c_n = 1 / (2n + 1) leave a tail
+// below 1e-12 of alpha also at the longest, |eps| = 0.6), so that an offset beta - x_s of 1e-6
+// arcsec still has FP32 precision, as with the closed form. That, a complex arctangent, costs
+// three times the instructions of the longest series kept and is left to the sampler's launches
+// (glens_chain.h).
 // The radius is not floored here (|w|^2 is above its floor and |X| = |eps|): at the particle's
 // floored sub-pixel, if it has one, the result is not finite or not used, and the caller takes
 // the prologue's c.fl_s instead.
@@ -512,13 +521,15 @@ __device__ __forceinline__ RayRow ray_row(const PConst& c, double y) {
   return {fma(-c.e2, zi, -c.ome1 * c.xc), fma(c.ope1, zi, c.e2 * c.xc), fma(-c.g2, y, -c.sxs),
           fma(c.opg1, y, -c.sys)};
 }
+template <int MASS>
 __device__ __forceinline__ void ray_trace(const PConst& c, const double* __restrict__ cs,
                                           const double* __restrict__ pw, double yy, double x,
                                           const RayRow& row, float& sdx, float& sdy) {
   const double wr = fma(c.ome1, x, row.wr), wi = fma(-c.e2, x, row.wi);
   const double wi2 = wi * wi;
   const double w2 = fma(wr, wr, wi2);
-  const double inv = rcp_f64(w2);
+  const double rw = MASS == 0 ? rsq_f64(w2) : 0.0;
+  const double inv = MASS == 0 ? rw * rw : rcp_f64(w2);
   const double pr = fma(wr, wr, -wi2), pi = wr * wi;  // w^2 = pr + 2 i pi
   const double Xr = inv * fma(c.e1, pr, c.e22 * pi), Xi = inv * fma(c.e12, pi, -c.e2 * pr);
   // The coefficients are real, so the series is evaluated at the complex point y = -X by
@@ -537,7 +548,7 @@ __device__ __forceinline__ void ray_trace(const PConst& c, const double* __restr
     b1 = fma(r2, b2, fma(-yy, b1, cs[n0]));
   }
   const double Sr = fma(Xr, b2, b1), Sm = Xi * b2;  // S = Sr - i Sm
-  const double A = pow_from_table(pw, w2);
+  const double A = MASS == 0 ? c.bmass * rw : pow_from_table(pw, w2);
   const double tr = fma(wr, Sr, wi * Sm), ti = fma(wi, Sr, -wr * Sm);
   // beta - x_s = x - alpha - alpha_ext - x_s
   sdx = float(fma(-A, tr, fma(x, c.omg1, row.ax)));

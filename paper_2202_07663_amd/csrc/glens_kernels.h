@@ -37,12 +37,12 @@ __global__ void __launch_bounds__(64 * WAVES) prologue_kernel(Group g) {
 // ------------------------------------------------------------------------------------------
 // sub-pixel forward: lanes own pixels, loop over the k x k sub-pixels
 // ------------------------------------------------------------------------------------------
-// LL: lens light on (1) or off (0); NMAX: shapelet order (-1: none). Every system of one launch
-// has the same (LL, NMAX).
+// MASS: 0 SIE, 1 EPL; LL: lens light on (1) or off (0); NMAX: shapelet order (-1: none). Every
+// system of one launch has the same (MASS, LL, NMAX).
 // The pixels [p0, p1) of one particle's model image. The restrict qualifiers tell the compiler
 // that the image stores do not write the particle's constants, which then stay scalar loads.
 // beta (or null): where beta - x_s of each sub-pixel is kept for the adjoint, [k^2][H][W].
-template <int LL, int NMAX>
+template <int MASS, int LL, int NMAX>
 __device__ __forceinline__ void forward_pixels(const SysDesc& s, const PConst* __restrict__ c,
                                                const double* s_pw, float* __restrict__ out,
                                                float2* __restrict__ beta, int p0, int p1) {
@@ -74,7 +74,7 @@ __device__ __forceinline__ void forward_pixels(const SysDesc& s, const PConst* _
       double x = xj;
       for (int b = 0; b < k; ++b, x += dxs, bp += HW * sizeof(float2)) {
         float sdx, sdy;
-        ray_trace(*c, c->c, s_pw, yy, x, row, sdx, sdy);
+        ray_trace<MASS>(*c, c->c, s_pw, yy, x, row, sdx, sdy);
         if (a * k + b == fl_sub && pix == c->fl_pix) {  // the first test is wave-uniform
           sdx = c->fl_s[0];
           sdy = c->fl_s[1];
@@ -100,7 +100,7 @@ __device__ __forceinline__ void forward_pixels(const SysDesc& s, const PConst* _
 // left to itself the compiler takes 83 registers and five waves. Measured: 312 -> 291 us (60 x 60,
 // 4096 vectors, log L), 149 -> 76 us (53 x 37 SIE + lens light, k = 3, 777 vectors; its closed
 // form needed 116 registers and two library transcendentals per sub-pixel).
-template <int LL, int NMAX>
+template <int MASS, int LL, int NMAX>
 __global__ void __launch_bounds__(kSubThreads)
 __attribute__((amdgpu_waves_per_eu(NMAX >= 7 ? 5 : 6))) subpix_fwd_kernel(Group g) {
   const int si = find_sys(g, blockIdx.x);
@@ -108,18 +108,20 @@ __attribute__((amdgpu_waves_per_eu(NMAX >= 7 ? 5 : 6))) subpix_fwd_kernel(Group 
   const int lb = blockIdx.x - g.block0[si];
   const int part = lb / s.ftiles, tile = lb - part * s.ftiles;
   const PConst& c = s.pc[part];
-  // the power tables in LDS (lanes read entries of their own); the value series' coefficients
-  // stay in the particle's constants, read through the scalar cache: uniform over the
+  // the EPL's power tables in LDS (lanes read entries of their own); the value series'
+  // coefficients stay in the particle's constants, read through the scalar cache: uniform over the
   // workgroup, they enter the series' FMAs as scalar operands
-  __shared__ double s_pw[kPowExp + kPowSeg * 8];
-  for (int i = threadIdx.x; i < kPowExp + kPowSeg * 8; i += blockDim.x) s_pw[i] = c.pw[i];
-  __syncthreads();
+  __shared__ double s_pw[MASS == 1 ? kPowExp + kPowSeg * 8 : 1];
+  if (MASS == 1) {
+    for (int i = threadIdx.x; i < kPowExp + kPowSeg * 8; i += blockDim.x) s_pw[i] = c.pw[i];
+    __syncthreads();
+  }
   const int HW = s.H * s.W;
   const int p0 = tile * s.fpix_per_tile;
   const int p1 = min(HW, p0 + s.fpix_per_tile);
   float2* beta = s.mode == 2 && s.beta ? s.beta + (size_t)part * s.k * s.k * HW : nullptr;
   float* out = s.m0 + (size_t)part * HW;
-  forward_pixels<LL, NMAX>(s, &c, s_pw, out, beta, p0, p1);
+  forward_pixels<MASS, LL, NMAX>(s, &c, s_pw, out, beta, p0, p1);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -24,8 +24,11 @@ constexpr double kR2FloorD = 1e-12;
 constexpr double kMinPitch = 1e-4;
 constexpr float kMassEpsMax = 0.6f;
 constexpr float kLightEpsMax = 0.9f;
-constexpr float kSieClosedMin = 0.1f;  // SIE closed form for |eps| >= this, series below
-constexpr double kSeriesTol = 1e-10;   // EPL series truncation, relative (far below FP32)
+// The sampler's ray trace takes the SIE's closed form for |eps| >= this, the series below; the
+// other calls sum the series with more terms there (kSeriesTolSie).
+constexpr float kSieClosedMin = 0.1f;
+constexpr double kSeriesTol = 1e-10;   // series truncation, relative (far below FP32)
+constexpr double kSeriesTolSie = 1e-12;  // the SIE's where its closed form would serve
 constexpr double kSeriesTolDeriv = 1e-7;  // truncation of the derivative series (adjoint)
 // dS/dX from S by the first-order identity of the series for |eps| >= this (its cancellation
 // costs 1e-10 / |eps| relative: below 1e-8 here); the derivative series below
@@ -78,7 +81,7 @@ struct LightC {
 struct MassC {
   int nterms;          // EPL / SIE series terms
   int nterms_d;        // terms of the derivative series (adjoint), <= nterms
-  int sie_closed;      // SIE: 1 = closed form, 0 = series (the sampler's ray trace)
+  int sie_closed;      // SIE, |eps| >= kSieClosedMin (the sampler's ray trace: closed form)
   // FP64 part: positions and the deflection are evaluated in double precision, because the
   // ray-traced source offset beta - x_s must be accurate to far below the FP32 resolution
   // of arcsecond-scale coordinates near a cuspy source.
