@@ -136,7 +136,9 @@ GL_HD void decode_mass(const float* th, int mass, int shear, MassC& c) {
   c.e2 = e2;
   c.ee = ee;
   c.tlnb = t * log(B);
-  c.bmass = B;
+  // theta_E < 0: the SIE from kSieClosedMin on has an image (alpha is odd in B there) and no
+  // gradient; elsewhere the power B^t does not exist and log L is -inf
+  c.bmass = B < 0.0 && !(mass == 0 && eabs >= kSieClosedMin) ? NAN : B;
   c.w2floor = 1e-12 * (1.0 + eabs) * (1.0 + eabs);
   c.epsabs = eabs;
   c.theta_e = float(theta_e);
@@ -149,7 +151,7 @@ GL_HD void decode_mass(const float* th, int mass, int shear, MassC& c) {
   c.w2floorf = float(c.w2floor);
   c.tlnb2 = float(c.tlnb * 1.4426950408889634);
   c.l2b2 = float(2.0 * log(B) * 1.4426950408889634);
-  c.hb = float(0.5 * B);
+  c.hb = B < 0.0 ? NAN : float(0.5 * B);
   c.tf = float(t);
   c.lnb = float(log(B));
   c.xcf = float(c.xc);

@@ -1,11 +1,11 @@
 """The SIE's ray trace where its closed form would serve (|eps| >= 0.1): as exact as that form next
-to the source's centre."""
+to the source's centre, and defined for a negative Einstein radius."""
 import numpy as np
 import pytest
 
 import oracle
 import synth
-from helpers import oracle_model
+from helpers import assert_logl_close, oracle_model
 
 pytestmark = pytest.mark.gpu
 
@@ -59,3 +59,31 @@ def test_gradient_next_to_the_source_centre():
     err = np.linalg.norm((g - ref)[:, 11:13], axis=1) / np.linalg.norm(ref[:, 11:13], axis=1)
     print("max", err.max(), "median", np.median(err), flush=True)
     assert err.max() <= 30 * 6e-8
+
+
+def test_negative_einstein_radius():
+    """alpha is odd in theta_E. The gradient calls have never taken it, nor has the series below
+    |eps| = 0.1: log L is -inf there, with a zero gradient."""
+    import torch
+    import paper_2202_07663_amd as G
+    spec = _spec(24)
+    th, _ = _vectors(spec, 40, 9)
+    th[:, 0] = -np.abs(th[:, 0])
+    th[20:, 1:3] *= 0.09 / np.hypot(th[20:, 1], th[20:, 2])[:, None]
+    obs = np.zeros((24, 24), np.float32)
+    m, t = G.Model.from_spec(spec, obs), torch.from_numpy(th).cuda()
+    pix = float(np.float32(spec.pix))
+    c = (np.arange(24) - 11.5) * pix
+    y, x = (v.ravel() for v in np.meshgrid(c, c, indexing="ij"))
+    b = np.stack([_land(th[:20], a, d) for a, d in zip(x, y)], 1) - th[:20, None, 11:13]  # [20, 576, 2]
+    R, n, i0 = (th[:20, k, None].astype(np.float64) for k in (7, 8, 13))
+    ref = i0 * np.exp(-(1.9992 * n - 0.3271) * ((np.hypot(b[..., 0], b[..., 1]) / R) ** (1 / n) - 1))
+    img = m.simulate(t).cpu().numpy().reshape(40, -1)
+    assert np.all(np.isfinite(img[:20])) and not np.any(np.isfinite(img[20:]))
+    assert (np.abs(img[:20] - ref).max(1) / ref.max(1)).max() < 2e-5
+    ll = m.loglik(t).cpu().numpy()
+    s2 = float(np.float32(spec.sigma_bkg)) ** 2 + ref / float(np.float32(spec.t_exp))
+    assert_logl_close(ll[:20], -0.5 * (ref ** 2 / s2 + np.log(2 * np.pi * s2)).sum(1))
+    assert np.all(ll[20:] == -np.inf)
+    ll, g = m.loglik_grad(t)
+    assert bool((ll == -np.inf).all()) and not bool(g.any())
