@@ -145,13 +145,29 @@ GL_HD void decode_mass(const float* th, int mass, int shear, MassC& c) {
   c.hp = float(1.0 - 0.5 * t);
   c.hm = float(-0.5 * t);
   c.omt = float(1.0 - t);
+  const bool sx = eabs < kSxClosedMin;
+  c.icr = sx ? 1.0 : e1 * (1.0 - ee);
+  c.ici = sx ? 0.0 : -e2 * (1.0 - ee);
+  const double oo = 1.0 / (1.0 - ee);
+  c.sr1 = float((c.icr * (1.0 + e1) - c.ici * e2) * oo);
+  c.sr2 = float((c.icr * e2 - c.ici * (1.0 - e1)) * oo);
+  c.si1 = float((c.icr * e2 + c.ici * (1.0 + e1)) * oo);
+  c.si2 = float((c.icr * (1.0 - e1) + c.ici * e2) * oo);
+  c.ka = sx ? 0.f : float(-t * ee);
   c.e1f = float(e1);
   c.e2f = float(e2);
   c.eef = float(ee);
   c.w2floorf = float(c.w2floor);
   c.tlnb2 = float(c.tlnb * 1.4426950408889634);
-  c.l2b2 = float(2.0 * log(B) * 1.4426950408889634);
   c.hb = B < 0.0 ? NAN : float(0.5 * B);
+  // kappa is in proportion to constants rounded to FP32 (EPL: 2^(hm log2|w|^2 + tlnb2), on the
+  // ring |w| = B), and hq is rounded with them
+  const double l2b2 = 2.0 * log(B) * 1.4426950408889634;
+  c.l2b2 = float(l2b2);
+  const double sc = mass == 1 ? 1.0 + 0.6931471805599453 * (c.hm * l2b2 + c.tlnb2) : c.hb / (0.5 * B);
+  const double hq = c.hp * (1.0 - ee) * sc;
+  c.hq = float(hq);
+  c.hql = float(hq - c.hq);
   c.tf = float(t);
   c.lnb = float(log(B));
   c.xcf = float(c.xc);
@@ -570,10 +586,23 @@ __device__ __forceinline__ void ray_trace(const PConst& c, const double* __restr
 //     X ((t/2) S + X S_X)), the derivative of the closed form, into (1 - t/2) A;
 //   * alpha has degree 1 - t in z, so z alpha_z + conj(z) alpha_zb = (1 - t) alpha gives
 //       Gamma = alpha_zb = ((1 - t) alpha - kappa z) z / |z|^2   (SIE: -kappa z^2 / |z|^2);
-//   * d alpha / d(eps, conj(eps)) are combinations of kappa, Gamma, z and alpha by
-//     per-particle constants, formed from sums over the sub-pixels in mass_sums. One of them is
-//     divided by |eps|, at a relative cost of 1e-7 / |eps|: for |eps| < kSxClosedMin its sum
-//     (slots A_M_WR, A_M_WI) is taken from the derivative series instead;
+//   * aw = d alpha/dw and awb = d alpha/d conj(w) at fixed eps solve kappa = aw - conj(eps) awb,
+//     Gamma = awb - eps aw, so (1 - |eps|^2)(aw, awb) = (kappa + conj(eps) Gamma, Gamma + eps
+//     kappa). With U = gb aw, V = gb awb, Sp = Re U + Re V and Dm = Im U - Im V,
+//       g . d alpha/dx = (1 - e1) Sp + e2 Dm, g . d alpha/dy = -(1 + e1) Dm - e2 Sp,
+//     which are had from kappa and Gamma directly and solved for Sp and Dm;
+//   * d alpha/d eps = -tfac conj(eps) alpha - conj(z) aw,
+//     d alpha/d conj(eps) = -tfac eps alpha - z awb + W, tfac = t / (2 (1 - |eps|^2)),
+//     W = A w u2 dS/dX (A depends on |eps|^2, X on conj(eps); w aw = alpha (1 - t/2) + A w X S_X):
+//       g . d alpha/de1 = -2 tfac e1 Re(gb alpha) - Re(z) Sp - Im(z) Dm + Re(gb W),
+//       g . d alpha/de2 = -2 tfac e2 Re(gb alpha) + Re(z) Dm - Im(z) Sp + Im(gb W),
+//     W from conj(eps) W = w aw - (1 - t/2) alpha. Its terms cancel like |eps|, and what is left
+//     against the others: taken per sub-pixel (of sums over a tile, the differences had twice the
+//     error), everything times ic = conj(eps) (1 - |eps|^2), which the sums are divided by at the
+//     end. With g.(d alpha/d eps_1) + i g.(d alpha/d eps_2) =: G and S = Sp - i Dm,
+//       ic G = gb (w (kappa + conj(eps) Gamma) - (1 - t/2)(1 - |eps|^2) alpha) - z (ic S)
+//              - t |eps|^2 Re(gb alpha).
+//     For |eps| < kSxClosedMin W is summed by the derivative series instead, and ic = 1;
 //   * d alpha / dt = alpha (ln B - ln|w|^2 / 2) + A w S_t by its series (EPL), with the
 //     coefficients times -2 / ln 2 so that the sum runs over base-2 logarithms.
 // Series are summed by synthetic division at y = -X (ray_trace), four terms per trip (the length
@@ -594,7 +623,7 @@ __device__ __forceinline__ void mass_adjoint(const PConst& c, const float* __res
     z2 = fmaxf(z2, kR2Floor);
   }
   const float iz2 = rcp_f32(z2);
-  const float gar = fmaf(g.i, ai, g.r * ar);  // Re(gb alpha)
+  const float ga = fmaf(g.i, ai, g.r * ar);  // Re(gb alpha)
   float kap, A = 0.f, l2w2 = 0.f, Gr, Gi;
   if (MASS == 1) {
     l2w2 = log2_f32(w2);
@@ -614,55 +643,58 @@ __device__ __forceinline__ void mass_adjoint(const PConst& c, const float* __res
   const float kr = kap * g.r, ki = kap * g.i;
   const float hxr = fmaf(g.i, Gi, fmaf(g.r, Gr, kr));
   const float hxi = fmaf(-g.i, Gr, fmaf(g.r, Gi, ki));
-  acc[A_M_GAR] += gar;
-  acc[A_M_GAI] = fmaf(-g.i, ar, fmaf(g.r, ai, acc[A_M_GAI]));
+  acc[A_M_ALPHA] += ga;
   acc[A_M_X] += hxr;
   acc[A_M_Y] += hxi;
-  acc[A_M_KRR] = fmaf(kr, zr, acc[A_M_KRR]);
-  acc[A_M_KRI] = fmaf(kr, zi, acc[A_M_KRI]);
-  acc[A_M_KIR] = fmaf(ki, zr, acc[A_M_KIR]);
-  acc[A_M_KII] = fmaf(ki, zi, acc[A_M_KII]);
-  acc[A_M_HZR] = fmaf(-hxi, zi, fmaf(hxr, zr, acc[A_M_HZR]));
-  acc[A_M_HZI] = fmaf(hxi, zr, fmaf(hxr, zi, acc[A_M_HZI]));
   acc[A_M_G1] = fmaf(-g.i, zi, fmaf(g.r, zr, acc[A_M_G1]));
   acc[A_M_G2] = fmaf(g.i, zr, fmaf(g.r, zi, acc[A_M_G2]));
   const bool sx = GENERAL && c.epsabs < kSxClosedMin;
-  if (MASS == 1 || sx) {
+  const float sr = fmaf(c.sr1, hxr, c.sr2 * hxi), si = fmaf(c.si1, hxr, c.si2 * hxi);
+  float u2r = 0.f, u2i = 0.f, Xr = 0.f, Xi = 0.f;
+  if (MASS == 1 || GENERAL) {
     const float iw2 = rcp_f32(w2);
-    const float u2r = fmaf(-wi, wi, wr2) * iw2, u2i = 2.0f * wr * wi * iw2;
-    const float Xr = e1 * u2r + e2 * u2i, Xi = e1 * u2i - e2 * u2r;
-    const float r2 = -2.0f * Xr, yy = c.eef;
-    const float gwr = fmaf(g.i, wi, g.r * wr), gwi = fmaf(g.r, wi, -g.i * wr);  // gb w
-    const int nd4 = (c.nterms_d + 3) & ~3;
-    if (MASS == 1) {
-      float t1 = 0.f, t2 = 0.f;
-      for (int n0 = nd4 - 4; n0 >= 0; n0 -= 4) {
+    u2r = fmaf(-wi, wi, wr2) * iw2;
+    u2i = 2.0f * wr * wi * iw2;
+    Xr = e1 * u2r + e2 * u2i;
+    Xi = e1 * u2i - e2 * u2r;
+  }
+  const float r2 = -2.0f * Xr, yy = c.eef;
+  const float gwr = fmaf(g.i, wi, g.r * wr), gwi = fmaf(g.r, wi, -g.i * wr);  // gb w
+  const int nd4 = (c.nterms_d + 3) & ~3;
+  if (MASS == 1) {
+    float t1 = 0.f, t2 = 0.f;
+    for (int n0 = nd4 - 4; n0 >= 0; n0 -= 4) {
 #pragma unroll
-        for (int q = 3; q >= 0; --q) {
-          const float t0 = fmaf(r2, t1, fmaf(-yy, t2, dcs[n0 + q]));
-          t2 = t1;
-          t1 = t0;
-        }
+      for (int q = 3; q >= 0; --q) {
+        const float t0 = fmaf(r2, t1, fmaf(-yy, t2, dcs[n0 + q]));
+        t2 = t1;
+        t1 = t0;
       }
-      // Re(gb w S_t), S_t = t1 + conj(X) t2
-      const float p = fmaf(gwr, t1, t2 * fmaf(gwi, Xi, gwr * Xr));
-      acc[A_M_T] = fmaf(A, p, fmaf(l2w2 - c.l2b2, gar, acc[A_M_T]));
     }
-    if (sx) {
-      float d1 = 0.f, d2 = 0.f;
-      for (int n0 = nd4 - 4; n0 >= 0; n0 -= 4) {
+    // Re(gb w S_t), S_t = t1 + conj(X) t2
+    const float p = fmaf(gwr, t1, t2 * fmaf(gwi, Xi, gwr * Xr));
+    acc[A_M_T] = fmaf(A, p, fmaf(l2w2 - c.l2b2, ga, acc[A_M_T]));
+  }
+  if (sx) {  // gb W
+    float d1 = 0.f, d2 = 0.f;
+    for (int n0 = nd4 - 4; n0 >= 0; n0 -= 4) {
 #pragma unroll
-        for (int q = 3; q >= 0; --q) {
-          const float d0 = fmaf(r2, d1, fmaf(-yy, d2, ncs[n0 + q]));
-          d2 = d1;
-          d1 = d0;
-        }
+      for (int q = 3; q >= 0; --q) {
+        const float d0 = fmaf(r2, d1, fmaf(-yy, d2, ncs[n0 + q]));
+        d2 = d1;
+        d1 = d0;
       }
-      const Cx SX = {-fmaf(Xr, d2, d1), Xi * d2};  // dS/dX = -dS/dy
-      const Cx W = cmul(Cx{A * gwr, A * gwi}, cmul(Cx{u2r, u2i}, SX));
-      acc[A_M_WR] += W.r;
-      acc[A_M_WI] += W.i;
     }
+    const Cx SX = {-fmaf(Xr, d2, d1), Xi * d2};  // dS/dX = -dS/dy
+    const Cx W = cmul(Cx{A * gwr, A * gwi}, cmul(Cx{u2r, u2i}, SX));
+    acc[A_M_E1] += fmaf(zi, si, fmaf(-zr, sr, W.r));
+    acc[A_M_E2] += fmaf(-zi, sr, fmaf(-zr, si, W.i));
+  } else {
+    const float tr = fmaf(e1, Gr, fmaf(e2, Gi, kap)), ti = fmaf(e1, Gi, -e2 * Gr);
+    const float qr = fmaf(wr, tr, fmaf(-wi, ti, fmaf(-c.hql, ar, -c.hq * ar)));
+    const float qi = fmaf(wr, ti, fmaf(wi, tr, fmaf(-c.hql, ai, -c.hq * ai)));
+    acc[A_M_E1] += fmaf(zi, si, fmaf(-zr, sr, fmaf(c.ka, ga, fmaf(g.i, qi, g.r * qr))));
+    acc[A_M_E2] += fmaf(-zi, sr, fmaf(-zr, si, fmaf(-g.i, qr, g.r * qi)));
   }
 }
 
@@ -866,45 +898,20 @@ GL_HD void light_grad(const LightC& L, const double* a, bool offsets, float* g) 
   g[6] = float(a[L_E]);                                                        // I0
 }
 
-// Sums of g . d alpha/d(theta) over the sub-pixels, from the accumulators a (mass_adjoint):
-// gb alpha, and with K = kappa gb, H = gb Gamma and Hx = H + kappa g the sums
-//   S1 = K z, S2 = K conj(z), S3 = H z = Hx z - kappa g z,
-//   S4 = H conj(z) = (1 - t) gb alpha - K z  (Gamma conj(z) = (1 - t) alpha - kappa z).
-// aw = d alpha/dw and awb = d alpha/d conj(w) at fixed eps solve kappa = aw - conj(eps) awb,
-// Gamma = awb - eps aw, so (1 - |eps|^2)(aw, awb) = (kappa + conj(eps) Gamma, Gamma + eps kappa);
-//   d alpha/d eps = -tfac conj(eps) alpha - conj(z) aw,
-//   d alpha/d conj(eps) = -tfac eps alpha - z awb + (w aw - (1 - t/2) alpha) / conj(eps),
-// tfac = t / (2 (1 - |eps|^2)); the last term is A w u2 dS/dX (A depends on |eps|^2, X on
-// conj(eps); w aw = alpha (1 - t/2) + A w X S_X).
+// Sums of g . d alpha/d(theta) over the sub-pixels, from the accumulators a (mass_adjoint).
 struct MassSums {
   double alpha, t, e1, e2, x, y, g1, g2;
 };
 GL_HD MassSums mass_sums(const PConst& c, const double* a) {
   MassSums m;
   const double e1 = c.e1, e2 = c.e2, ee = e1 * e1 + e2 * e2, oo = 1.0 / (1.0 - ee);
-  const double gar = a[A_M_GAR], gai = a[A_M_GAI];
-  const double s1r = a[A_M_KRR] + a[A_M_KII], s1i = a[A_M_KRI] - a[A_M_KIR];
-  const double s2r = a[A_M_KRR] - a[A_M_KII], s2i = -a[A_M_KRI] - a[A_M_KIR];
-  const double s3r = a[A_M_HZR] - s2r, s3i = a[A_M_HZI] + s2i;  // kappa g z = conj(S2)
-  const double omt = 1.0 - c.t;
-  const double s4r = omt * gar - s1r, s4i = omt * gai - s1i;
-  // sums of gb conj(z) aw, gb z awb, gb z aw
-  const double zbr = (s2r + e1 * s4r + e2 * s4i) * oo, zbi = (s2i + e1 * s4i - e2 * s4r) * oo;
-  const double zwr = (s3r + e1 * s1r - e2 * s1i) * oo, zwi = (s3i + e1 * s1i + e2 * s1r) * oo;
-  const double zar = (s1r + e1 * s3r + e2 * s3i) * oo, zai = (s1i + e1 * s3i - e2 * s3r) * oo;
-  double wr = a[A_M_WR], wi = a[A_M_WI];
-  if (!(c.epsabs < kSxClosedMin)) {  // (sum gb w aw - (1 - t/2) gb alpha) / conj(eps)
-    const double hp = 1.0 - 0.5 * c.t;
-    const double nr = zar - (e1 * zbr - e2 * zbi) - hp * gar;
-    const double ni = zai - (e1 * zbi + e2 * zbr) - hp * gai;
-    wr = (nr * e1 - ni * e2) / ee;
-    wi = (ni * e1 + nr * e2) / ee;
-  }
-  const double k = -c.t * oo;  // -2 tfac
-  m.alpha = gar;
+  const double ii = 1.0 / (c.icr * c.icr + c.ici * c.ici);
+  // -2 tfac Re(gb alpha), where its part is not in the sums
+  const double k = c.epsabs < kSxClosedMin ? -c.t * oo * a[A_M_ALPHA] : 0.0;
+  m.alpha = a[A_M_ALPHA];
   m.t = -0.5 * kLn2 * a[A_M_T];
-  m.e1 = k * e1 * gar - zbr - zwr + wr;
-  m.e2 = k * e2 * gar + zbi - zwi + wi;
+  m.e1 = (a[A_M_E1] * c.icr + a[A_M_E2] * c.ici) * ii + k * e1;
+  m.e2 = (a[A_M_E2] * c.icr - a[A_M_E1] * c.ici) * ii + k * e2;
   m.x = a[A_M_X];
   m.y = a[A_M_Y];
   const double gr = a[A_SRC + L_DX], gi = a[A_SRC + L_DY];  // sum g

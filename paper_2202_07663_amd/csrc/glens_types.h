@@ -16,7 +16,7 @@ constexpr int kPowDeg = 6;
 constexpr int kMaxNmax = 8;        // shapelet order
 constexpr int kMaxShp = (kMaxNmax + 1) * (kMaxNmax + 2) / 2;  // 45
 constexpr int kMaxParams = 68;
-constexpr int kNAcc = 80;          // adjoint accumulator slots per (particle, tile)
+constexpr int kNAcc = 72;          // adjoint accumulator slots per (particle, tile)
 constexpr float kR2Floor = 1e-12f; // arcsec^2 floor on elliptical radii
 constexpr double kR2FloorD = 1e-12;
 // Smallest sub-pixel pitch (arcsec): a mass radius below the floor needs the sub-pixel within
@@ -30,27 +30,23 @@ constexpr float kSieClosedMin = 0.1f;
 constexpr double kSeriesTol = 1e-10;   // series truncation, relative (far below FP32)
 constexpr double kSeriesTolSie = 1e-12;  // the SIE's where its closed form would serve
 constexpr double kSeriesTolDeriv = 1e-7;  // truncation of the derivative series (adjoint)
-// dS/dX from S by the first-order identity of the series for |eps| >= this (its cancellation
-// costs 1e-10 / |eps| relative: below 1e-8 here); the derivative series below
+// conj(eps) W of the adjoint (mass_adjoint) from alpha and its derivatives for |eps| >= this (they
+// cancel like |eps|, at a relative cost of 1e-7 / |eps| per sub-pixel); the derivative series below
 constexpr double kSxClosedMin = 0.02;
 
-// Accumulator slots of the adjoint (per particle, summed over sub-pixels). Only sums that need a
-// value of their own per sub-pixel are kept: with g the weighted light gradient, gb = conj(g),
-// kappa = d alpha / dz (real), Gamma = d alpha / d conj(z) and Hx = gb Gamma + kappa g, every
-// other sum of the mass gradient is a combination of these by per-particle constants
-// (mass_sums), and so are those of the light profiles (light_grad).
+// Accumulator slots of the adjoint (per particle, summed over sub-pixels), with g the weighted
+// light gradient and gb = conj(g). Sums of which one is a combination by per-particle constants
+// are not kept twice (mass_sums, light_grad), where that combination does not cancel: a sum of
+// differences is taken difference by difference.
 enum AccSlot {
-  A_M_GAR = 0, A_M_GAI = 1,  // sum gb alpha
-  A_M_T = 2,      // sum g.(d alpha / d t) / (-ln 2 / 2)
-  A_M_X = 3, A_M_Y = 4,      // sum Hx = g.(d alpha / dx) + i g.(d alpha / dy)
-  A_M_KRR = 5, A_M_KRI = 6,  // sum kappa Re(g) z
-  A_M_KIR = 7, A_M_KII = 8,  // sum kappa Im(g) z
-  A_M_HZR = 9, A_M_HZI = 10, // sum Hx z
-  A_M_G1 = 11, A_M_G2 = 12,  // sum g.(zr, -zi), g.(zi, zr)
-  A_M_WR = 13, A_M_WI = 14,  // sum gb A w u2 dS/dX (|eps| < kSxClosedMin only)
-  A_SRC = 15,     // 8 slots, see LightSlot; the centre slots also collect the shapelet gradient
-  A_SHP_BETA = 23,
-  A_SHP_C = 24,   // one slot per shapelet coefficient, then the lens light's 8 (lens_slot)
+  A_M_ALPHA = 0,  // sum g.alpha
+  A_M_T = 1,      // sum g.(d alpha / d t) / (-ln 2 / 2)
+  A_M_E1 = 2, A_M_E2 = 3,  // sum g.(d alpha / d eps_1) + i g.(d alpha / d eps_2), times MassC::ic
+  A_M_X = 4, A_M_Y = 5,    // sum g.(d alpha / dx), g.(d alpha / dy)
+  A_M_G1 = 6, A_M_G2 = 7,  // sum g.(zr, -zi), g.(zi, zr)
+  A_SRC = 8,      // 8 slots, see LightSlot; the centre slots also collect the shapelet gradient
+  A_SHP_BETA = 16,
+  A_SHP_C = 17,   // one slot per shapelet coefficient, then the lens light's 8 (lens_slot)
 };
 // First slot of the lens light, which comes last so that systems without one do not sum it.
 __host__ __device__ constexpr int lens_slot(int nmax) {
@@ -99,6 +95,11 @@ struct MassC {
   float theta_e;       // Einstein radius
   float hp, hm;        // 1 - t/2, -t/2
   float omt;           // 1 - t
+  double icr, ici;     // ic: conj(eps) (1 - |eps|^2) for |eps| >= kSxClosedMin, else 1
+  float sr1, sr2, si1, si2;  // (S', -D') = the 2 x 2 matrix (sr; si) of g.(d alpha / d(x, y))
+  float ka;            // -2 tfac |eps|^2 (1 - |eps|^2), or 0 where ic = 1
+  float hq, hql;       // (1 - t/2)(1 - |eps|^2) in two parts, and rounded as kappa is: an error
+                       // that all sub-pixels share would be divided by |eps| (mass_adjoint)
   float w2floorf;      // R^2 floor on |w|^2 (FP32)
   float tlnb2;         // t log2 B
   float l2b2;          // 2 log2 B
