@@ -712,7 +712,8 @@ GL_HD float sersic_fwd(const LightC& L, float dx, float dy) {
 // half gradient (px, py) = (qa dx + qb dy / 2, qb dx / 2 + qc dy) of R^2 = dx px + dy py,
 // dI/d(dx, dy) = s (px, py), s = I0 (-b_n / n) E rho / R^2. The sums over the ellipticity terms
 // are combinations of s dx^2, s dx dy and s dy^2 (s R^2 itself is one), so only these three are
-// kept, and I0 multiplies the sums instead of their terms.
+// kept, and I0 multiplies the sums instead of their terms. E rho - E is kept as a sum of its own:
+// of the two sums, the difference had up to 1.4 times its error at rho near 1.
 __device__ __forceinline__ float sersic_adj(const LightC& L, float dx, float dy, float px,
                                             float py, float sb, float* acc) {
   const float q0 = fmaf(dx, px, dy * py);
@@ -723,6 +724,7 @@ __device__ __forceinline__ float sersic_adj(const LightC& L, float dx, float dy,
   const float s = q0 < kR2Floor ? 0.0f : sEr * L.kqi * rcp_f32(q);
   acc[L_E] += sE;
   acc[L_RHO] += sEr;
+  acc[L_RHO1] += sEr - sE;
   acc[L_RHOLN] = fmaf(sEr, l2rho, acc[L_RHOLN]);
   const float sx = s * dx, sy = s * dy;
   acc[L_XX] = fmaf(sx, dx, acc[L_XX]);
@@ -884,7 +886,7 @@ GL_HD void source_light_grad(const PConst& c, int nmax, double sdx, double sdy, 
 GL_HD void light_grad(const LightC& L, const double* a, bool offsets, float* g) {
   const double i0 = L.i0, bnn = L.bn / double(L.n);
   g[0] = float(i0 * a[L_RHO] * (bnn / L.re));                                  // R_eff
-  g[1] = float(i0 * (bnn * kLn2 * a[L_RHOLN] - 1.9992 * (a[L_RHO] - a[L_E])));  // n
+  g[1] = float(i0 * (bnn * kLn2 * a[L_RHOLN] - 1.9992 * a[L_RHO1]));          // n
   // sum s R^2 and the two eccentricity sums
   const double xx = a[L_XX], xy = a[L_XY], yy = a[L_YY];
   const double r2q = xx + yy + L.qa * xx + L.qb * xy + L.qc * yy;

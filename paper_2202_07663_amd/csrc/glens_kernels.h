@@ -915,7 +915,7 @@ template <int MASS, int LL, int NMAX>
 __global__ void __launch_bounds__(kSubThreads)
 __attribute__((amdgpu_waves_per_eu(NMAX >= 8 ? 2 : 3)))
 subpix_adj_kernel(Group g) {
-  constexpr int NS = lens_slot(NMAX) + (LL ? 8 : 0);
+  constexpr int NS = lens_slot(NMAX) + (LL ? kLightSlots : 0);
   __shared__ double red[kSubThreads / 64][NS];
   const int si = find_sys(g, blockIdx.x);
   const SysDesc& s = g.sys[si];

@@ -122,7 +122,7 @@ __device__ __forceinline__ FinalGrad finalize_particle(const SysDesc& s, int p) 
   const int lens0 = CHAIN ? int(chain::A_LENS) : lens_slot(nmax);
   const int src0 = CHAIN ? int(chain::A_SRC) : int(A_SRC);
   const int ns = CHAIN ? int(chain::A_SHP_BETA) + (nmax < 0 ? 0 : 1 + (nmax + 1) * (nmax + 2) / 2)
-                       : lens0 + (s.lens_light ? 8 : 0);
+                       : lens0 + (s.lens_light ? kLightSlots : 0);
   const int tiles = CHAIN ? s.tiles : s.adj_tiles;
   const double logl = s.logl[p];
   const LightC L = lane == 1 ? c.lens : c.src;  // on its way while the sums are taken

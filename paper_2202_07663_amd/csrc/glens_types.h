@@ -44,18 +44,22 @@ enum AccSlot {
   A_M_E1 = 2, A_M_E2 = 3,  // sum g.(d alpha / d eps_1) + i g.(d alpha / d eps_2), times MassC::ic
   A_M_X = 4, A_M_Y = 5,    // sum g.(d alpha / dx), g.(d alpha / dy)
   A_M_G1 = 6, A_M_G2 = 7,  // sum g.(zr, -zi), g.(zi, zr)
-  A_SRC = 8,      // 8 slots, see LightSlot; the centre slots also collect the shapelet gradient
-  A_SHP_BETA = 16,
-  A_SHP_C = 17,   // one slot per shapelet coefficient, then the lens light's 8 (lens_slot)
+  A_SRC = 8,      // 9 slots, see LightSlot; the centre slots also collect the shapelet gradient
+  A_SHP_BETA = 17,
+  A_SHP_C = 18,   // one slot per shapelet coefficient, then the lens light's 9 (lens_slot)
 };
 // First slot of the lens light, which comes last so that systems without one do not sum it.
 __host__ __device__ constexpr int lens_slot(int nmax) {
   return nmax < 0 ? int(A_SHP_BETA) : int(A_SHP_C) + (nmax + 1) * (nmax + 2) / 2;
 }
 // Sums of one light profile, with E = I / I0, rho = (R / R_eff)^(1/n) and s the weighted
-// 2 dI/dR^2: E, E rho, E rho log2(rho) (all weighted), s dx^2, s dx dy, s dy^2; L_DX, L_DY: the source's gradient in the offset, the lens light's s dx, s dy.
-enum LightSlot { L_E = 0, L_RHO = 1, L_RHOLN = 2, L_XX = 3, L_XY = 4, L_YY = 5, L_DX = 6, L_DY = 7 };
-static_assert(lens_slot(kMaxNmax) + 8 <= kNAcc, "accumulator slots");
+// 2 dI/dR^2: E, E rho, E rho log2(rho) (all weighted), s dx^2, s dx dy, s dy^2; L_DX, L_DY: the
+// source's gradient in the offset, the lens light's s dx, s dy; E (rho - 1).
+enum LightSlot {
+  L_E = 0, L_RHO = 1, L_RHOLN = 2, L_XX = 3, L_XY = 4, L_YY = 5, L_DX = 6, L_DY = 7, L_RHO1 = 8
+};
+constexpr int kLightSlots = 9;
+static_assert(lens_slot(kMaxNmax) + kLightSlots <= kNAcc, "accumulator slots");
 
 // Elliptical Sersic constants of one particle.
 struct LightC {

@@ -45,3 +45,10 @@ def test_mass_ellipticity():
     r = _ratio(cases, ["e1", "e2"])
     print("ratio", r)
     assert r <= 1.2
+
+
+def test_sersic_index():
+    cases = [(epl, nmax, 0.1) for epl, nmax in ((True, -1), (False, -1), (True, 3), (False, 2))]
+    r = _ratio(cases, ["l_n", "s_n"], n=192)
+    print("ratio", r)
+    assert r <= 1.1
