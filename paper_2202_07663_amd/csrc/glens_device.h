@@ -937,11 +937,16 @@ GL_HD void mass_grad(const MassC& c, const MassSums& m, int mass, int shear, flo
   }
 }
 
+// 1 / beta as the adjoint's sub-pixels have it (shapelet_adj): its FP32 rounding enters their
+// Gaussians and these factors alike, and the two errors partly cancel (they do in G / beta at r =
+// beta).
+GL_HD double adjoint_inv_beta(const PConst& c) { return 0.7071067811865476 * c.rt2_ib; }
+
 // Gradient component of shapelet coefficient q (0 <= q < M).
 GL_HD float shapelet_coef_grad(const PConst& c, const double* a, int q) {
   int n1, n2;
   shapelet_orders(q, n1, n2);
-  return float(a[A_SHP_C + q] * (double(c.inv_beta) * kInvSqrtPi) *
+  return float(a[A_SHP_C + q] * (adjoint_inv_beta(c) * kInvSqrtPi) *
                (hermite_scale(n1, n2) * double(kHeScale[n1 + n2])));
 }
 

@@ -154,7 +154,7 @@ __device__ __forceinline__ FinalGrad finalize_particle(const SysDesc& s, int p) 
     gr[jb + 1 + q] = CHAIN ? chain::shapelet_coef_grad(c, a, q) : shapelet_coef_grad(c, a, q);
   if (lane == 0) {
     if (nmax >= 0)
-      gr[jb] = CHAIN ? float(a[chain::A_SHP_BETA]) : float(-double(c.inv_beta) * a[A_SHP_BETA]);
+      gr[jb] = CHAIN ? float(a[chain::A_SHP_BETA]) : float(-adjoint_inv_beta(c) * a[A_SHP_BETA]);
     MassSums ms = CHAIN ? chain::mass_sums(a) : mass_sums(c, a);
     if (c.fl_i >= 0) {
       // the floored sub-pixel: g = sbar d(source light)/d(beta) there (FP64), contracted with
