@@ -448,6 +448,10 @@ __device__ __forceinline__ float rcp_f32(float x) { return __builtin_amdgcn_rcpf
 __host__ inline float rcp_f32(float x) { return 1.0f / x; }
 __device__ __forceinline__ float rsq_f32(float x) { return __builtin_amdgcn_rsqf(x); }
 __host__ inline float rsq_f32(float x) { return 1.0f / sqrtf(x); }
+__device__ __forceinline__ float clamp_f32(float x, float most) {
+  return __builtin_amdgcn_fmed3f(x, -most, most);
+}
+__host__ inline float clamp_f32(float x, float most) { return fminf(fmaxf(x, -most), most); }
 constexpr float kLn2f = 0.69314718055994531f;
 constexpr float kLog2e = 1.44269504088896341f;
 
@@ -795,7 +799,9 @@ template <int NMAX>
 GL_HD void shapelet_adj(const PConst& c, float sdx, float sdy, const float* he, float sb,
                         float* acc, float& gbx, float& gby) {
   const float ib = c.rt2_ib;
-  const float x = sdx * ib, y = sdy * ib;
+  // sg is zero from |y| = 32 on (e^-256), and stays so: the y-polynomials, which do not carry it,
+  // would overflow where the forward pass's g_n(v) are still finite (NaN from 0 x infinity)
+  const float x = sdx * ib, y = clamp_f32(sdy * ib, 32.0f);
   const float sg = sb * exp2_f32(-0.25f * kLog2e * fmaf(x, x, y * y));
   float hx[NMAX + 2], hy[NMAX + 2];  // He_n, hx times sg
   float ex[NMAX + 2], ey[NMAX + 2];  // n He_(n-1), ex times sg
