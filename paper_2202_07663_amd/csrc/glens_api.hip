@@ -558,10 +558,12 @@ static int conv_lds_limit(size_t lds) {
                                            int(kConvLdsMax));
         if (e != hipSuccess) attr_err = e;
       }
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_mfma_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       int(kConvLdsMax));
-    if (e != hipSuccess) attr_err = e;
+    for (const GroupKernel k : {conv_mfma_kernel<false>, conv_mfma_kernel<true>}) {
+      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         int(kConvLdsMax));
+      if (e != hipSuccess) attr_err = e;
+    }
   });
   if (attr_err != hipSuccess && lds > 64 * 1024)
     return set_error(GL_E_DEVICE, "cannot raise the LDS limit: %s", hipGetErrorString(attr_err));
@@ -571,9 +573,9 @@ static int conv_lds_limit(size_t lds) {
 // Static LDS of the matrix-core kernel (the tiles' sums), rounded up.
 constexpr int kMfmaStaticLds = 1280;
 
-// Systems with take(s): block offsets are set here.
+// Systems with take(s): block offsets are set here. adj_only: the adjoint half of a banded pass.
 template <class F>
-static int launch_conv_mfma(Group& g, F take, hipStream_t st) {
+static int launch_conv_mfma(Group& g, bool adj_only, F take, hipStream_t st) {
   size_t lds = 0;
   int tiles = 0;
   for (int i = 0; i < g.nsys; ++i) {
@@ -592,7 +594,8 @@ static int launch_conv_mfma(Group& g, F take, hipStream_t st) {
   const int per_cu = std::min(int(160 * 1024 / (lds + kMfmaStaticLds)), blocks / 256);
   int threads = per_cu >= 4 ? 256 : (per_cu >= 2 ? 512 : kMfmaMaxThreads);
   while (threads > 256 && threads / 64 * 2 > tiles) threads /= 2;
-  return launch(conv_mfma_kernel, blocks, threads, lds, g, st);
+  return launch(adj_only ? conv_mfma_kernel<true> : conv_mfma_kernel<false>, blocks, threads, lds, g,
+                st);
 }
 
 int launch_conv(int K, const Group& g, size_t lds, hipStream_t st) {
@@ -635,10 +638,7 @@ static int launch_conv_band(int K, Group& g, int mode, bool chain, hipStream_t s
     if ((rc = launch(conv_table().band_adj[(K - 1) / 2], g.block0[g.nsys], threads, lds, g, st)))
       return rc;
     if (!any_mfma) return GL_OK;
-    for (int i = 0; i < g.nsys; ++i) g.sys[i].mode = 3;
-    rc = launch_conv_mfma(g, on_mfma, st);
-    for (int i = 0; i < g.nsys; ++i) g.sys[i].mode = mode;
-    return rc;
+    return launch_conv_mfma(g, true, on_mfma, st);
   }
   if (mode == 1) {
     set_blocks(g, [](const SysDesc& s) { return s.conv_mfma ? 0 : (s.P + 63) / 64; });
@@ -678,7 +678,7 @@ int run_group(Group& g, int key, int K, int mode, hipStream_t st, hipEvent_t* ev
   }
   if (any_mfma) {
     const auto on_mfma = [](const SysDesc& s) { return s.conv_mfma != 0; };
-    if ((rc = launch_conv_mfma(g, on_mfma, st))) return rc;
+    if ((rc = launch_conv_mfma(g, false, on_mfma, st))) return rc;
   }
   if (any_valu && banded) {
     if ((rc = launch_conv_band(K, g, mode, chain, st))) return rc;

@@ -348,14 +348,17 @@ __device__ __forceinline__ f32x4 mfma_f16(f16x8 a, f16x8 b, f32x4 c) {
 // acc[v] = correlation of the scaled LDS image (parts x, x + nel) with the scaled PSF over
 // the tiles t0 + v nw, v < G, of one of the block's nw waves. tab: this direction's fragments [K][64][h, l];
 // those of row a + 2 are loaded while row a is computed. Each product is issued over the G
-// tiles before the next, so consecutive matrix instructions are independent.
-template <int G>
+// tiles before the next, so consecutive matrix instructions are independent. APART: the products
+// with a low part, some 2^-11 of the others, are summed apart, so that a third as many additions
+// round at the size of the result.
+template <int G, bool APART>
 __device__ __forceinline__ void mfma_tiles(const uint16_t* x, int nel, const MfmaGeom& q,
                                            const uint4* __restrict__ tab, int K, int t0, int nw,
                                            f32x4* acc) {
   const int lane = threadIdx.x & 63, mr = lane & 15, g = lane >> 4;
   int off[G];  // this lane's fragment offset in tile v at row a = 0
   f16x8 ah[G], al[G];
+  f32x4 low[G];
 #pragma unroll
   for (int v = 0; v < G; ++v) {
     const int t = t0 + v * nw;
@@ -363,7 +366,7 @@ __device__ __forceinline__ void mfma_tiles(const uint16_t* x, int nel, const Mfm
     off[v] = (tr * 16 + mr) * q.pitch + tc * q.N + 8 * g;
     ah[v] = lds_frag(x + off[v]);
     al[v] = lds_frag(x + off[v] + nel);
-    acc[v] = f32x4{0.f, 0.f, 0.f, 0.f};
+    acc[v] = low[v] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   // PSF fragments two rows ahead (an L2 round trip is longer than one row's products)
   const uint4* tb = tab + lane * 2;
@@ -381,10 +384,11 @@ __device__ __forceinline__ void mfma_tiles(const uint16_t* x, int nel, const Mfm
       nnh = tb[(a + 2) * 128];
       nnl = tb[(a + 2) * 128 + 1];
     }
+    f32x4* lo = APART ? low : acc;
 #pragma unroll
-    for (int v = 0; v < G; ++v) acc[v] = mfma_f16(ah[v], bl, acc[v]);
+    for (int v = 0; v < G; ++v) lo[v] = mfma_f16(ah[v], bl, lo[v]);
 #pragma unroll
-    for (int v = 0; v < G; ++v) acc[v] = mfma_f16(al[v], bh, acc[v]);
+    for (int v = 0; v < G; ++v) lo[v] = mfma_f16(al[v], bh, lo[v]);
 #pragma unroll
     for (int v = 0; v < G; ++v) acc[v] = mfma_f16(ah[v], bh, acc[v]);
     if (a + 1 < K) {
@@ -403,6 +407,9 @@ __device__ __forceinline__ void mfma_tiles(const uint16_t* x, int nel, const Mfm
       }
     }
   }
+  if (APART)
+#pragma unroll
+    for (int v = 0; v < G; ++v) acc[v] += low[v];
 }
 
 // Per-pixel state of the matrix-core PSF kernel. The launch descriptor's fields are copied
@@ -497,18 +504,18 @@ __device__ __forceinline__ void mfma_fill(const float* src, const float* v, int 
 }
 
 // G tiles of the wave: correlate, then the per-pixel step.
-template <int G, bool ADJ>
+template <int G, bool ADJ, bool APART>
 __device__ __forceinline__ void mfma_group(MfmaPass& P, const uint16_t* x, int nel,
                                            const uint4* tab, int K, int t0) {
   f32x4 acc[G];
-  mfma_tiles<G>(x, nel, P.q, tab, K, t0, P.nw, acc);
+  mfma_tiles<G, APART>(x, nel, P.q, tab, K, t0, P.nw, acc);
   mfma_pixels<G, ADJ>(P, t0, acc);
 }
 
 // The wave's tiles wave, wave + nw, .. in groups of at most five, as even as possible: a group's
 // products hide the latency of the PSF fragment loads only when it has several tiles. The forward
 // pass of a likelihood leaves its sums of each tile in tile_ll and, if not null, tile_c2 (LDS).
-template <bool ADJ>
+template <bool ADJ, bool APART>
 __device__ __forceinline__ void mfma_pass(MfmaPass& P, const uint16_t* x, int nel,
                                           const uint4* tab, int K, double* tile_ll = nullptr,
                                           double* tile_c2 = nullptr) {
@@ -522,11 +529,11 @@ __device__ __forceinline__ void mfma_pass(MfmaPass& P, const uint16_t* x, int ne
 #pragma unroll
       for (int v = 0; v < kMfmaGroup; ++v) P.ll[v] = P.c2[v] = 0.0;
     switch (n) {
-      case 1: mfma_group<1, ADJ>(P, x, nel, tab, K, t0); break;
-      case 2: mfma_group<2, ADJ>(P, x, nel, tab, K, t0); break;
-      case 3: mfma_group<3, ADJ>(P, x, nel, tab, K, t0); break;
-      case 4: mfma_group<4, ADJ>(P, x, nel, tab, K, t0); break;
-      default: mfma_group<5, ADJ>(P, x, nel, tab, K, t0); break;
+      case 1: mfma_group<1, ADJ, APART>(P, x, nel, tab, K, t0); break;
+      case 2: mfma_group<2, ADJ, APART>(P, x, nel, tab, K, t0); break;
+      case 3: mfma_group<3, ADJ, APART>(P, x, nel, tab, K, t0); break;
+      case 4: mfma_group<4, ADJ, APART>(P, x, nel, tab, K, t0); break;
+      default: mfma_group<5, ADJ, APART>(P, x, nel, tab, K, t0); break;
     }
     if (!ADJ && P.mode != 0) {  // one copy of the sums' code for every group size
       const int lane = threadIdx.x & 63;  // lane 8 v holds tile v's
@@ -568,9 +575,13 @@ __device__ __forceinline__ void band_totals(const SysDesc& s, int part) {
 // half): reloading either part of the fragments from LDS instead of shifting it measured 278 us
 // for the kernel, both 394; five waves per SIMD, at most four or three tiles a group, 180 against
 // 176 at the same clocks; four tiles a group at four waves 189.
-// mode 3: only the adjoint pass, from the seed that the banded forward kernel left in memory (and
-// log L from its bands' partial sums). Against the banded VALU adjoint: 43 -> 33 us (80 x 80, 300
-// vectors), 52 -> 33.6 us (500).
+// ADJ_ONLY: only the adjoint pass, from the seed that the banded forward kernel left in memory (and
+// log L from its bands' partial sums), in place of the banded VALU adjoint: 43 -> 33 us (80 x 80, 300
+// vectors), 52 -> 33.6 us (500). The operands' two parts are 22 bits or more of a seed's 24, so
+// that the sums have to be the better for it: with the low products apart the rms error against 64
+// bits is 0.41 to 0.83 of the VALU sums' over the sizes that come here (1.2 to 1.4 of them in one
+// accumulator, at the sizes whose strips are summed over two lanes).
+template <bool ADJ_ONLY>
 __global__ void __launch_bounds__(kMfmaMaxThreads) __attribute__((amdgpu_waves_per_eu(4)))
 conv_mfma_kernel(Group g) {
   extern __shared__ __align__(16) uint16_t xlds[];
@@ -584,10 +595,9 @@ conv_mfma_kernel(Group g) {
   const int nel = q.Hq * q.pitch;  // fp16 per part (a multiple of 4)
   for (int i = threadIdx.x; i < nel / 4; i += blockDim.x)
     reinterpret_cast<uint4*>(xlds)[i] = make_uint4(0u, 0u, 0u, 0u);
-  const bool adj_only = mode == 3;
   // a lane's pixels wait in registers (those of a large image past the sixteenth are read again,
   // from L2) for the image's largest magnitude: in LDS they would take as much room again
-  const float* src = (adj_only ? s.seed : s.m0) + (size_t)part * HW;
+  const float* src = (ADJ_ONLY ? s.seed : s.m0) + (size_t)part * HW;
   float v[kMfmaKeep], mx = 0.f;
   mfma_load(src, HW, v);
 #pragma unroll
@@ -599,10 +609,10 @@ conv_mfma_kernel(Group g) {
   mfma_fill(src, v, HW, W, C, sx, xlds, q.pitch, nel);
   MfmaPass P{q, int(blockDim.x) >> 6, -(sx + s.psf_mfma_exp), H, W, mode, s.s2b, s.inv_gt,
              s.inv_k2, s.obs, (mode == 0 ? s.img : s.sbar) + (size_t)part * HW, 0.f, {}, {}};
-  if (adj_only) {
+  if (ADJ_ONLY) {
     if (threadIdx.x == 0) band_totals(s, part);
   } else {
-    mfma_pass<false>(P, xlds, nel, s.psf_mfma, K, tile_ll, s.chi2 ? tile_c2 : nullptr);
+    mfma_pass<false, false>(P, xlds, nel, s.psf_mfma, K, tile_ll, s.chi2 ? tile_c2 : nullptr);
     if (mode == 0) return;
     __syncthreads();  // the tiles' sums are there
     if (threadIdx.x < 64) {
@@ -622,7 +632,7 @@ conv_mfma_kernel(Group g) {
     P.unscale = -(sx + s.psf_mfma_exp);
   }
   // d logL / d m0 = correlation of the pixel seed with the (unflipped) PSF
-  mfma_pass<true>(P, xlds, nel, s.psf_mfma + 2 * 64 * K, K);
+  mfma_pass<true, ADJ_ONLY>(P, xlds, nel, s.psf_mfma + 2 * 64 * K, K);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -633,7 +643,7 @@ conv_mfma_kernel(Group g) {
 //                          adjoint seed of each pixel (to a [P][H][W] buffer);
 //   conv_band_adj_kernel   the correlation of the seed with the PSF; the first band of a
 //                          particle also adds the likelihood partials (band order). Where the
-//                          matrix-core kernel takes the system it does this instead (mode 3),
+//                          matrix-core kernel takes the system it does this instead,
 //                          except for the sampler's chains;
 //   conv_band_sum_kernel   the same addition when there is no adjoint pass.
 // With band_split = 1 the arithmetic per pixel is that of conv_kernel (only the order of the

@@ -7,7 +7,7 @@ def sampler_gradient(model, theta):
     """log L and its gradient at theta [P, d] (numpy) from the sampler's kernels. With normal priors
     of width 1e9 the unconstrained coordinates are theta itself and the prior's gradient is far
     below FP32 resolution of that of log L. From zero momentum, a step of 2^-40 moves no FP32
-    coordinate, and p = 2^-40 (g / 2 + g / 2) is exact."""
+    coordinate (one that is zero by 1e-24 g), and p = 2^-40 (g / 2 + g / 2) is exact."""
     import torch
     import paper_2202_07663_amd as G
     P, d = theta.shape
