@@ -108,7 +108,7 @@ int gl_model_reserve(gl_model* model, int P, int with_fit);
  *              at most 64 tiles of 16 rows, and one band: P >= 512 or at most 8 rows),
  *              GL_PSF_VALU (vector ALUs, one workgroup per vector) or GL_PSF_BANDED (vector
  *              ALUs, row bands of the image per vector, for P < 512; its adjoint half on matrix
- *              cores, where the image fits them, from P H W K^2 = 2e8);
+ *              cores for K >= 15 and at most 48 tiles from P H W K^2 = 2e8);
  *   tiles, fwd_tiles: sub-pixel work tiles per vector of the adjoint and the forward pass;
  *   bands:     row bands of the PSF pass (1 unless banded);
  *   workspace_bytes: device work space of a likelihood call at this P (gl_model_reserve);

@@ -392,9 +392,13 @@ SysDesc make_sys(const SystemData& sd, const Workspace& ws, int P, int tiles) {
                     size_t(mfma_lds_bytes(q, c.H)) <= kConvLdsMax;
   s.conv_mfma = fits && s.bands == 1;
   // the adjoint half of a banded pass: from about 2e8 products the matrix cores win over the VALU
-  // kernel's shorter latency (60 x 60, K = 21: 64 vectors, 1.0e8, 13.2 us against 10.2; 80 x 80, 300
-  // vectors, 8.5e8, 33.3 against 43.4)
-  s.adj_mfma = fits && s.bands > 1 && double(P) * HW * c.K * c.K >= 2e8;
+  // kernel's shorter latency (PSF pass of 60 x 60, K = 21, VALU / matrix cores: 63 vectors 22.3 /
+  // 24.9 us, 126 (2.0e8) 27.5 / 27.7, 176 36.4 / 32.3, 504 63.6 / 55.2), but not with small PSFs,
+  // whose columns fill less than half of a product's window (80 x 80, K = 13: 0.91 to 1.03 times as
+  // fast from 100 to 511 vectors, K = 15 1.00 to 1.09, K = 11 0.90 to 0.98), nor with more than 48
+  // tiles, whose block takes so long that a second turn of the chip with few blocks shows (100 x
+  // 100, K = 21, 63 tiles: 0.89 at 300 vectors, 1.07 at 511; 96 x 96, 48 tiles: 1.01 and 1.18)
+  s.adj_mfma = fits && s.bands > 1 && c.K >= 15 && q.T <= 48 && double(P) * HW * c.K * c.K >= 2e8;
   return s;
 }
 
