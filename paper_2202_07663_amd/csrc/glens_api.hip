@@ -266,10 +266,10 @@ size_t acc_rows_upto(int P, int HW) {
   return std::max(rows, size_t(std::max(P, 0)) * choose_tiles(std::max(P, 1), HW));
 }
 
-// Bytes of a work space as batch limits and memory budgets count it: const_b bytes of constants
-// per particle, slots sums per accumulator row, images pixel arrays per particle.
-static size_t layout_bytes(size_t const_b, int slots, int images, int P, size_t rows, int HW,
-                           int d, bool fit, int beta_pp) {
+// Bytes of a work space with const_b bytes of constants per particle, slots sums per accumulator
+// row and images pixel arrays per particle.
+size_t layout_bytes(size_t const_b, int slots, int images, int P, size_t rows, int HW,
+                    int d, bool fit, int beta_pp) {
   size_t b = align256(const_b * P) + images * align256(sizeof(float) * (size_t)P * HW) +
              align256(sizeof(double) * rows * slots) +
              align256(sizeof(double) * (size_t)P * kConvMaxBands * 2) +
@@ -279,10 +279,7 @@ static size_t layout_bytes(size_t const_b, int slots, int images, int P, size_t 
 }
 
 size_t workspace_bytes(int P, size_t rows, int HW, int d, bool fit, int beta_pp) {
-  // The fixed allowance keeps the batch that fits a given budget independent of the layout; the
-  // layout itself is smaller (two pixel arrays, not three) except for images of a few pixels.
-  return std::max(layout_bytes(3472, 72, 3, P, rows, HW, d, fit, beta_pp),
-                  layout_bytes(sizeof(PConst), kNAcc, 2, P, rows, HW, d, fit, beta_pp));
+  return layout_bytes(sizeof(PConst), kNAcc, 2, P, rows, HW, d, fit, beta_pp);
 }
 
 void workspace_layout(Workspace& ws, char* base, int cP, size_t rows, int HW, int d, bool fit,
@@ -314,7 +311,7 @@ void workspace_layout(Workspace& ws, char* base, int cP, size_t rows, int HW, in
   ws.cap_P = cP;
   ws.cap_rows = rows;
   ws.HW = HW;
-  ws.bytes = workspace_bytes(cP, rows, HW, d, fit, beta_pp);
+  ws.bytes = off;
 }
 
 void workspace_free(Workspace& ws) {

@@ -60,6 +60,8 @@ struct Workspace {
 // beta_pp: float2 entries of the beta buffer per particle (beta_per_particle(cfg)); rows:
 // accumulator rows, P x tiles for one batch size (acc_rows_upto for every size up to P).
 size_t workspace_bytes(int P, size_t rows, int HW, int d, bool fit_buffers, int beta_pp);
+size_t layout_bytes(size_t const_b, int slots, int images, int P, size_t rows, int HW, int d,
+                    bool fit_buffers, int beta_pp);
 size_t acc_rows_upto(int P, int HW);
 // Carve the work space out of `base` (workspace_bytes long, 256-byte aligned).
 void workspace_layout(Workspace& ws, char* base, int P, size_t rows, int HW, int d,
@@ -145,7 +147,7 @@ constexpr int kStageTimesMaxCalls = 10000;
 
 // Work space of gl_loglik_grad_noalloc: a fixed device array of kNoAllocBytes per device.
 constexpr size_t kNoAllocBytes = size_t(128) << 20;
-size_t noalloc_bytes(const ModelCfg& c, int P);    // its work space at P particles
+size_t noalloc_bytes(const ModelCfg& c, int P);    // what P particles count of it
 int noalloc_max_particles(const ModelCfg& c);      // the largest P that fits
 
 }  // namespace glens

@@ -47,16 +47,23 @@ static int scratch_ptr(int dev, char** out) {
   return GL_OK;
 }
 
+// The limit counts a fixed allowance (3472 bytes of constants and three pixel arrays per vector, 72
+// sums per tile), not the layout's own size, so that it stays where callers have found it. The
+// layout takes less, but for images of fewer than 40 pixels, whose arrays at the limit still fit
+// (127.9 MiB at most).
+static size_t counted_bytes(const ModelCfg& c, int P, size_t rows) {
+  return layout_bytes(3472, 72, 3, P, rows, c.H * c.W, c.d, false, beta_per_particle(c));
+}
+static_assert(sizeof(PConst) <= 3616 && kNAcc <= 72, "the layout at the limit");
+
 size_t noalloc_bytes(const ModelCfg& c, int P) {
-  const int HW = c.H * c.W;
-  return workspace_bytes(P, size_t(P) * choose_tiles(P, HW), HW, c.d, false,
-                         beta_per_particle(c));
+  return counted_bytes(c, P, size_t(P) * choose_tiles(P, c.H * c.W));
 }
 
 int noalloc_max_particles(const ModelCfg& c) {
   // the per-particle arrays alone bound P from above; scan down from there to the largest P
   // whose work space (with its accumulator rows, which shrink as P grows) fits
-  const size_t per = workspace_bytes(1, 0, c.H * c.W, c.d, false, beta_per_particle(c));
+  const size_t per = counted_bytes(c, 1, 0);
   int P = int(std::min<size_t>(kNoAllocBytes / per, size_t(1) << 24));
   while (P > 0 && noalloc_bytes(c, P) > kNoAllocBytes) --P;
   return P;
@@ -94,6 +101,9 @@ int gl_loglik_grad_noalloc(gl_model* m, const float* theta, int P, double* logl,
   char* base = nullptr;
   if ((rc = scratch_ptr(dev, &base))) return rc;
   const int HW = c.H * c.W, tiles = choose_tiles(P, HW);
+  if (workspace_bytes(P, size_t(P) * tiles, HW, c.d, false, beta_per_particle(c)) >
+      kNoAllocBytes)
+    return set_error(GL_E_BUDGET, "P = %d does not fit the allocation-free work space", P);
   Workspace ws;
   workspace_layout(ws, base, P, size_t(P) * tiles, HW, c.d, false, beta_per_particle(c));
   Group g;
