@@ -46,6 +46,23 @@ __device__ __forceinline__ int find_sys(const Group& g, int b) {
   return i;
 }
 
+// Single-precision hardware transcendentals in base 2 (about 1 ulp), for normal, finite
+// arguments; callers fold log2(e) into their per-particle constants.
+__device__ __forceinline__ float exp2_f32(float x) { return __builtin_amdgcn_exp2f(x); }
+__host__ inline float exp2_f32(float x) { return exp2f(x); }
+__device__ __forceinline__ float log2_f32(float x) { return __builtin_amdgcn_logf(x); }
+__host__ inline float log2_f32(float x) { return log2f(x); }
+__device__ __forceinline__ float rcp_f32(float x) { return __builtin_amdgcn_rcpf(x); }
+__host__ inline float rcp_f32(float x) { return 1.0f / x; }
+__device__ __forceinline__ float rsq_f32(float x) { return __builtin_amdgcn_rsqf(x); }
+__host__ inline float rsq_f32(float x) { return 1.0f / sqrtf(x); }
+__device__ __forceinline__ float clamp_f32(float x, float most) {
+  return __builtin_amdgcn_fmed3f(x, -most, most);
+}
+__host__ inline float clamp_f32(float x, float most) { return fminf(fmaxf(x, -most), most); }
+constexpr float kLn2f = 0.69314718055994531f;
+constexpr float kLog2e = 1.44269504088896341f;
+
 // ------------------------------------------------------------------------------------------
 // Per-particle decode (prologue). Double precision: it runs once per particle.
 // ------------------------------------------------------------------------------------------
@@ -146,13 +163,13 @@ GL_HD void decode_mass(const float* th, int mass, int shear, MassC& c) {
   c.hm = float(-0.5 * t);
   c.omt = float(1.0 - t);
   const bool sx = eabs < kSxClosedMin;
-  c.icr = sx ? 1.0 : e1 * (1.0 - ee);
+  // ic S with S = ((1 + e1) hx + e2 hy + i (e2 hx + (1 - e1) hy)) / (1 - |eps|^2)
+  c.icr = (1.0 - ee) * (sx ? 1.0 : e1);
   c.ici = sx ? 0.0 : -e2 * (1.0 - ee);
-  const double oo = 1.0 / (1.0 - ee);
-  c.sr1 = float((c.icr * (1.0 + e1) - c.ici * e2) * oo);
-  c.sr2 = float((c.icr * e2 - c.ici * (1.0 - e1)) * oo);
-  c.si1 = float((c.icr * e2 + c.ici * (1.0 + e1)) * oo);
-  c.si2 = float((c.icr * (1.0 - e1) + c.ici * e2) * oo);
+  c.sr1 = float(sx ? 1.0 + e1 : e1 + ee);
+  c.sr2 = float(e2);
+  c.si1 = float(sx ? e2 : -e2);
+  c.si2 = float(sx ? 1.0 - e1 : e1 - ee);
   c.ka = sx ? 0.f : float(-t * ee);
   c.e1f = float(e1);
   c.e2f = float(e2);
@@ -164,7 +181,7 @@ GL_HD void decode_mass(const float* th, int mass, int shear, MassC& c) {
   // ring |w| = B), and hq is rounded with them
   const double l2b2 = 2.0 * log(B) * 1.4426950408889634;
   c.l2b2 = float(l2b2);
-  const double sc = mass == 1 ? 1.0 + 0.6931471805599453 * (c.hm * l2b2 + c.tlnb2) : c.hb / (0.5 * B);
+  const double sc = mass == 1 ? 1.0 + 0.6931471805599453 * (c.hm * l2b2 + c.tlnb2) : 1.0 + (c.hb - 0.5 * B) * rcp_f32(c.hb);
   const double hq = c.hp * (1.0 - ee) * sc;
   c.hq = float(hq);
   c.hql = float(hq - c.hq);
@@ -438,23 +455,6 @@ __device__ __forceinline__ double rsq_f64(double x) {
 }
 __host__ inline double rsq_f64(double x) { return 1.0 / sqrt(x); }
 
-// Single-precision hardware transcendentals in base 2 (about 1 ulp), for normal, finite
-// arguments; callers fold log2(e) into their per-particle constants.
-__device__ __forceinline__ float exp2_f32(float x) { return __builtin_amdgcn_exp2f(x); }
-__host__ inline float exp2_f32(float x) { return exp2f(x); }
-__device__ __forceinline__ float log2_f32(float x) { return __builtin_amdgcn_logf(x); }
-__host__ inline float log2_f32(float x) { return log2f(x); }
-__device__ __forceinline__ float rcp_f32(float x) { return __builtin_amdgcn_rcpf(x); }
-__host__ inline float rcp_f32(float x) { return 1.0f / x; }
-__device__ __forceinline__ float rsq_f32(float x) { return __builtin_amdgcn_rsqf(x); }
-__host__ inline float rsq_f32(float x) { return 1.0f / sqrtf(x); }
-__device__ __forceinline__ float clamp_f32(float x, float most) {
-  return __builtin_amdgcn_fmed3f(x, -most, most);
-}
-__host__ inline float clamp_f32(float x, float most) { return fminf(fmaxf(x, -most), most); }
-constexpr float kLn2f = 0.69314718055994531f;
-constexpr float kLog2e = 1.44269504088896341f;
-
 constexpr double kLn2 = 0.6931471805599453;  // nearest double to ln 2
 
 // The power tables (PConst::pw): entry i < kPowExp is B^t 2^(-t e/2) for e = i - kPowExp/2 ...
@@ -606,7 +606,7 @@ __device__ __forceinline__ void ray_trace(const PConst& c, const double* __restr
 //     end. With g.(d alpha/d eps_1) + i g.(d alpha/d eps_2) =: G and S = Sp - i Dm,
 //       ic G = gb (w (kappa + conj(eps) Gamma) - (1 - t/2)(1 - |eps|^2) alpha) - z (ic S)
 //              - t |eps|^2 Re(gb alpha).
-//     For |eps| < kSxClosedMin W is summed by the derivative series instead, and ic = 1;
+//     For |eps| < kSxClosedMin W is summed by the derivative series instead, and ic = 1 - |eps|^2;
 //   * d alpha / dt = alpha (ln B - ln|w|^2 / 2) + A w S_t by its series (EPL), with the
 //     coefficients times -2 / ln 2 so that the sum runs over base-2 logarithms.
 // Series are summed by synthetic division at y = -X (ray_trace), four terms per trip (the length
@@ -690,6 +690,7 @@ __device__ __forceinline__ void mass_adjoint(const PConst& c, const float* __res
       }
     }
     const Cx SX = {-fmaf(Xr, d2, d1), Xi * d2};  // dS/dX = -dS/dy
+    A *= 1.0f - c.eef;
     const Cx W = cmul(Cx{A * gwr, A * gwi}, cmul(Cx{u2r, u2i}, SX));
     acc[A_M_E1] += fmaf(zi, si, fmaf(-zr, sr, W.r));
     acc[A_M_E2] += fmaf(-zi, sr, fmaf(-zr, si, W.i));
