@@ -203,13 +203,16 @@ int choose_tiles(int P, int HW) {
 }
 
 // The forward pass (6 workgroups per CU) gains from finer tiles where the adjoint (3 per CU,
-// with a partial sum per tile) does not: aim at >= 12288 workgroups (8 rounds of the chip), and
+// with a partial sum per tile) does not: aim at >= 12288 workgroups (8 rounds of the chip), at a
+// third of it without supersampling, where a block's start (its constants and power tables) is as
+// long as a pixel (59 systems with k = 1: 0.96 times the time on average, 1.01 at most; 59 x 69,
+// 1848 vectors 3 tiles for 8, 62.5 -> 54.5 us; 75 x 75, 600 7 for 22, 37.8 -> 32.5), and
 // at up to two fifths more where that leaves fewer lanes and waves idle at a tile's end (turns
 // of 64 pixels, a tenth of one per wave without a last one, 0.8 / k^2 per tile): 80 x 80, 512
 // vectors 25 tiles for 24, 80.6 -> 68.3 us between events; 60 x 60, 900 15 for 14, 88.1 -> 75.2;
 // 1024 15 for 12, 88.3 -> 84.5; 100 x 100, 400 40 for 31, 92.2 -> 81.3.
 static int choose_fwd_tiles(int P, int HW, int k) {
-  const int want = (12288 + P - 1) / std::max(P, 1);
+  const int want = ((k == 1 ? 4096 : 12288) + P - 1) / std::max(P, 1);
   const int maxt = std::max(1, (HW + kSubThreads - 1) / kSubThreads);
   const int first = std::max(1, std::min(want, maxt));
   int best = first;
