@@ -229,25 +229,24 @@ static int choose_fwd_tiles(int P, int HW, int k) {
 }
 
 // Tiles of the batched calls' adjoint (at most choose_tiles, which sizes the accumulators): the
-// fewest cycles by the blocks of a CU (up to eight, those of the fullest one; beyond, their mean, as
-// CUs then even out) and 1.3 more for the last to end, each as long as its waves' pixels and a
-// fixed part (the sums across its lanes) of about as much as 1.65 sub-pixels (2 at n_max = 8, whose
+// fewest cycles by the blocks of a CU (up to twelve, those of the fullest one; beyond, their mean, as
+// CUs then even out) and one more for the last to end, each as long as its waves' pixels and a
+// fixed part (the sums across its lanes) of about as much as 2 sub-pixels (3.3 at n_max = 8, whose
 // sums go in two parts), and 0.3 more where it takes a second turn of 256 pixels. A block takes as
-// many turns as its first wave where it has a SIMD nearly for itself; beside others, which use in
-// part what its last pixels leave idle, a fifth less of its last one. Over 360 systems and batches
-// (24 to 112 pixels, 16 to 2047 vectors, every n_max) between 0.98 and 1.5 times as fast as with as
-// many tiles as choose_tiles allows, 1.035 on average, and within 2 % of the best number on average:
-// 60 x 60, n_max = 6, k = 2: 200 vectors 49 -> 44.5 us, 300 (5 tiles for 7) 61.3 -> 52.7; 44 x 44,
-// k = 1, 605 (2 for 4) 33.1 -> 26.8.
+// many turns as its first wave where it has a SIMD nearly for itself; others beside it use half of
+// what its last pixels leave idle. Over 760 systems and batches (24 to 112 pixels, 16 to 2047
+// vectors, every n_max) 1.04 times as fast on average as with as many tiles as choose_tiles allows
+// (0.91 to 1.5), and within 1.3 % of the best number on average: 60 x 60, n_max = 6, k = 2: 200
+// vectors 49 -> 44.5 us, 300 (5 tiles for 7) 61.3 -> 52.7; 44 x 44, k = 1, 605 (2 for 4) 33.1 -> 26.8.
 static int choose_adj_tiles(const ModelCfg& c, int P, int tiles) {
-  const double per = 1.0 / (c.k * c.k), fixed = (c.nmax >= 8 ? 2.0 : 1.65) * per;
+  const double per = 1.0 / (c.k * c.k), fixed = (c.nmax >= 8 ? 3.3 : 2.0) * per;
   int best = 1;
   double least = 0.0;
   for (int t = 1; t <= tiles; ++t) {
-    const double mean = P * (t / 256.0), blocks = mean > 8.0 ? mean : std::ceil(mean);
+    const double mean = P * (t / 256.0), blocks = mean > 12.0 ? mean : std::ceil(mean);
     const int pixels = (c.H * c.W + t - 1) / t, turns = (pixels + kSubThreads - 1) / kSubThreads;
-    const double whole = blocks <= 2.0 ? 1.0 : 0.8;
-    const double cost = (blocks + 1.3) * (whole * turns + (1.0 - whole) * pixels / kSubThreads +
+    const double whole = blocks <= 2.0 ? 1.0 : 0.5;
+    const double cost = (blocks + 1.0) * (whole * turns + (1.0 - whole) * pixels / kSubThreads +
                                           fixed + (turns > 1 ? 0.3 * per : 0.0));
     if (t == 1 || cost <= 1.01 * least) {
       least = cost;
