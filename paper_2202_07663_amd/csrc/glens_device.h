@@ -163,14 +163,8 @@ GL_HD void decode_mass(const float* th, int mass, int shear, MassC& c) {
   c.hm = float(-0.5 * t);
   c.omt = float(1.0 - t);
   const bool sx = eabs < kSxClosedMin;
-  // ic S with S = ((1 + e1) hx + e2 hy + i (e2 hx + (1 - e1) hy)) / (1 - |eps|^2)
   c.icr = (1.0 - ee) * (sx ? 1.0 : e1);
   c.ici = sx ? 0.0 : -e2 * (1.0 - ee);
-  c.sr1 = float(sx ? 1.0 + e1 : e1 + ee);
-  c.sr2 = float(e2);
-  c.si1 = float(sx ? e2 : -e2);
-  c.si2 = float(sx ? 1.0 - e1 : e1 - ee);
-  c.ka = sx ? 0.f : float(-t * ee);
   c.e1f = float(e1);
   c.e2f = float(e2);
   c.eef = float(ee);
@@ -178,11 +172,13 @@ GL_HD void decode_mass(const float* th, int mass, int shear, MassC& c) {
   c.tlnb2 = float(c.tlnb * 1.4426950408889634);
   c.hb = B < 0.0 ? NAN : float(0.5 * B);
   // kappa is in proportion to constants rounded to FP32 (EPL: 2^(hm log2|w|^2 + tlnb2), on the
-  // ring |w| = B), and hq is rounded with them
+  // ring |w| = B), and ha and hq are rounded with them
   const double l2b2 = 2.0 * log(B) * 1.4426950408889634;
   c.l2b2 = float(l2b2);
   const double sc = mass == 1 ? 1.0 + 0.6931471805599453 * (c.hm * l2b2 + c.tlnb2) : 1.0 + (c.hb - 0.5 * B) * rcp_f32(c.hb);
-  const double hq = c.hp * (1.0 - ee) * sc;
+  const double ha = c.hp * (1.0 + ee) * sc, hq = c.hp * (1.0 - ee) * sc;
+  c.ha = float(ha);
+  c.hal = float(ha - c.ha);
   c.hq = float(hq);
   c.hql = float(hq - c.hq);
   c.tf = float(t);
@@ -590,23 +586,20 @@ __device__ __forceinline__ void ray_trace(const PConst& c, const double* __restr
 //     X ((t/2) S + X S_X)), the derivative of the closed form, into (1 - t/2) A;
 //   * alpha has degree 1 - t in z, so z alpha_z + conj(z) alpha_zb = (1 - t) alpha gives
 //       Gamma = alpha_zb = ((1 - t) alpha - kappa z) z / |z|^2   (SIE: -kappa z^2 / |z|^2);
-//   * aw = d alpha/dw and awb = d alpha/d conj(w) at fixed eps solve kappa = aw - conj(eps) awb,
-//     Gamma = awb - eps aw, so (1 - |eps|^2)(aw, awb) = (kappa + conj(eps) Gamma, Gamma + eps
-//     kappa). With U = gb aw, V = gb awb, Sp = Re U + Re V and Dm = Im U - Im V,
-//       g . d alpha/dx = (1 - e1) Sp + e2 Dm, g . d alpha/dy = -(1 + e1) Dm - e2 Sp,
-//     which are had from kappa and Gamma directly and solved for Sp and Dm;
 //   * d alpha/d eps = -tfac conj(eps) alpha - conj(z) aw,
-//     d alpha/d conj(eps) = -tfac eps alpha - z awb + W, tfac = t / (2 (1 - |eps|^2)),
-//     W = A w u2 dS/dX (A depends on |eps|^2, X on conj(eps); w aw = alpha (1 - t/2) + A w X S_X):
-//       g . d alpha/de1 = -2 tfac e1 Re(gb alpha) - Re(z) Sp - Im(z) Dm + Re(gb W),
-//       g . d alpha/de2 = -2 tfac e2 Re(gb alpha) + Re(z) Dm - Im(z) Sp + Im(gb W),
-//     W from conj(eps) W = w aw - (1 - t/2) alpha. Its terms cancel like |eps|, and what is left
-//     against the others: taken per sub-pixel (of sums over a tile, the differences had twice the
-//     error), everything times ic = conj(eps) (1 - |eps|^2), which the sums are divided by at the
-//     end. With g.(d alpha/d eps_1) + i g.(d alpha/d eps_2) =: G and S = Sp - i Dm,
-//       ic G = gb (w (kappa + conj(eps) Gamma) - (1 - t/2)(1 - |eps|^2) alpha) - z (ic S)
-//              - t |eps|^2 Re(gb alpha).
-//     For |eps| < kSxClosedMin W is summed by the derivative series instead, and ic = 1 - |eps|^2;
+//     d alpha/d conj(eps) = -tfac eps alpha - z awb + W, with tfac = t / (2 (1 - |eps|^2)),
+//     aw = d alpha/dw, awb = d alpha/d conj(w) at fixed eps and W = A w u2 dS/dX (A depends on
+//     |eps|^2, X on conj(eps)). kappa = aw - conj(eps) awb and Gamma = awb - eps aw, so
+//     (1 - |eps|^2)(aw, awb) = (kappa + conj(eps) Gamma, Gamma + eps kappa), and conj(eps) W = w aw -
+//     (1 - t/2) alpha. With h = g . (d alpha/dx) + i g . (d alpha/dy) = kappa g + gb Gamma, the two
+//     components G = g.(d alpha/d eps_1) + i g.(d alpha/d eps_2) are
+//       (1 - |eps|^2) G = -t eps Re(gb alpha) - z (h + eps conj(h)) + (1 - |eps|^2) gb W;
+//     times conj(eps), with w = z - eps conj(z) and Re(conj(z) h) = (1 - t) Re(gb alpha),
+//       conj(eps)(1 - |eps|^2) G = kappa w (gb - conj(eps) g)
+//         - (1 - t/2)((1 + |eps|^2) Re(gb alpha) + i (1 - |eps|^2) Im(gb alpha)).
+//     These terms cancel like |eps|, so the difference is taken per sub-pixel (of sums over a tile,
+//     the differences had twice the error) and the sums are divided at the end. For |eps| <
+//     kSxClosedMin W is summed by the derivative series instead, in the form above it;
 //   * d alpha / dt = alpha (ln B - ln|w|^2 / 2) + A w S_t by its series (EPL), with the
 //     coefficients times -2 / ln 2 so that the sum runs over base-2 logarithms.
 // Series are summed by synthetic division at y = -X (ray_trace), four terms per trip (the length
@@ -653,7 +646,6 @@ __device__ __forceinline__ void mass_adjoint(const PConst& c, const float* __res
   acc[A_M_G1] = fmaf(-g.i, zi, fmaf(g.r, zr, acc[A_M_G1]));
   acc[A_M_G2] = fmaf(g.i, zr, fmaf(g.r, zi, acc[A_M_G2]));
   const bool sx = GENERAL && c.epsabs < kSxClosedMin;
-  const float sr = fmaf(c.sr1, hxr, c.sr2 * hxi), si = fmaf(c.si1, hxr, c.si2 * hxi);
   float u2r = 0.f, u2i = 0.f, Xr = 0.f, Xi = 0.f;
   if (MASS == 1 || GENERAL) {
     const float iw2 = rcp_f32(w2);
@@ -692,14 +684,15 @@ __device__ __forceinline__ void mass_adjoint(const PConst& c, const float* __res
     const Cx SX = {-fmaf(Xr, d2, d1), Xi * d2};  // dS/dX = -dS/dy
     A *= 1.0f - c.eef;
     const Cx W = cmul(Cx{A * gwr, A * gwi}, cmul(Cx{u2r, u2i}, SX));
+    const float sr = fmaf(e1, hxr, fmaf(e2, hxi, hxr)), si = fmaf(e2, hxr, fmaf(-e1, hxi, hxi));
     acc[A_M_E1] += fmaf(zi, si, fmaf(-zr, sr, W.r));
     acc[A_M_E2] += fmaf(-zi, sr, fmaf(-zr, si, W.i));
   } else {
-    const float tr = fmaf(e1, Gr, fmaf(e2, Gi, kap)), ti = fmaf(e1, Gi, -e2 * Gr);
-    const float qr = fmaf(wr, tr, fmaf(-wi, ti, fmaf(-c.hql, ar, -c.hq * ar)));
-    const float qi = fmaf(wr, ti, fmaf(wi, tr, fmaf(-c.hql, ai, -c.hq * ai)));
-    acc[A_M_E1] += fmaf(zi, si, fmaf(-zr, sr, fmaf(c.ka, ga, fmaf(g.i, qi, g.r * qr))));
-    acc[A_M_E2] += fmaf(-zi, sr, fmaf(-zr, si, fmaf(-g.i, qr, g.r * qi)));
+    // kappa (gb - conj(eps) g), Im(gb alpha)
+    const float ur = fmaf(-e1, kr, fmaf(-e2, ki, kr)), ui = fmaf(e2, kr, fmaf(-e1, ki, -ki));
+    const float gi = fmaf(-g.i, ar, g.r * ai);
+    acc[A_M_E1] += fmaf(wr, ur, fmaf(-wi, ui, fmaf(-c.hal, ga, -c.ha * ga)));
+    acc[A_M_E2] += fmaf(wr, ui, fmaf(wi, ur, fmaf(-c.hql, gi, -c.hq * gi)));
   }
 }
 
@@ -915,7 +908,7 @@ GL_HD MassSums mass_sums(const PConst& c, const double* a) {
   MassSums m;
   const double e1 = c.e1, e2 = c.e2, ee = e1 * e1 + e2 * e2, oo = 1.0 / (1.0 - ee);
   const double ii = 1.0 / (c.icr * c.icr + c.ici * c.ici);
-  // -2 tfac Re(gb alpha), where its part is not in the sums
+  // -2 tfac Re(gb alpha), where it is not in the sums
   const double k = c.epsabs < kSxClosedMin ? -c.t * oo * a[A_M_ALPHA] : 0.0;
   m.alpha = a[A_M_ALPHA];
   m.t = -0.5 * kLn2 * a[A_M_T];

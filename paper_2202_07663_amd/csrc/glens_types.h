@@ -100,9 +100,7 @@ struct MassC {
   float hp, hm;        // 1 - t/2, -t/2
   float omt;           // 1 - t
   double icr, ici;     // ic: (1 - |eps|^2) times conj(eps) for |eps| >= kSxClosedMin, or 1
-  float sr1, sr2, si1, si2;  // (S', -D') = the 2 x 2 matrix (sr; si) of g.(d alpha / d(x, y))
-  float ka;            // -2 tfac |eps|^2 (1 - |eps|^2) for |eps| >= kSxClosedMin, else 0
-  float hq, hql;       // (1 - t/2)(1 - |eps|^2) in two parts, and rounded as kappa is: an error
+  float ha, hal, hq, hql;  // (1 - t/2)(1 +- |eps|^2) in two parts, and rounded as kappa is: an error
                        // that all sub-pixels share would be divided by |eps| (mass_adjoint)
   float w2floorf;      // R^2 floor on |w|^2 (FP32)
   float tlnb2;         // t log2 B
