@@ -7,8 +7,12 @@
 // leapfrog steps, and the log p~ reached differ by 1e-6). So that a seed keeps giving the chains
 // that it gave, the HMC launches keep this arithmetic, term for term; the batched likelihood
 // calls, the fit and the variational fit take the shorter sums of glens_device.h (mass_adjoint).
-// At a sampler's batch sizes the launches are bound by latency and the two run equally fast
-// (60 x 60, 64 vectors: 68.0 and 67.7 us a gradient call).
+// What that costs, one leapfrog step (these kernels, and the kick, move and decode fused into one
+// launch) beside one gradient call of the batched kernels, in us: 60 x 60 EPL with n_max 6,
+// 62.2 / 58.2 at 64 chains, 127 / 111 at 256, 180 / 165 at 512, 307 / 284 at 1024; with n_max 8,
+// whose adjoint spills here, 97.6 / 62.2 at 64 and 288 / 195 at 512; an SIE with n_max 3, 52.5 / 53.1
+// at 64 and 165 / 131 at 512. The two are alike where a launch leaves the chip partly idle and the
+// adjoint does not spill; elsewhere the same chains are what is paid for.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -20,8 +24,7 @@ namespace glens {
 namespace chain {
 
 // EPL / SIE deflection plus shear at image position (x, y), in FP64: returns beta - x_s with
-// beta = x - alpha - alpha_ext. cs: the particle's series coefficients c.c (the kernels pass
-// a copy staged in LDS).
+// beta = x - alpha - alpha_ext.
 // at_floor: this is the particle's floored sub-pixel (c.fl_*); the SIE then takes the
 // frozen-radius closed form the prologue evaluated (the EPL's value there is this formula's).
 // cs / pw: the particle's series coefficients c.c and power tables c.pw (staged in LDS).

@@ -94,11 +94,11 @@ __device__ __forceinline__ void forward_pixels(const SysDesc& s, const PConst* _
   }
 }
 
-// Bound by VALU issue at large batches: 172 instructions per sub-pixel at 60 x 60, n_max 6 (190
+// Bound by VALU issue at large batches: 175 instructions per sub-pixel at 60 x 60, n_max 6 (193
 // with w and beta - x_s formed term by term), 36 of them the FP64 series. The register cap keeps
 // six waves per SIMD (five from n_max = 7, whose coefficients alone take 36 or 45 registers):
-// left to itself the compiler takes 83 registers and five waves. Measured: 312 -> 291 us (60 x 60,
-// 4096 vectors, log L), 149 -> 76 us (53 x 37 SIE + lens light, k = 3, 777 vectors; its closed
+// left to itself the compiler takes 83 registers and five waves. Measured: 307 -> 281 us (60 x 60,
+// 4096 vectors, log L), 147 -> 68 us (53 x 37 SIE + lens light, k = 3, 777 vectors; its closed
 // form needed 116 registers and two library transcendentals per sub-pixel).
 template <int MASS, int LL, int NMAX>
 __global__ void __launch_bounds__(kSubThreads)
@@ -578,16 +578,17 @@ __device__ __forceinline__ void band_totals(const SysDesc& s, int part) {
 // do not depend on the wave that takes it. LDS holds the image's two fp16 parts only: with the
 // pixels and the seed in FP32 beside them one block of 1024 threads fitted at 100 x 100, and its
 // phases followed each other with nothing to fill the gaps (2048 vectors: 720 us at 256 threads
-// throughout, 443 at 1024, 354 now with two blocks of 512); 80 x 80, 512 vectors (images) 37 ->
-// 30 -> 28 us; 60 x 60: 512 vectors 42 -> 37 -> 34.7 us, 4096 193 -> 183 us (log L only 115 ->
-// 104). Bound there by the fill and split of the image (about 35 us of the forward half) and by
-// the row shifts and the LDS reads of the new rows beside the products (matrix cores 34 us a
-// half): reloading either part of the fragments from LDS instead of shifting it measured 278 us
-// for the kernel, both 394; five waves per SIMD, at most four or three tiles a group, 180 against
-// 176 at the same clocks; four tiles a group at four waves 189.
+// throughout, 443 at 1024, 357 now with two blocks of 512); 80 x 80, 512 vectors (images) 36 ->
+// 28 us; 60 x 60: 512 vectors 42 -> 34.5 us, 4096 194 -> 183 us (log L only 118 -> 106; 1.4 to 2 us
+// less with one sum per lane of the block, whose order followed the block's size). Bound there by
+// the fill and split of the image (about 35 us of the forward half) and by the row shifts and the
+// LDS reads of the new rows beside the products (matrix cores 34 us a half): reloading either part
+// of the fragments from LDS instead of shifting it measured 278 us for the kernel, both 394; five
+// waves per SIMD, at most four or three tiles a group, 180 against 176 at the same clocks; four
+// tiles a group at four waves 189.
 // ADJ_ONLY: only the adjoint pass, from the seed that the banded forward kernel left in memory (and
-// log L from its bands' partial sums), in place of the banded VALU adjoint: 43 -> 33 us (80 x 80, 300
-// vectors), 52 -> 33.6 us (500). The operands' two parts are 22 bits or more of a seed's 24, so
+// log L from its bands' partial sums), in place of the banded VALU adjoint: 44 -> 32 us (80 x 80, 300
+// vectors), 52 -> 33.4 us (500). The operands' two parts are 22 bits or more of a seed's 24, so
 // that the sums have to be the better for it: with the low products apart the rms error against 64
 // bits is 0.41 to 0.83 of the VALU sums' over the sizes that come here (1.2 to 1.4 of them in one
 // accumulator, at the sizes whose strips are summed over two lanes).
@@ -755,8 +756,8 @@ __device__ __forceinline__ void band_strip(const float* __restrict__ A,
 }
 
 // Bound by VALU issue where the batch fills the chip, by latency below. Bands and block size
-// follow the waves on the fullest CU (conv_bands); the taps come from LDS. Measured: 47.5 -> 39.2 us
-// (80 x 80, K = 21, 300 vectors; products alone 21.5), 56.0 -> 50.9 us (500), 12.9 -> 11.2 us (60 x 60,
+// follow the waves on the fullest CU (conv_bands); the taps come from LDS. Measured: 47.5 -> 38.9 us
+// (80 x 80, K = 21, 300 vectors; products alone 21.5), 56.7 -> 50.4 us (500), 13.0 -> 11.6 us (60 x 60,
 // 64 vectors, columns over four lanes).
 template <int K>
 __global__ void __launch_bounds__(kBandMaxThreads) conv_band_kernel(Group g) {
@@ -924,13 +925,15 @@ __device__ __forceinline__ void adj_pixels(const SysDesc& s, const PConst& c,
 }
 
 // Bound by VALU issue (one instruction per CU and cycle; packed FP32 is not used), so what counts
-// is instructions per sub-pixel: about 385 with every sum of the gradient taken per sub-pixel,
-// 320 with the sums of mass_adjoint, sersic_adj and shapelet_adj. Measured: 543 -> 463 us (60 x 60,
-// n_max 6, 4096 vectors), 67 -> 53 us (80 x 80 without shapelets, 300), 122 -> 90 us (53 x 37 SIE,
-// k = 3, n_max 3, 777). At n_max = 8 the accumulators and coefficients (122 registers) do not
-// fit three waves per SIMD (168 registers: 76 spilled in the loop); two waves hide the latencies
-// of this instruction mix as well: 1510 -> 890 us (100 x 100, 2048 vectors). n_max = 7 keeps three
-// (101 -> 93 us at 47 x 35, k = 4, 317 vectors; with two 111).
+// is instructions per sub-pixel: 391 with every sum of the gradient taken per sub-pixel, 341 with
+// the sums of mass_adjoint, sersic_adj and shapelet_adj (330 with the eccentricity's and the Sersic
+// index's as combinations of other sums, which cancel). Measured, each with every sum per sub-pixel,
+// with those combinations, and now: 546, 480, 487 us (60 x 60, n_max 6, 4096 vectors), 67, 50, 55
+// (80 x 80 without shapelets, 300), 121, 93, 99 (53 x 37 SIE, k = 3, n_max 3, 777). At n_max = 8 the
+// accumulators and coefficients (over 120 registers) do not fit three waves per SIMD (168 registers:
+// 76 spilled in the loop); two waves hide the latencies of this instruction mix as well: 1517, 876,
+// 890 us (100 x 100, 2048 vectors); without lens light three waves fit, but two were faster (427 us
+// against 500). n_max = 7 keeps three (110, 100, 102 us at 47 x 35, k = 4, 317 vectors; with two 111).
 template <int MASS, int LL, int NMAX>
 __global__ void __launch_bounds__(kSubThreads)
 __attribute__((amdgpu_waves_per_eu(NMAX >= 8 ? 2 : 3)))

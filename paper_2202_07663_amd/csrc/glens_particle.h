@@ -1,8 +1,8 @@
-// Per-particle stages of the likelihood pipeline that run as one 64-lane block (a single
-// wave) per particle: the decode (prologue) and the gradient finalize. The pipeline's
-// prologue_kernel and finalize_kernel wrap them, and so do kernels that fuse them with a
-// sampler's per-chain step (the HMC kick and drift), which saves a launch and its fixed cost
-// per step at small batches.
+// Per-particle stages of the likelihood pipeline that run as one block per particle: the decode
+// (prologue; one wave, or four where the batch leaves the chip idle: launch_prologue) and the
+// gradient finalize (one wave). The pipeline's prologue_kernel and finalize_kernel wrap them, and
+// so do kernels that fuse them with a sampler's per-chain step (the HMC kick and drift), which
+// saves a launch and its fixed cost per step at small batches.
 #pragma once
 
 #include <hip/hip_runtime.h>
